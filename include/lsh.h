@@ -293,7 +293,11 @@ int lsh_time_launches(const lsh_params_t *params, int which, const void *d_in, u
  *   (a stable radix sort of this library, eight passes of 8 bits, the keys read in place) and
  *   does not wait: d_keys must stay alive until the stream has passed the build, and the index
  *   may be used by later work on the same stream (or after synchronising).  A second buffer of
- *   12 bytes per pair is allocated and released in stream order.
+ *   12 bytes per pair serves as scratch.  While any index is alive on a device, the memory of
+ *   destroyed ones and of scratch is kept for the next build, up to 2 GiB; the destruction of the
+ *   last one gives it back.
+ * lsh_index_destroy: waits for the device, as hipFree does (work on any stream may still read the
+ *   tables).
  * lsh_index_tables: N, L and the device arrays sorted keys [L][N], ids in key order [L][N]
  *   (owned by the index; any out pointer may be NULL).
  * lsh_index_probe: d_qkeys [Q][L] -> d_start [Q][L], d_count [Q][L]: the bucket of query q in

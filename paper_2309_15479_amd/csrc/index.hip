@@ -19,6 +19,7 @@
 #include <mutex>
 #include <new>
 
+#include "index_memory.h"
 #include "lsh.h"
 
 struct lsh_index {
@@ -27,6 +28,7 @@ struct lsh_index {
     int device = -1;
     uint64_t *d_keys = nullptr;  // [L][N] ascending per table
     uint32_t *d_ids = nullptr;   // [L][N] vector ids in key order (ascending within equal keys)
+    lsh::IndexBlock tables;      // holds both
 };
 
 namespace {
@@ -434,20 +436,27 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
     ix->L = L;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const uint32_t tiles = (uint32_t)((N + kSortTile - 1) / kSortTile);
-    // the other half of the ping-pong, and the (digit, tile) counts of every table
+    const size_t pairs = (size_t)L * N;
+    // scratch: the other half of the ping-pong, and the (digit, tile) counts of every table
+    lsh::IndexBlock scratch;
     uint64_t *tmp_keys = nullptr;
     uint32_t *tmp_ids = nullptr, *hist = nullptr;
     int rc = LSH_OK;
-    if (hipGetDevice(&ix->device) != hipSuccess) rc = LSH_ERR_HIP;
-    if (rc == LSH_OK && hipMalloc(&ix->d_keys, (size_t)L * N * sizeof(uint64_t)) != hipSuccess) rc = LSH_ERR_ALLOC;
-    if (rc == LSH_OK && hipMalloc(&ix->d_ids, (size_t)L * N * sizeof(uint32_t)) != hipSuccess) rc = LSH_ERR_ALLOC;
-    // temporaries are allocated and released in stream order: the host does not wait for the sort
-    if (rc == LSH_OK && hipMallocAsync(reinterpret_cast<void **>(&tmp_keys), (size_t)L * N * sizeof(uint64_t), s) != hipSuccess)
+    if (hipGetDevice(&ix->device) != hipSuccess) {
+        delete ix;
+        return LSH_ERR_HIP;
+    }
+    lsh::index_memory_enter(ix->device);
+    if (!lsh::index_memory_take(ix->device, pairs * 12, false, s, ix->tables)) rc = LSH_ERR_ALLOC;
+    if (rc == LSH_OK && !lsh::index_memory_take(ix->device, pairs * 12 + (size_t)L * 256 * tiles * 4, true, s, scratch))
         rc = LSH_ERR_ALLOC;
-    if (rc == LSH_OK && hipMallocAsync(reinterpret_cast<void **>(&tmp_ids), (size_t)L * N * sizeof(uint32_t), s) != hipSuccess)
-        rc = LSH_ERR_ALLOC;
-    if (rc == LSH_OK && hipMallocAsync(reinterpret_cast<void **>(&hist), (size_t)L * 256 * tiles * sizeof(uint32_t), s) != hipSuccess)
-        rc = LSH_ERR_ALLOC;
+    if (rc == LSH_OK) {
+        ix->d_keys = static_cast<uint64_t *>(ix->tables.ptr);
+        ix->d_ids = reinterpret_cast<uint32_t *>(ix->d_keys + pairs);
+        tmp_keys = static_cast<uint64_t *>(scratch.ptr);
+        tmp_ids = reinterpret_cast<uint32_t *>(tmp_keys + pairs);
+        hist = tmp_ids + pairs;
+    }
     if (rc == LSH_OK) {
         const dim3 grid(tiles, L), block(kSortThreads);
         // eight passes; odd passes write the index's own arrays, so the last one ends there
@@ -472,9 +481,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
         }
         if (hipGetLastError() != hipSuccess) rc = LSH_ERR_HIP;
     }
-    if (tmp_keys) (void)hipFreeAsync(tmp_keys, s);
-    if (tmp_ids) (void)hipFreeAsync(tmp_ids, s);
-    if (hist) (void)hipFreeAsync(hist, s);
+    lsh::index_memory_give_scratch(ix->device, scratch, s);
     if (rc != LSH_OK) {
         (void)hipStreamSynchronize(s);
         (void)hipGetLastError();
@@ -490,8 +497,10 @@ void lsh_index_destroy(lsh_index_t *ix) {
     int prev = -1;  // the tables live on the device the index was built on
     const bool switched = ix->device >= 0 && hipGetDevice(&prev) == hipSuccess && prev != ix->device &&
                           hipSetDevice(ix->device) == hipSuccess;
-    if (ix->d_keys) (void)hipFree(ix->d_keys);
-    if (ix->d_ids) (void)hipFree(ix->d_ids);
+    // work on any stream may still read the tables: wait for the device, as hipFree does
+    if (hipDeviceSynchronize() == hipSuccess) lsh::index_memory_give(ix->device, ix->tables);
+    else (void)hipFree(ix->tables.ptr);
+    lsh::index_memory_leave(ix->device);
     if (switched) (void)hipSetDevice(prev);
     delete ix;
 }

@@ -1,0 +1,90 @@
+"""Building an index: the tables are the stable sort of every column of keys, whatever the memory
+they are built in was used for before."""
+import ctypes
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lsh():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2309_15479_amd as lib
+    lib.load_library()
+    return lib
+
+
+class _View:
+    def __init__(self, address, shape, kind):
+        self.__cuda_array_interface__ = {"data": (address, False), "shape": shape, "typestr": kind, "version": 2}
+
+
+def _tables(lsh, ix):
+    """Copies of the sorted keys [L, N] (signed views of the unsigned keys) and the ids."""
+    keys, ids = ctypes.c_void_p(), ctypes.c_void_p()
+    assert lsh.load_library().lsh_index_tables(ix.handle, None, None, ctypes.byref(keys), ctypes.byref(ids)) == 0
+    shape = (ix.L, ix.N)
+    return (torch.as_tensor(_View(keys.value, shape, "<i8"), device="cuda").clone(),
+            torch.as_tensor(_View(ids.value, shape, "<i4"), device="cuda").clone())
+
+
+def _check(lsh, ix, keys, label):
+    got_keys, got_ids = _tables(lsh, ix)
+    # unsigned order: flip the sign bit, sort as signed numbers
+    flipped = keys.t().contiguous() ^ torch.tensor(-2 ** 63, device="cuda")
+    want, order = torch.sort(flipped, dim=1, stable=True)
+    assert torch.equal(got_keys, want ^ torch.tensor(-2 ** 63, device="cuda")), label
+    assert torch.equal(got_ids.long(), order), label
+
+
+def _random_keys(N, L, distinct, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    pool = torch.randint(-2 ** 63, 2 ** 63 - 1, (distinct, L), generator=g, device="cuda")
+    return torch.gather(pool, 0, torch.randint(0, distinct, (N, L), generator=g, device="cuda"))
+
+
+def test_tables_built_in_memory_of_earlier_indexes(lsh):
+    """Indexes of several sizes built, used and dropped in turn: each must be whole while others come
+    and go in the memory that earlier ones and their scratch left behind."""
+    alive = []
+    for i, (N, L) in enumerate([(5000, 3), (70000, 4), (5000, 3), (300, 40), (70000, 4), (68000, 4), (1, 1), (90000, 2)]):
+        print(f"index {i}: N={N} L={L}", flush=True)
+        keys = _random_keys(N, L, max(1, N // 3), i)
+        alive.append((lsh.LshIndex(keys), keys))
+        if len(alive) == 3:
+            alive.pop(0)[0].close()
+        for ix, k in alive:
+            _check(lsh, ix, k, f"index {i}")
+    for ix, _ in alive:
+        ix.close()
+
+
+def test_indexes_built_by_several_threads_and_streams(lsh):
+    sizes = [(40000, 4), (40000, 4), (36000, 4), (9000, 7)]
+    keys = [_random_keys(N, L, N // 2, 50 + i) for i, (N, L) in enumerate(sizes)]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(6):
+                    with lsh.LshIndex(keys[i]) as ix:
+                        _check(lsh, ix, keys[i], f"thread {i}")
+        except BaseException as e:      # noqa: BLE001 -- reported by the main thread
+            bad.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sizes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
