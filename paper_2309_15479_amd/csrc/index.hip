@@ -33,30 +33,52 @@ struct lsh_index {
 
 namespace {
 
-// one thread per (query, table): lower and upper bound of the query's key in the table
-__global__ void probe_kernel(const uint64_t *__restrict__ sorted_keys, uint64_t N, uint32_t L,
-                             const uint64_t *__restrict__ qkeys, uint64_t items, uint32_t *__restrict__ start,
-                             uint32_t *__restrict__ count) {
-    const uint64_t item = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (item >= items) return;
-    const uint32_t l = (uint32_t)(item % L);
-    const uint64_t key = qkeys[item];
-    const uint64_t *table = sorted_keys + (uint64_t)l * N;
-    uint64_t lo = 0, hi = N;  // first position with table[pos] >= key
+// A group of LANES lanes per (query, table): lower and upper bound of the query's key in the table.
+// A group reads LANES keys spread over its range at a time, which leaves one of LANES + 1 parts of
+// it, and looks for the end of a bucket right behind its beginning first.  Few lookups are bound
+// by the chain of dependent reads, many by the number of separate lines read, hence two sizes.
+// Tables of 1e5 keys, one lane (halving, both ends from scratch) / 2 / 4 / 8 / 16 lanes: 512 lookups
+// 7.1, 4.5, 4.0, 3.7, 3.7 us; 16384 lookups 13.5, 6.2, 5.3, 5.4, 6.5 us; 64000 lookups 24.7, 12.4, 14.5,
+// 17.8, 20.2 us; 256000 lookups 87, 41, 49, 57, 67 us.
+constexpr uint64_t kFewLookups = 16384;
+constexpr uint32_t kFewLanes = 8, kManyLanes = 2;
+
+// within positions [lo, hi) of an ascending table: the first one whose key is not below `key` (UPPER: is above it)
+template <uint32_t LANES, bool UPPER>
+__device__ __forceinline__ uint32_t group_bound(const uint64_t *__restrict__ table, uint32_t lo, uint32_t hi, uint64_t key) {
+    constexpr uint64_t kMask = (1u << LANES) - 1;
+    const uint32_t lane = threadIdx.x & (LANES - 1), first_lane = threadIdx.x & (63u & ~(LANES - 1));
     while (lo < hi) {
-        const uint64_t mid = (lo + hi) / 2;
-        if (table[mid] < key) lo = mid + 1;
-        else hi = mid;
+        const uint32_t len = hi - lo, part = len / (LANES + 1);
+        auto at = [&](uint32_t i) { return lo + (part ? part * (i + 1) : i < len ? i : len - 1); };  // ascending, below hi
+        const uint64_t have = table[at(lane)];
+        const uint32_t before = __popcll((__ballot(UPPER ? have <= key : have < key) >> first_lane) & kMask);
+        const uint32_t end = before < LANES ? at(before) : hi;
+        if (before) lo = at(before - 1) + 1;
+        hi = end;
     }
-    const uint64_t first = lo;
-    hi = N;  // first position with table[pos] > key
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) / 2;
-        if (table[mid] <= key) lo = mid + 1;
-        else hi = mid;
+    return lo;
+}
+
+template <uint32_t LANES>
+__global__ __launch_bounds__(256) void probe_kernel(const uint64_t *__restrict__ sorted_keys, uint64_t N, uint32_t L,
+                                                    const uint64_t *__restrict__ qkeys, uint64_t items,
+                                                    uint32_t *__restrict__ start, uint32_t *__restrict__ count) {
+    constexpr uint64_t kMask = (1u << LANES) - 1;
+    const uint32_t lane = threadIdx.x & (LANES - 1), first_lane = threadIdx.x & (63u & ~(LANES - 1));
+    const uint64_t groups = (uint64_t)gridDim.x * (blockDim.x / LANES);
+    for (uint64_t item = (blockIdx.x * (uint64_t)blockDim.x + threadIdx.x) / LANES; item < items; item += groups) {
+        const uint64_t key = qkeys[item];
+        const uint64_t *table = sorted_keys + (item % L) * N;
+        const uint32_t first = group_bound<LANES, false>(table, 0, (uint32_t)N, key);
+        const bool same = first + lane < N && table[first + lane] == key;  // positions are below 2^31
+        uint32_t end = first + __popcll((__ballot(same) >> first_lane) & kMask);
+        if (end == first + LANES) end = group_bound<LANES, true>(table, end, (uint32_t)N, key);
+        if (lane == 0) {
+            start[item] = first;
+            count[item] = end - first;
+        }
     }
-    start[item] = (uint32_t)first;
-    count[item] = (uint32_t)(lo - first);
 }
 
 // Exclusive prefix sum of 32-bit counts into 64-bit offsets, three small launches: (1) every
@@ -348,58 +370,167 @@ __global__ void candidates_kernel(const uint32_t *__restrict__ sorted_ids, uint6
     }
 }
 
-// one workgroup per query: squared l2 distance of every candidate of its L buckets (a candidate
-// met in several tables is simply evaluated again), minimum with ties to the smaller id.
+// One workgroup per query: squared l2 distance of every distinct candidate of its L buckets,
+// minimum with ties to the smaller id.
 // INNER: the score is the inner product with the query instead and the largest one wins
 // (maximum inner product search; internally the negated product is minimised).
-template <bool INNER>
-__global__ __launch_bounds__(256) void nearest_kernel(const uint32_t *__restrict__ sorted_ids, uint64_t N, uint32_t L,
-                                                      const float *__restrict__ data, const float *__restrict__ queries,
-                                                      uint32_t n, const uint32_t *__restrict__ start,
-                                                      const uint32_t *__restrict__ count, uint32_t max_candidates,
-                                                      uint32_t *__restrict__ best_id, float *__restrict__ best_dist) {
-    extern __shared__ float query[];  // [n], then per-wave results
+// The work is reading the candidates' vectors, so the kernel first lays out which ones: the
+// positions of the combined list are dealt to all threads (a prefix sum over the bucket lengths
+// says which bucket a position is in), and an id goes on the list in LDS unless it is among those
+// met before (a table of 2048 slots in LDS; an id that finds no slot in a few tries is simply
+// evaluated again, which changes nothing).  The list is then evaluated by groups of lanes, as many
+// as a vector has pieces of VEC coordinates (at most a wave), four candidates in flight in each.
+// VEC = 4 (16-byte loads) for vectors and queries on 16-byte boundaries with n a multiple of 4.
+// QUERY_IN_LDS up to kQueryInLds coordinates (all of the LDS used stays below 64 KB).
+// 1000 queries against 1e5 vectors of 960 dimensions, every candidate of 64 buckets: 1028 -> 70 us
+// (one wave a candidate, 4-byte loads, one in flight, repeats evaluated again -> this).
+constexpr uint32_t kListIds = 1024, kSeenSlots = 2048, kSeenTries = 4, kBucketsAtOnce = 256, kQueryInLds = 11264;
+constexpr uint32_t kNearestThreads = 1024, kNoId = 0xFFFFFFFFu;
+
+template <int VEC>
+struct Piece {
+    float x[VEC];
+};
+
+template <int VEC>
+__device__ __forceinline__ Piece<VEC> read_piece(const float *at) {
+    Piece<VEC> r;
+    if constexpr (VEC == 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(at);
+        r.x[0] = v.x, r.x[1] = v.y, r.x[2] = v.z, r.x[3] = v.w;
+    } else {
+        r.x[0] = *at;
+    }
+    return r;
+}
+
+template <bool INNER, int VEC, bool QUERY_IN_LDS>
+__global__ __launch_bounds__(kNearestThreads) void nearest_kernel(
+    const uint32_t *__restrict__ sorted_ids, uint64_t N, uint32_t L, const float *__restrict__ data,
+    const float *__restrict__ queries, uint32_t n, uint32_t group_lanes, const uint32_t *__restrict__ start,
+    const uint32_t *__restrict__ count, uint32_t max_candidates, uint32_t *__restrict__ best_id,
+    float *__restrict__ best_dist) {
+    extern __shared__ __align__(16) float query_lds[];  // [n] when QUERY_IN_LDS
+    __shared__ uint64_t bucket_end[kBucketsAtOnce];     // positions up to the end of the bucket, from the first of these buckets
+    __shared__ uint32_t bucket_first[kBucketsAtOnce];
+    __shared__ uint64_t wave_sums[kBucketsAtOnce / 64];
+    __shared__ uint32_t seen[kSeenSlots];
+    __shared__ uint32_t list[kListIds];
+    __shared__ uint32_t listed;
+    __shared__ float wave_d[kNearestThreads / 64];
+    __shared__ uint32_t wave_id[kNearestThreads / 64];
     const uint64_t q = blockIdx.x;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    for (uint32_t c = threadIdx.x; c < n; c += blockDim.x) query[c] = queries[q * n + c];
-    __syncthreads();
+    const uint32_t tid = threadIdx.x, threads = blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const float *query = queries + q * n;
+    if constexpr (QUERY_IN_LDS) {
+        for (uint32_t c = tid * VEC; c < n; c += threads * VEC) {
+            const Piece<VEC> p = read_piece<VEC>(query + c);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) query_lds[c + e] = p.x[e];
+        }
+    }
+    for (uint32_t i = tid; i < kSeenSlots; i += threads) seen[i] = kNoId;
+    if (tid == 0) listed = 0;
     float mine_d = INFINITY;
-    uint32_t mine_id = 0xFFFFFFFFu;
-    uint32_t seen = 0;  // candidates are dealt to the waves round-robin over all L buckets
-    for (uint32_t l = 0; l < L && seen < max_candidates; ++l) {
-        const uint32_t first = start[q * L + l];
-        uint32_t len = count[q * L + l];
-        if (len > max_candidates - seen) len = max_candidates - seen;  // only the first max_candidates of the list
-        const uint32_t *bucket = sorted_ids + (uint64_t)l * N + first;
-        for (uint32_t i = (wave + waves - seen % waves) % waves; i < len; i += waves) {
-            const uint32_t id = bucket[i];
-            const float *v = data + (uint64_t)id * n;
-            float acc = 0.f;
-            for (uint32_t c = lane; c < n; c += 64) {
-                if constexpr (INNER) {
-                    acc = fmaf(-v[c], query[c], acc);
-                } else {
-                    const float d = v[c] - query[c];
-                    acc = fmaf(d, d, acc);
+    uint32_t mine_id = kNoId;
+    uint64_t left = max_candidates;  // of the combined list, still to be looked at
+    for (uint32_t l0 = 0; l0 < L && left; l0 += kBucketsAtOnce) {
+        uint64_t incl = 0;
+        if (tid < kBucketsAtOnce) {
+            const uint32_t l = l0 + tid;
+            incl = l < L ? count[q * L + l] : 0;
+            bucket_first[tid] = l < L ? start[q * L + l] : 0;
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t up = __shfl_up(incl, d);
+                if (lane >= (uint32_t)d) incl += up;
+            }
+            if (lane == 63) wave_sums[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < kBucketsAtOnce) {
+            for (uint32_t w = 0; w < wave; ++w) incl += wave_sums[w];
+            bucket_end[tid] = incl;
+        }
+        __syncthreads();
+        const uint64_t all = bucket_end[kBucketsAtOnce - 1], total = all < left ? all : left;
+        for (uint64_t base = 0; base < total; base += kListIds) {
+            const uint64_t stop = total - base < kListIds ? total : base + kListIds;
+            for (uint64_t pos = base + tid; pos < stop; pos += threads) {
+                uint32_t b = 0;  // first bucket that ends behind pos
+                for (uint32_t half = kBucketsAtOnce / 2; half; half >>= 1)
+                    if (bucket_end[b + half - 1] <= pos) b += half;
+                const uint64_t before = b ? bucket_end[b - 1] : 0;
+                const uint32_t id = sorted_ids[(uint64_t)(l0 + b) * N + bucket_first[b] + (pos - before)];
+                bool fresh = true;
+                uint32_t slot = (id * 0x9E3779B1u) >> 21;
+                for (uint32_t t = 0; t < kSeenTries; ++t) {
+                    const uint32_t was = atomicCAS(&seen[slot], kNoId, id);
+                    if (was == id) fresh = false;
+                    if (was == id || was == kNoId) break;
+                    slot = (slot + 1) & (kSeenSlots - 1);
+                }
+                if (fresh) list[atomicAdd(&listed, 1u)] = id;
+            }
+            __syncthreads();
+            const uint32_t have = listed;
+            const uint32_t groups = threads / group_lanes, group = tid / group_lanes, piece0 = tid & (group_lanes - 1);
+            for (uint32_t e0 = group; e0 < have; e0 += 4 * groups) {
+                uint32_t id[4];
+                const float *v[4];
+                float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) {
+                    const uint32_t e = e0 + u * groups;
+                    id[u] = list[e < have ? e : have - 1];
+                    v[u] = data + (uint64_t)id[u] * n;
+                }
+                for (uint32_t c = piece0 * VEC; c < n; c += group_lanes * VEC) {
+                    Piece<VEC> x[4];
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) x[u] = read_piece<VEC>(v[u] + c);
+                    const Piece<VEC> y = read_piece<VEC>((QUERY_IN_LDS ? query_lds : query) + c);
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) {
+                            if constexpr (INNER) {
+                                acc[u] = fmaf(-x[u].x[e], y.x[e], acc[u]);
+                            } else {
+                                const float d = x[u].x[e] - y.x[e];
+                                acc[u] = fmaf(d, d, acc[u]);
+                            }
+                        }
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) {
+                    for (uint32_t s = group_lanes / 2; s > 0; s >>= 1) acc[u] += __shfl_xor(acc[u], s);
+                    if (acc[u] < mine_d || (acc[u] == mine_d && id[u] < mine_id)) {  // the last one again: no change
+                        mine_d = acc[u];
+                        mine_id = id[u];
+                    }
                 }
             }
-            for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-            if (acc < mine_d || (acc == mine_d && id < mine_id)) {
-                mine_d = acc;
-                mine_id = id;
-            }
+            __syncthreads();  // the list has been read
+            if (tid == 0) listed = 0;
+            __syncthreads();
         }
-        seen += len;
+        left -= total;
     }
-    float *wave_d = query + n;
-    uint32_t *wave_id = reinterpret_cast<uint32_t *>(wave_d + waves);
+    for (uint32_t s = 32; s > 0; s >>= 1) {
+        const float d = __shfl_xor(mine_d, s);
+        const uint32_t id = __shfl_xor(mine_id, s);
+        if (d < mine_d || (d == mine_d && id < mine_id)) {
+            mine_d = d;
+            mine_id = id;
+        }
+    }
     if (lane == 0) {
         wave_d[wave] = mine_d;
         wave_id[wave] = mine_id;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (uint32_t w = 1; w < waves; ++w)
+    if (tid == 0) {
+        for (uint32_t w = 1; w < threads / 64; ++w)
             if (wave_d[w] < mine_d || (wave_d[w] == mine_d && wave_id[w] < mine_id)) {
                 mine_d = wave_d[w];
                 mine_id = wave_id[w];
@@ -407,6 +538,31 @@ __global__ __launch_bounds__(256) void nearest_kernel(const uint32_t *__restrict
         best_id[q] = mine_id;
         best_dist[q] = INNER ? -mine_d : mine_d;  // no candidate: +inf distance, -inf inner product
     }
+}
+
+template <bool INNER>
+void launch_nearest(const lsh_index *ix, const float *d_data, const float *d_queries, uint32_t n, const uint32_t *d_start,
+                    const uint32_t *d_count, uint64_t Q, uint32_t limit, uint32_t *d_best_id, float *d_best_score,
+                    hipStream_t s) {
+    const bool pieces4 = n % 4 == 0 && ((reinterpret_cast<uintptr_t>(d_data) | reinterpret_cast<uintptr_t>(d_queries)) & 15) == 0;
+    const uint32_t pieces = pieces4 ? n / 4 : n;
+    uint32_t group_lanes = 8;
+    while (group_lanes < 64 && group_lanes < pieces) group_lanes *= 2;
+    // Few queries leave the chip idle: a workgroup as large as can be for each then.  Many fill it by
+    // themselves, and what a workgroup spends around its candidates weighs more.  With 256, 512, 1024
+    // threads, hashing and lookup included: 88, 74, 69 us for 100 queries of 960 dimensions and every
+    // candidate, 107, 99, 102 us for 512 of them, 141, 143, 150 us for 1000; 96 candidates of 128
+    // dimensions for 4000 queries 121, 138, 187 us.
+    const uint32_t threads = Q <= 256 ? kNearestThreads : Q < 1000 ? kNearestThreads / 2 : kNearestThreads / 4;
+    auto launch = [&](auto kernel, uint32_t lds) {
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)Q), dim3(threads), lds, s, ix->d_ids, ix->N, ix->L, d_data, d_queries, n,
+                           group_lanes, d_start, d_count, limit, d_best_id, d_best_score);
+    };
+    const bool in_lds = n <= kQueryInLds;
+    if (pieces4 && in_lds) launch(nearest_kernel<INNER, 4, true>, n * 4);
+    else if (pieces4) launch(nearest_kernel<INNER, 4, false>, 0);
+    else if (in_lds) launch(nearest_kernel<INNER, 1, true>, n * 4);
+    else launch(nearest_kernel<INNER, 1, false>, 0);
 }
 
 int on_index_device(const lsh_index *ix) {
@@ -523,8 +679,14 @@ int lsh_index_probe(const lsh_index_t *ix, const uint64_t *d_qkeys, uint64_t Q, 
     int rc = on_index_device(ix);
     if (rc != LSH_OK) return rc;
     const uint64_t items = Q * ix->L;
-    hipLaunchKernelGGL(probe_kernel, dim3((uint32_t)((items + 255) / 256)), dim3(256), 0,
-                       reinterpret_cast<hipStream_t>(stream), ix->d_keys, ix->N, ix->L, d_qkeys, items, d_start, d_count);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    auto launch = [&](auto kernel, uint32_t lanes) {
+        const uint64_t wanted = (items * lanes + 255) / 256;  // one group per item, up to 2^20 workgroups
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)(wanted < (1u << 20) ? wanted : (1u << 20))), dim3(256), 0, s, ix->d_keys,
+                           ix->N, ix->L, d_qkeys, items, d_start, d_count);
+    };
+    if (items <= kFewLookups) launch(probe_kernel<kFewLanes>, kFewLanes);
+    else launch(probe_kernel<kManyLanes>, kManyLanes);
     return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
 }
 
@@ -571,18 +733,13 @@ static int best_candidate(bool inner, const lsh_index_t *ix, const float *d_data
     if (Q == 0) return LSH_OK;
     if (!d_data || !d_queries || !d_start || !d_count || !d_best_id || !d_best_score) return LSH_ERR_INVALID_ARG;
     if (Q >= (1ull << 31)) return LSH_ERR_INVALID_ARG;
-    if ((uint64_t)n * 4 + 64 > 64 * 1024) return LSH_ERR_UNSUPPORTED;  // the query is kept in LDS
+    if ((uint64_t)n * 4 + 64 > 64 * 1024) return LSH_ERR_UNSUPPORTED;
     int rc = on_index_device(ix);
     if (rc != LSH_OK) return rc;
-    const uint32_t lds = n * 4 + 4 * 8;
     const uint32_t limit = max_candidates ? max_candidates : 0xFFFFFFFFu;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (inner)
-        hipLaunchKernelGGL(nearest_kernel<true>, dim3((uint32_t)Q), dim3(256), lds, s, ix->d_ids, ix->N, ix->L, d_data,
-                           d_queries, n, d_start, d_count, limit, d_best_id, d_best_score);
-    else
-        hipLaunchKernelGGL(nearest_kernel<false>, dim3((uint32_t)Q), dim3(256), lds, s, ix->d_ids, ix->N, ix->L, d_data,
-                           d_queries, n, d_start, d_count, limit, d_best_id, d_best_score);
+    if (inner) launch_nearest<true>(ix, d_data, d_queries, n, d_start, d_count, Q, limit, d_best_id, d_best_score, s);
+    else launch_nearest<false>(ix, d_data, d_queries, n, d_start, d_count, Q, limit, d_best_id, d_best_score, s);
     return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
 }
 
