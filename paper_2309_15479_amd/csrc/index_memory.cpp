@@ -62,6 +62,17 @@ void index_memory_leave(int device) {
 bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t stream, IndexBlock &out) {
     bytes = (bytes + 65535) / 65536 * 65536;
     Idle found = {};
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        // work recorded now runs when its graph does, later and any number of times: it gets no
+        // block that others use in between, and what the runtime refuses to a capture is refused
+        out.stream_ordered = scratch;
+        out.bytes = bytes;
+        if ((scratch ? hipMallocAsync(&out.ptr, bytes, stream) : hipMalloc(&out.ptr, bytes)) == hipSuccess) return true;
+        (void)hipGetLastError();
+        out = IndexBlock();
+        return false;
+    }
     {
         std::lock_guard<std::mutex> lock(mu);
         DeviceMemory &m = memory[device];

@@ -1,6 +1,9 @@
 """Building an index: the tables are the stable sort of every column of keys, whatever the memory
 they are built in was used for before."""
 import ctypes
+import os
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -88,3 +91,30 @@ def test_indexes_built_by_several_threads_and_streams(lsh):
     for t in threads:
         t.join()
     assert not bad, bad
+
+
+_CAPTURE = """
+import torch
+import paper_2309_15479_amd as lsh
+keys = torch.randint(0, 5000, (20000, 3), device="cuda")
+other = lsh.LshIndex(keys)
+lsh.LshIndex(keys).close()
+torch.cuda.synchronize()
+try:
+    with torch.cuda.graph(torch.cuda.CUDAGraph()):
+        try:
+            built = lsh.LshIndex(keys)
+            print("built", flush=True)
+        except lsh.LshError:
+            print("refused", flush=True)
+except RuntimeError:
+    pass
+"""
+
+
+def test_build_is_refused_under_capture(lsh):
+    """Memory that earlier builds left must not make a capture take what it may not hold (in a process
+    of its own: the refused call invalidates the capture and what the stream does after it)."""
+    r = subprocess.run([sys.executable, "-c", _CAPTURE], capture_output=True, text=True, timeout=100,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert "refused" in r.stdout and "built" not in r.stdout, r.stdout + r.stderr
