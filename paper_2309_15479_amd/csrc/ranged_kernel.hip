@@ -141,13 +141,16 @@ __device__ __forceinline__ void gather_quad(const uint4 c, const uint2 o, float 
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// FPT functions per lane, QPF quads of each per list block
-template <int FPT, int QPF, int EP>
+// SETS functions per lane in the lists, QPF quads of each per list block.  SPLIT: a workgroup takes
+// one of the SETS (blockIdx.z) out of the same lists; else all of them (see launch_ranged).
+template <int SETS, int QPF, int EP, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledArgs a,
                                                                   const uint32_t *__restrict__ barriers,
                                                                   const uint2 *__restrict__ streams) {
     extern __shared__ __align__(16) char lds[];  // [8 ring slots][4 sub-tiles][256 coordinates] x 16 bytes
+    constexpr int FPT = SPLIT ? 1 : SETS;  // functions of a lane here
     constexpr int U = FPT * QPF;
+    const uint32_t first_set = SPLIT ? blockIdx.z : 0;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t n = a.n, R = a.nchunks, stages = a.stages;
@@ -230,8 +233,8 @@ __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledA
     // ---- gathering waves
     const uint32_t stream_id = blockIdx.y * kCW + wave;
     const uint2 si = streams[stream_id];  // {first block, blocks per tile}
-    // a block in memory: U x 64 lanes x 16 bytes of coefficients, then U x 64 x 8 bytes of offsets
-    constexpr uint32_t kBlockWords = U * 64 * 6;
+    // a block in memory: SETS x QPF x 64 lanes x 16 bytes of coefficients, then as many times 8 bytes of offsets
+    constexpr uint32_t kQuads = SETS * QPF, kBlockWords = kQuads * 64 * 6;
     const uint32_t *sbase = reinterpret_cast<const uint32_t *>(a.triples) + (size_t)si.x * kBlockWords;
     const uint32_t sblocks = si.y;
     // barriers to pass before the first block of a tile and after each of its blocks
@@ -243,15 +246,16 @@ __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledA
         const uint32_t *src = sbase + (size_t)next_block * kBlockWords;
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            blk.coef[i] = *reinterpret_cast<const uint4 *>(src + (i * 64 + lane) * 4);
-            blk.off[i] = *reinterpret_cast<const uint2 *>(src + U * 64 * 4 + (i * 64 + lane) * 2);
+            const uint32_t at = (first_set * QPF + i) * 64 + lane;
+            blk.coef[i] = *reinterpret_cast<const uint4 *>(src + at * 4);
+            blk.off[i] = *reinterpret_cast<const uint2 *>(src + kQuads * 64 * 4 + at * 2);
         }
         next_block = next_block + 1 == sblocks ? 0 : next_block + 1;
     };
     load_block(P);
 
     // function of this lane in set f: sets are kCW apart
-    const uint32_t j0 = (blockIdx.y * kCW * FPT + wave) * 64 + lane;
+    const uint32_t j0 = ((blockIdx.y * SETS + first_set) * kCW + wave) * 64 + lane;
     float bias[FPT];
     uint64_t key_pow[FPT];
 #pragma unroll
@@ -447,17 +451,21 @@ int launch_ranged(const lsh_params *p, Epilogue ep, const float *d_data, uint64_
     uint64_t gx = (uint64_t)p->num_cus / pl.kblocks;
     gx = gx < 8 ? 8 : gx / 8 * 8;
     if (gx > ntiles) gx = ntiles;
-    const dim3 grid((uint32_t)gx, pl.kblocks);
+    // Few tiles leave CUs idle: the sets of functions of a lane are then dealt to workgroups of their own,
+    // which bring the tile in once each, as long as every one of them still has a CU.  Keys of 4096 dimensions,
+    // 2048 functions (four a lane): 100 vectors at m = 64 40.9 -> 18.0 us, 1024 vectors (256 workgroups) 41.2 -> 20.0
+    // at m = 64 and 96 -> 39 at m = 256; 16 vectors of 16384 dimensions at m = 512 186 -> 72.
+    const bool split = pl.fpt > 1 && ntiles * pl.kblocks * pl.fpt <= (uint64_t)p->num_cus;
+    const dim3 grid((uint32_t)gx, pl.kblocks, split ? pl.fpt : 1);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+#define LSH_RANGED_CASE(F_, Q_, EP_) \
+    case F_ * 8 + Q_: \
+        if (split) return launch(&sampled_ranged_kernel<F_, Q_, EP_, (F_ > 1)>, a, grid, s); \
+        return launch(&sampled_ranged_kernel<F_, Q_, EP_, false>, a, grid, s);
 #define LSH_RANGED_FPT(EP_) \
     switch (pl.fpt * 8 + pl.qpf) { \
-        case 1 * 8 + 1: return launch(&sampled_ranged_kernel<1, 1, EP_>, a, grid, s); \
-        case 1 * 8 + 2: return launch(&sampled_ranged_kernel<1, 2, EP_>, a, grid, s); \
-        case 1 * 8 + 4: return launch(&sampled_ranged_kernel<1, 4, EP_>, a, grid, s); \
-        case 2 * 8 + 1: return launch(&sampled_ranged_kernel<2, 1, EP_>, a, grid, s); \
-        case 2 * 8 + 2: return launch(&sampled_ranged_kernel<2, 2, EP_>, a, grid, s); \
-        case 3 * 8 + 1: return launch(&sampled_ranged_kernel<3, 1, EP_>, a, grid, s); \
-        case 4 * 8 + 1: return launch(&sampled_ranged_kernel<4, 1, EP_>, a, grid, s); \
+        LSH_RANGED_CASE(1, 1, EP_) LSH_RANGED_CASE(1, 2, EP_) LSH_RANGED_CASE(1, 4, EP_) LSH_RANGED_CASE(2, 1, EP_) \
+        LSH_RANGED_CASE(2, 2, EP_) LSH_RANGED_CASE(3, 1, EP_) LSH_RANGED_CASE(4, 1, EP_) \
         default: return LSH_ERR_UNSUPPORTED; \
     }
     switch (ep) {
@@ -468,6 +476,7 @@ int launch_ranged(const lsh_params *p, Epilogue ep, const float *d_data, uint64_
         default: LSH_RANGED_FPT((int)Epilogue::Keys)
     }
 #undef LSH_RANGED_FPT
+#undef LSH_RANGED_CASE
 }
 
 }  // namespace lsh
