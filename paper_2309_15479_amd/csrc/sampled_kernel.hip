@@ -39,11 +39,12 @@ constexpr int kChunk = 32;                     // samples held in registers at a
 constexpr uint32_t kLdsBudget = 158u * 1024u;  // of the CU's 160 KB
 
 // Streamed-list kernel: every tile, each lane streams its (offset, coefficient) list through
-// registers one chunk at a time and applies the chunk to all SUB sub-tiles.
-template <int RT, int SUB, int EP>
+// registers one chunk at a time and applies the chunk to all SUB sub-tiles.  The lists are made for
+// tiles of SLOTS sub-tiles; launches of few vectors use fewer of them (see launch_sampled).
+template <int RT, int SUB, int EP, int SLOTS = SUB>
 __global__ __launch_bounds__(1024) void sampled_kernel(const SampledArgs a) {
     extern __shared__ __align__(16) float tile[];  // [n + classes][SP][RT]
-    constexpr uint32_t SP = SUB == 1 ? 1 : SUB + 1;
+    constexpr uint32_t SP = SLOTS == 1 ? 1 : SLOTS + 1;
     constexpr uint32_t kTileRows = RT * SUB;
     const uint32_t n = a.n;
     const uint32_t j = blockIdx.y * blockDim.x + threadIdx.x;  // < kpad
@@ -451,7 +452,21 @@ int launch_sampled(const lsh_params *p, Epilogue ep, const float *d_data, uint64
     a.g = L ? p->k / L : 1;
     a.buf_floats = pl.lds_bytes / 4;
     a.copy_b_floats = pl.copies == 2 ? (p->n + pl.classes) * pl.sp * pl.rt : 0;
-    const uint64_t tile_rows = (uint64_t)pl.rt * pl.sub;
+    // Streamed lists and few vectors: a whole tile for every CU would leave most of them idle, and a CU is
+    // bound by its own multiply-adds.  A workgroup then takes a quarter of a tile (two sub-tiles of eight, one
+    // of four) and, while CUs are left, half or a quarter of the functions.  Keys of 960 dimensions, 1024
+    // functions, m = 128 (tiles of 32 vectors): 100 vectors 43.4 -> 12.7 us, 1000 43.8 -> 16.1, 4000 (the last
+    // 125 tiles that are cut) 45.9 -> 42.0.
+    uint32_t sub = pl.sub, threads = pl.block, kblocks = pl.kblocks;
+    if (!pl.reg_table && pl.rt == 4 && N) {
+        auto workgroups = [&] { return (N + 4 * sub - 1) / (4 * sub) * kblocks; };
+        if (sub >= 4 && workgroups() * 2 <= (uint64_t)p->num_cus) sub /= 4;
+        while (threads % 128 == 0 && threads > 256 && workgroups() * 2 <= (uint64_t)p->num_cus) {
+            threads /= 2;
+            kblocks *= 2;
+        }
+    }
+    const uint64_t tile_rows = (uint64_t)pl.rt * sub;
     const uint64_t ntiles = (N + tile_rows - 1) / tile_rows;
     // persistent workgroups: as many per CU as LDS and waves allow (at most 2048 lanes), count
     // a multiple of 8 so that the kblocks workgroups sharing a vector tile land on one XCD
@@ -460,13 +475,13 @@ int launch_sampled(const lsh_params *p, Epilogue ep, const float *d_data, uint64
     // register-list kernel: 4 waves per SIMD (128 VGPRs per lane; 2 and 256 with two list
     // chunks), else 8
     const uint32_t by_lanes =
-        (pl.reg_table ? (pl.m_pad == (uint32_t)kChunk ? 1024 : 512) : 2048) / pl.block;
+        (pl.reg_table ? (pl.m_pad == (uint32_t)kChunk ? 1024 : 512) : 2048) / threads;
     if (per_cu > by_lanes) per_cu = by_lanes;
     if (per_cu < 1) per_cu = 1;
-    uint64_t gx = (uint64_t)p->num_cus * per_cu / pl.kblocks;
+    uint64_t gx = (uint64_t)p->num_cus * per_cu / kblocks;
     gx = gx < 8 ? 8 : gx / 8 * 8;
     if (gx > ntiles) gx = ntiles;
-    dim3 grid((uint32_t)gx, pl.kblocks), block(pl.block);
+    dim3 grid((uint32_t)gx, kblocks), block(threads);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // one instantiation per epilogue: a run-time switch inside the kernels costs registers
     // (spills) in the gather loop
@@ -518,22 +533,23 @@ int launch_sampled(const lsh_params *p, Epilogue ep, const float *d_data, uint64
 #undef LSH_REG_LAUNCH
         return LSH_ERR_UNSUPPORTED;
     }
+#define LSH_GEN_LAUNCH(RT_, SUB_, EP_, SLOTS_) launch_kernel(&sampled_kernel<RT_, SUB_, EP_, SLOTS_>, lds_bytes, a, grid, block, s)
+#define LSH_GEN_QUADS(EP_) \
+    if (pl.rt == 4 && pl.sub == 8) return sub == 8 ? LSH_GEN_LAUNCH(4, 8, EP_, 8) : LSH_GEN_LAUNCH(4, 2, EP_, 8); \
+    if (pl.rt == 4 && pl.sub == 4) return sub == 4 ? LSH_GEN_LAUNCH(4, 4, EP_, 4) : LSH_GEN_LAUNCH(4, 1, EP_, 4); \
+    if (pl.rt == 4 && pl.sub == 2) return LSH_GEN_LAUNCH(4, 2, EP_, 2); \
+    if (pl.rt == 4) return LSH_GEN_LAUNCH(4, 1, EP_, 1);
     if (ep == Epilogue::IdsKeys) {  // 4-vector sub-tiles only (checked above)
-        constexpr int EK = (int)Epilogue::IdsKeys;
-        if (pl.sub == 8) return launch_kernel(&sampled_kernel<4, 8, EK>, lds_bytes, a, grid, block, s);
-        if (pl.sub == 4) return launch_kernel(&sampled_kernel<4, 4, EK>, lds_bytes, a, grid, block, s);
-        if (pl.sub == 2) return launch_kernel(&sampled_kernel<4, 2, EK>, lds_bytes, a, grid, block, s);
-        return launch_kernel(&sampled_kernel<4, 1, EK>, lds_bytes, a, grid, block, s);
+        LSH_GEN_QUADS((int)Epilogue::IdsKeys)
     }
 #define LSH_GEN_ALL(EP_) \
-    if (pl.rt == 4 && pl.sub == 8) return launch_kernel(&sampled_kernel<4, 8, EP_>, lds_bytes, a, grid, block, s); \
-    if (pl.rt == 4 && pl.sub == 4) return launch_kernel(&sampled_kernel<4, 4, EP_>, lds_bytes, a, grid, block, s); \
-    if (pl.rt == 4 && pl.sub == 2) return launch_kernel(&sampled_kernel<4, 2, EP_>, lds_bytes, a, grid, block, s); \
-    if (pl.rt == 4) return launch_kernel(&sampled_kernel<4, 1, EP_>, lds_bytes, a, grid, block, s); \
-    if (pl.rt == 2) return launch_kernel(&sampled_kernel<2, 1, EP_>, lds_bytes, a, grid, block, s); \
-    return launch_kernel(&sampled_kernel<1, 1, EP_>, lds_bytes, a, grid, block, s);
+    LSH_GEN_QUADS(EP_) \
+    if (pl.rt == 2) return LSH_GEN_LAUNCH(2, 1, EP_, 1); \
+    return LSH_GEN_LAUNCH(1, 1, EP_, 1);
     LSH_EP_CASES(LSH_GEN_ALL)
 #undef LSH_GEN_ALL
+#undef LSH_GEN_QUADS
+#undef LSH_GEN_LAUNCH
 #undef LSH_EP_CASES
     return LSH_ERR_UNSUPPORTED;
 }

@@ -1,0 +1,50 @@
+"""Launches of few vectors deal a tile's functions (and sub-tiles) to more workgroups than launches of
+many do, out of the same lists: a vector's results are the same numbers either way."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lsh():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2309_15479_amd as lib
+    lib.load_library()
+    return lib
+
+
+@pytest.mark.parametrize("n,k,m,L,w", [
+    (4096, 2048, 64, 128, 8.0),    # lists by coordinate ranges: four functions a lane
+    (4100, 1500, 40, 375, 3.0),    # three, idle lanes in the last set
+    (2100, 1024, 100, 64, 4.0),    # two, and blocks of two quads
+    (2500, 4000, 70, 250, 4.0),    # two workgroups along the functions already
+    (4096, 512, 64, 32, 8.0),      # one: nothing to deal out
+    (960, 1024, 128, 64, 1.0),     # whole-vector tiles of eight sub-tiles
+    (403, 250, 100, 125, 0.75),    # the same, nothing a multiple of anything
+    (1500, 700, 100, 175, 2.0),    # tiles of four sub-tiles
+    (2500, 300, 100, 75, 2.0),     # tiles of two sub-tiles: the functions alone
+])
+def test_few_vectors_equal_many(lsh, n, k, m, L, w):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + k)
+    N = 9000                       # more tiles than the chip has CUs, in every one of these shapes
+    data = torch.randn((N, n), generator=g, device="cuda")
+    with lsh.LshParams(n, k, m, w, 5) as p:
+        many = {"ids": lsh.hash_fastlsh(p, data), "proj": lsh.project_fastlsh(p, data), "signs": lsh.hash_signs(p, data)}
+        gs = k // L
+        if gs & (gs - 1) == 0:
+            many["keys"] = lsh.hash_fastlsh_keys(p, data, L)
+        for first, count in ((0, 1), (33, 17), (5, 100), (8000, 1000), (100, 2500)):
+            print(f"few vectors: n={n} k={k} m={m} first={first} count={count}", flush=True)
+            part = data[first:first + count].clone()
+            rows = slice(first, first + count)
+            assert torch.equal(lsh.hash_fastlsh(p, part), many["ids"][rows])
+            assert torch.equal(lsh.project_fastlsh(p, part), many["proj"][rows])
+            assert torch.equal(lsh.hash_signs(p, part), many["signs"][rows])
+            if "keys" in many:
+                assert torch.equal(lsh.hash_fastlsh_keys(p, part, L), many["keys"][rows])
+                ids, keys = lsh.hash_fastlsh_ids_keys(p, part, L)
+                assert torch.equal(ids, many["ids"][rows]) and torch.equal(keys, many["keys"][rows])
