@@ -176,7 +176,7 @@ int launch_offsets_scan(const uint32_t *d_count, uint64_t items, uint64_t *d_par
 
 // Stable least-significant-digit radix sort of all L key columns at once (one grid row per
 // table): eight passes of 8 bits.  A pass is three launches: per-tile digit histograms, an
-// exclusive scan of the (digit, tile) counts of every table, and the scatter.  A tile is 4096
+// exclusive scan of every table's and digit's counts over the tiles, and the scatter.  A tile is 4096
 // consecutive pairs; wave w of the workgroup owns pairs 1024 w ... 1024 w + 1023 of it, slot i
 // of lane l being pair 64 i + l, so (wave, slot, lane) order is memory order and the ranks
 // below keep equal keys in their original order (ids ascending inside a bucket).  The first
@@ -190,54 +190,88 @@ __device__ __forceinline__ uint64_t sort_key(const uint64_t *__restrict__ keys, 
     return FIRST ? keys[i * L + l] : keys[(uint64_t)l * N + i];
 }
 
+// Histograms of the first pass: a workgroup counts up to 32 columns of a tile of the caller's rows, so that
+// a wave reads whole pieces of rows (a column at a time, 8 bytes out of every row, took 329 us for 1e6 x 32
+// keys, as long as a scatter; this 119).
+constexpr uint32_t kRowThreads = 1024, kRowColumns = 32, kRowStride = 257;  // a column's bins one bank on from the column before
+
+__global__ __launch_bounds__(kRowThreads) void sort_histogram_rows(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L,
+                                                                    uint32_t columns, uint32_t width, uint32_t tiles,
+                                                                    uint32_t *__restrict__ hist) {
+    __shared__ uint32_t bins[kRowColumns * kRowStride];
+    const uint32_t tile = blockIdx.x, l0 = blockIdx.y * columns, here = L - l0 < columns ? L - l0 : columns;
+    for (uint32_t b = threadIdx.x; b < kRowColumns * kRowStride; b += kRowThreads) bins[b] = 0;
+    __syncthreads();
+    // width: a power of two, at least `columns` and at most 32
+    const uint32_t column = threadIdx.x & (width - 1), rows = kRowThreads / width;
+    const uint64_t first = (uint64_t)tile * kSortTile;
+    if (column < here) {
+        const uint64_t *at = keys + l0 + column;
+        const uint64_t end = N - first < kSortTile ? N : first + kSortTile;
+        for (uint64_t i = first + threadIdx.x / width; i < end; i += 4 * rows) {
+            uint32_t digit[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) digit[u] = i + u * rows < end ? (uint32_t)at[(i + u * rows) * L] & 255u : 256u;
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) atomicAdd(&bins[column * kRowStride + digit[u]], 1u);  // word 256 is not read
+        }
+    }
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < here * 256; b += kRowThreads)
+        hist[((size_t)l0 * 256 + b) * tiles + tile] = bins[(b >> 8) * kRowStride + (b & 255u)];
+}
+
 // hist[(l * 256 + digit) * tiles + tile] = pairs of the tile with that digit
-template <bool FIRST>
-__global__ __launch_bounds__(kSortThreads) void sort_histogram(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L,
+__global__ __launch_bounds__(kSortThreads) void sort_histogram(const uint64_t *__restrict__ keys, uint64_t N,
                                                                 uint32_t shift, uint32_t tiles,
                                                                 uint32_t *__restrict__ hist) {
-    __shared__ uint32_t bins[256];
-    // first pass: the L workgroups that read one tile of the caller's [N][L] rows are neighbours
-    // in launch order and find it in L2 (else every table would fetch the whole array again)
-    const uint32_t l = FIRST ? blockIdx.x % L : blockIdx.y, tile = FIRST ? blockIdx.x / L : blockIdx.x;
+    __shared__ uint32_t bins[257];
+    const uint32_t l = blockIdx.y, tile = blockIdx.x;
+    const uint64_t first = (uint64_t)tile * kSortTile + threadIdx.x;
+    uint32_t digit[kSortSlots];
+#pragma unroll
+    for (uint32_t e = 0; e < kSortSlots; ++e) {
+        const uint64_t i = first + e * kSortThreads;
+        digit[e] = i < N ? (uint32_t)(keys[(uint64_t)l * N + i] >> shift) & 255u : 256u;
+    }
     bins[threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t first = (uint64_t)tile * kSortTile;
-    for (uint32_t e = threadIdx.x; e < kSortTile; e += kSortThreads) {
-        const uint64_t i = first + e;
-        if (i < N) atomicAdd(&bins[(uint32_t)(sort_key<FIRST>(keys, N, L, l, i) >> shift) & 255u], 1u);
-    }
+#pragma unroll
+    for (uint32_t e = 0; e < kSortSlots; ++e) atomicAdd(&bins[digit[e]], 1u);  // word 256 is not read
     __syncthreads();
     hist[((size_t)l * 256 + threadIdx.x) * tiles + tile] = bins[threadIdx.x];
 }
 
-// one workgroup per table: hist <- exclusive prefix sum over its 256 * tiles counts, in place
-__global__ __launch_bounds__(kScanThreads) void sort_scan(uint32_t *__restrict__ hist, uint32_t tiles) {
-    __shared__ uint64_t wave_sums[kScanThreads / 64];
-    uint32_t *mine = hist + (size_t)blockIdx.x * 256 * tiles;
-    const uint64_t count = (uint64_t)256 * tiles;
-    uint64_t carry = 0;
-    for (uint64_t base = 0; base < count; base += kScanBlock) {
-        const uint64_t first = base + (uint64_t)threadIdx.x * kScanPerThread;
-        uint32_t v[kScanPerThread];
-        uint64_t sum = 0;
-        for (uint32_t e = 0; e < kScanPerThread; ++e) {
-            v[e] = first + e < count ? mine[first + e] : 0;
-            sum += v[e];
+// One wave per (table, digit): its counts <- their exclusive prefix sum over the tiles, in place, and the
+// sum of all of them to `total`; the scatter adds up the smaller digits' totals.  (One workgroup per table
+// that scanned all 256 * tiles counts: 74 us a pass at 1e6 x 32, 32 workgroups on 256 CUs; this 6.)
+__global__ __launch_bounds__(256) void sort_scan(uint32_t *__restrict__ hist, uint32_t tiles, uint32_t digits,
+                                                 uint32_t *__restrict__ total) {
+    const uint32_t lane = threadIdx.x & 63, digit = blockIdx.x * 4 + (threadIdx.x >> 6);  // of all tables
+    if (digit >= digits) return;
+    uint32_t *mine = hist + (size_t)digit * tiles;
+    uint32_t carry = 0;  // below N < 2^31
+    for (uint32_t base = 0; base < tiles; base += 256) {
+        uint32_t v[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) v[u] = base + u * 64 + lane < tiles ? mine[base + u * 64 + lane] : 0;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+            uint32_t incl = v[u];
+            for (uint32_t step = 1; step < 64; step <<= 1) {
+                const uint32_t up = __shfl_up(incl, step);
+                if (lane >= step) incl += up;
+            }
+            if (base + u * 64 + lane < tiles) mine[base + u * 64 + lane] = carry + incl - v[u];
+            carry += __shfl(incl, 63);
         }
-        uint64_t before;
-        const uint64_t total = block_scan(sum, wave_sums, before);
-        uint64_t run = carry + before;
-        for (uint32_t e = 0; e < kScanPerThread; ++e) {
-            if (first + e < count) mine[first + e] = (uint32_t)run;  // below N < 2^31
-            run += v[e];
-        }
-        carry += total;
     }
+    if (lane == 0) total[digit] = carry;
 }
 
 // The scatter of a pass.  A pair's place in the output is (pairs of smaller digits in its
 // table) + (pairs of its digit in earlier tiles) + (pairs of its digit before it in its tile);
-// the first two come scanned from the histograms, the third from wave ballots in memory order.
+// the first two come from the totals and the scanned histograms, the third from wave ballots in memory order.
 // The tile is first put in that order in LDS and then written out by consecutive threads:
 // pairs of one digit are then neighbours in LDS and in memory, so the stores of a wave are a
 // few runs instead of 64 separate 8-byte writes (about three times faster than scattering from the
@@ -247,14 +281,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__r
                                                               const uint32_t *__restrict__ ids, uint64_t N, uint32_t L,
                                                               uint32_t shift, uint32_t tiles,
                                                               const uint32_t *__restrict__ offsets,
+                                                              const uint32_t *__restrict__ total,
                                                               uint64_t *__restrict__ out_keys,
                                                               uint32_t *__restrict__ out_ids) {
     __shared__ uint32_t counter[kSortWaves][256];  // per wave: pairs seen so far per digit, then its first place in the tile's order
     __shared__ uint32_t delta[256];                // per digit: first output position minus first place in the tile's order
-    __shared__ uint32_t wave_total[kSortWaves];
+    __shared__ uint32_t wave_total[2][kSortWaves];
     __shared__ uint64_t tile_keys[kSortTile];
     __shared__ uint32_t tile_ids[kSortTile];
-    const uint32_t l = FIRST ? blockIdx.x % L : blockIdx.y, tile = FIRST ? blockIdx.x / L : blockIdx.x;  // as in sort_histogram
+    // first pass: the L workgroups that read one tile of the caller's [N][L] rows run on one XCD (number
+    // modulo 8), one after the other, and find it in its L2 (else every table would fetch the whole array again)
+    const uint32_t at_xcd = blockIdx.x >> 3;
+    const uint32_t l = FIRST ? at_xcd % L : blockIdx.y, tile = FIRST ? at_xcd / L * 8 + (blockIdx.x & 7) : blockIdx.x;
+    if (FIRST && tile >= tiles) return;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (uint32_t w = 0; w < kSortWaves; ++w) counter[w][threadIdx.x] = 0;
     __syncthreads();
@@ -265,12 +304,18 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__r
     uint32_t id[kSortSlots];
     uint32_t rank[kSortSlots];
     volatile uint32_t *mine = counter[wave];
+    // All loads first: behind the ordered LDS accesses of the ranking they go out one slot at a time (a pass over
+    // 1e6 x 32 pairs 334 -> 219 us, 3.5 TB/s).
 #pragma unroll
     for (uint32_t i = 0; i < kSortSlots; ++i) {
         const uint64_t at = first + (uint64_t)i * 64;
-        const bool valid = at < N;
-        key[i] = valid ? sort_key<FIRST>(keys, N, L, l, at) : 0;
-        id[i] = FIRST ? (uint32_t)at : valid ? ids[(uint64_t)l * N + at] : 0u;
+        key[i] = sort_key<FIRST>(keys, N, L, l, at < N ? at : N - 1);
+        id[i] = FIRST ? (uint32_t)at : ids[(uint64_t)l * N + (at < N ? at : N - 1)];
+    }
+    const uint32_t tile_offset = offsets[((size_t)l * 256 + threadIdx.x) * tiles + tile], digit_total = total[l * 256 + threadIdx.x];
+#pragma unroll
+    for (uint32_t i = 0; i < kSortSlots; ++i) {
+        const bool valid = first + (uint64_t)i * 64 < N;
         const uint32_t digit = (uint32_t)(key[i] >> shift) & 255u;
         // lanes of the wave that hold the same digit in this slot
         uint64_t peers = __ballot(valid);
@@ -288,22 +333,23 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__r
     __syncthreads();
     {   // thread d: the tile's pairs of digit d, their first place in the tile's order (an exclusive
         // scan over the digits) and, per wave, the first place of that wave's pairs of the digit
-        uint32_t per_wave[kSortWaves], total = 0;
+        uint32_t per_wave[kSortWaves], in_tile = 0;
         for (uint32_t w = 0; w < kSortWaves; ++w) {
             per_wave[w] = counter[w][threadIdx.x];
-            total += per_wave[w];
+            in_tile += per_wave[w];
         }
-        uint32_t incl = total;  // inclusive scan over the 64 digits of this wave, then over the waves
+        // inclusive scans over the 64 digits of this wave, then over the waves: of the tile, of the table
+        uint32_t incl = in_tile, incl_table = digit_total;
 #pragma unroll
         for (uint32_t step = 1; step < 64; step <<= 1) {
-            const uint32_t up = __shfl_up(incl, step);
-            if (lane >= step) incl += up;
+            const uint32_t up = __shfl_up(incl, step), up_table = __shfl_up(incl_table, step);
+            if (lane >= step) incl += up, incl_table += up_table;
         }
-        if (lane == 63) wave_total[wave] = incl;
+        if (lane == 63) wave_total[0][wave] = incl, wave_total[1][wave] = incl_table;
         __syncthreads();
-        uint32_t start = incl - total;
-        for (uint32_t w = 0; w < wave; ++w) start += wave_total[w];
-        delta[threadIdx.x] = offsets[((size_t)l * 256 + threadIdx.x) * tiles + tile] - start;
+        uint32_t start = incl - in_tile, table_start = incl_table - digit_total;
+        for (uint32_t w = 0; w < wave; ++w) start += wave_total[0][w], table_start += wave_total[1][w];
+        delta[threadIdx.x] = table_start + tile_offset - start;
         for (uint32_t w = 0; w < kSortWaves; ++w) {
             counter[w][threadIdx.x] = start;
             start += per_wave[w];
@@ -596,7 +642,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
     // scratch: the other half of the ping-pong, and the (digit, tile) counts of every table
     lsh::IndexBlock scratch;
     uint64_t *tmp_keys = nullptr;
-    uint32_t *tmp_ids = nullptr, *hist = nullptr;
+    uint32_t *tmp_ids = nullptr, *hist = nullptr, *total = nullptr;
     int rc = LSH_OK;
     if (hipGetDevice(&ix->device) != hipSuccess) {
         delete ix;
@@ -604,7 +650,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
     }
     lsh::index_memory_enter(ix->device);
     if (!lsh::index_memory_take(ix->device, pairs * 12, false, s, ix->tables)) rc = LSH_ERR_ALLOC;
-    if (rc == LSH_OK && !lsh::index_memory_take(ix->device, pairs * 12 + (size_t)L * 256 * tiles * 4, true, s, scratch))
+    if (rc == LSH_OK && !lsh::index_memory_take(ix->device, pairs * 12 + (size_t)L * 256 * (tiles + 1) * 4, true, s, scratch))
         rc = LSH_ERR_ALLOC;
     if (rc == LSH_OK) {
         ix->d_keys = static_cast<uint64_t *>(ix->tables.ptr);
@@ -612,6 +658,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
         tmp_keys = static_cast<uint64_t *>(scratch.ptr);
         tmp_ids = reinterpret_cast<uint32_t *>(tmp_keys + pairs);
         hist = tmp_ids + pairs;
+        total = hist + (size_t)L * 256 * tiles;
     }
     if (rc == LSH_OK) {
         const dim3 grid(tiles, L), block(kSortThreads);
@@ -623,17 +670,21 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
             uint64_t *dst_keys = (pass & 1) ? ix->d_keys : tmp_keys;
             uint32_t *dst_ids = (pass & 1) ? ix->d_ids : tmp_ids;
             if (pass == 0) {
-                const dim3 linear(tiles * L);  // below 2^31 (checked above)
-                hipLaunchKernelGGL(sort_histogram<true>, linear, block, 0, s, src_keys, N, L, shift, tiles, hist);
-                hipLaunchKernelGGL(sort_scan, dim3(L), dim3(kScanThreads), 0, s, hist, tiles);
-                hipLaunchKernelGGL(sort_scatter<true>, linear, block, 0, s, src_keys, src_ids, N, L, shift, tiles, hist,
-                                   dst_keys, dst_ids);
+                const uint32_t groups = (L + kRowColumns - 1) / kRowColumns, columns = (L + groups - 1) / groups;
+                uint32_t width = 1;
+                while (width < columns) width *= 2;
+                hipLaunchKernelGGL(sort_histogram_rows, dim3(tiles, groups), dim3(kRowThreads), 0, s, src_keys, N, L, columns,
+                                   width, tiles, hist);
             } else {
-                hipLaunchKernelGGL(sort_histogram<false>, grid, block, 0, s, src_keys, N, L, shift, tiles, hist);
-                hipLaunchKernelGGL(sort_scan, dim3(L), dim3(kScanThreads), 0, s, hist, tiles);
-                hipLaunchKernelGGL(sort_scatter<false>, grid, block, 0, s, src_keys, src_ids, N, L, shift, tiles, hist,
-                                   dst_keys, dst_ids);
+                hipLaunchKernelGGL(sort_histogram, grid, block, 0, s, src_keys, N, shift, tiles, hist);
             }
+            hipLaunchKernelGGL(sort_scan, dim3(L * 64), dim3(256), 0, s, hist, tiles, L * 256, total);
+            if (pass == 0)
+                hipLaunchKernelGGL(sort_scatter<true>, dim3((tiles + 7) / 8 * 8 * L), block, 0, s, src_keys, src_ids, N, L, shift,
+                                   tiles, hist, total, dst_keys, dst_ids);
+            else
+                hipLaunchKernelGGL(sort_scatter<false>, grid, block, 0, s, src_keys, src_ids, N, L, shift, tiles, hist, total,
+                                   dst_keys, dst_ids);
         }
         if (hipGetLastError() != hipSuccess) rc = LSH_ERR_HIP;
     }
