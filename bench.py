@@ -27,7 +27,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 MFMA_FP32_PEAK_TFLOPS = 157.3    # dense fp32 matrix peak
-MFMA_BF16_PEAK_TFLOPS = 2500.0   # dense bf16 matrix peak
+MFMA_BF16_PEAK_TFLOPS = 2500.0   # dense bf16 and fp16 matrix peak
 # fp32 multiply-adds on the vector ALU without packed instructions (this library is compiled
 # without them): 256 CUs x 64 lanes per clock x 2.4 GHz = 39.3 T FMA/s = 78.6 TFLOP/s
 VALU_FMA_PEAK_T = 256 * 64 * 2.4e9 / 1e12
@@ -156,6 +156,12 @@ def gather_roofline(N, n, k, m, out_bytes_per_vector, ms, traffic=None):
     return hbm
 
 
+def dense_arithmetic(n, m):
+    """Products of the matrix-core kernels for n other than 128: two-way fp16 splits for sums of 128 terms
+    and more, three-way bf16 splits for shorter ones."""
+    return {"products": 3, "fp16": True} if m >= 128 else {"products": 6}
+
+
 def dense_roofline(N, n, k, ms, arithmetic, traffic=None):
     tf = 2.0 * N * n * k / (ms * 1e-3) / 1e12
     if arithmetic == "fp32":
@@ -164,7 +170,9 @@ def dense_roofline(N, n, k, ms, arithmetic, traffic=None):
     products = arithmetic["products"]
     return {"bound": "mfma", "achieved": products * tf, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": products * tf / MFMA_BF16_PEAK_TFLOPS, "traffic": traffic,
-            "arithmetic": f"bf16 x 3 exact splits, fp32 accumulation, {products} of 6 MFMA products per coordinate",
+            "arithmetic": ("fp16 x 2 splits scaled by vector and function, fp32 accumulation, 3 MFMA products per coordinate"
+                           if arithmetic.get("fp16") else
+                           f"bf16 x 3 exact splits, fp32 accumulation, {products} of 6 MFMA products per coordinate"),
             "fp32_equivalent_tflops": tf}
 
 
@@ -286,9 +294,9 @@ class Bench:
             entry["parity"] = self.check_ids(p, wl, data, out, dense=True, count=48 if n > 1024 else 96)
             split = (n == 128 and k % 32 == 0) or (n != 128 and n % 4 == 0)
             if split:
-                # bf16 x 3 products; at n = 128 half of the six products are skipped by tile on byte-valued data
+                # split products; at n = 128 half of the six products are skipped by tile on byte-valued data
                 integer_data = n == 128 and bool((data[:4096] == data[:4096].round()).all().item())
-                arithmetic = {"products": 3 if integer_data else 6}
+                arithmetic = dense_arithmetic(n, n) if n != 128 else {"products": 3 if integer_data else 6}
                 p.set_dense_arithmetic(lsh.DENSE_FP32)
                 fp32_ms = self.timer.measure(lambda: lsh.hash_e2lsh(p, data, out=out))
                 p.set_dense_arithmetic(lsh.DENSE_AUTO)
@@ -304,7 +312,7 @@ class Bench:
             else:
                 arithmetic = "fp32"
         entry.update({"ms": ms, "hashes_per_s": N * k / (ms * 1e-3), "vectors_per_s": N / (ms * 1e-3),
-                      "dtype": "f32" if arithmetic == "fp32" else "bf16x3+f32acc",
+                      "dtype": "f32" if arithmetic == "fp32" else "fp16x2+f32acc" if arithmetic.get("fp16") else "bf16x3+f32acc",
                       "roofline": with_traffic(dense_roofline(N, n, k, ms, arithmetic), f"{wl.name}/e2lsh")})
         entry["roofline"]["hbm_frac"] = N * (4 * n + 4 * k) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
         return entry
@@ -568,8 +576,8 @@ class Bench:
                  "vectors_per_s": N / (ms[leg] * 1e-3), "dtype": "f32", "timed": "inside the step",
                  "parity": self.check_ids(p, wl, data, out, dense, count=48 if dense else 96)}
             if dense:
-                e["dtype"] = "bf16x3+f32acc"
-                e["roofline"] = with_traffic(dense_roofline(N, n, k, ms[leg], {"products": 6}), "highdim/e2lsh")
+                e["dtype"] = "fp16x2+f32acc"
+                e["roofline"] = with_traffic(dense_roofline(N, n, k, ms[leg], dense_arithmetic(n, n)), "highdim/e2lsh")
                 e["roofline"]["hbm_frac"] = N * (4 * n + 4 * k) / (ms[leg] * 1e-3) / 1e9 / HBM_PEAK_GBS
                 # the same launch on the fp32 matrix cores, timed outside the step
                 p.set_dense_arithmetic(lsh.DENSE_FP32)
@@ -672,7 +680,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (sampled projections); bf16x3+f32acc (dense product: exact three-way bf16 splits, fp32 accumulation)",
+        "dtype": "f32 (sampled projections); fp16x2+f32acc (dense product: two-way fp16 splits of 23 bits, fp32 accumulation)",
         "data": "synthetic",
         "config": {"workload": "high-dimensional: N=200000 n=4096 k=2048 w=8, i.i.d. N(0,1) rows + 5% planted "
                                "near-duplicates; FastLSH at m=64, 256, 1024 and dense E2LSH (m=n)",

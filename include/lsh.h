@@ -200,16 +200,21 @@ int lsh_hash_e2lsh(const lsh_params_t *params, const float *d_data, uint64_t N,
  * lsh_hash_signs runs on the matrix cores too, with two-way splits and three products: what
  * they leave out is below 3 * 2^-16 * sum_i |a_i v_i|, under half of the 1e-4 * |a| * |S(v)| around
  * zero inside which a sign bit is unspecified.  Objects with m == n and another n that is a
- * multiple of 4 take the same six products in lsh_hash_e2lsh and lsh_project_e2lsh (no
- * products skipped); any other shape uses fp32 MFMA.
+ * multiple of 4 run on the matrix cores in lsh_hash_e2lsh and lsh_project_e2lsh too (no products
+ * skipped): those with n < 128 by the same six products, those with n > 128 by three products of
+ * two-way fp16 splits (23 bits), every vector and function scaled by a power of two of its own first
+ * so that nothing leaves fp16.  The split is off by less than 2^-22 of each term |a_i v_i|, or by
+ * 2^-33 of the largest coordinate times the largest coefficient where that is more; the sum is rounded half
+ * as often and is the closer one to the exact value from 128 terms on.  A vector with an infinite or
+ * NaN coordinate has no defined result, as before.  Any other shape uses fp32 MFMA.
  * LSH_DENSE_FP32: fp32 MFMA for every dense product, and the gathered fp32 kernels for FastLSH
  * ids, projections, keys and signs at every n.
  * LSH_DENSE_MATRIX: as LSH_DENSE_AUTO, and lsh_hash_fastlsh and lsh_project_fastlsh of an object
- * with m < n and any n that is a multiple of 4 also run as that bf16 x 3 product over the
- * coefficients written out over all n coordinates (same error bound).  It costs n multiply-adds
+ * with m < n and any n that is a multiple of 4 also run as such a product (of fp16 splits if
+ * m >= 128, else bf16) over the coefficients written out over all n coordinates (same error bound).  It costs n multiply-adds
  * per function where the gather costs m, on matrix cores that are several times faster per
- * multiply-add: on the 4096-dimensional shape it is the faster route from about m = n / 5 on.
- * The first call with this mode builds the object's bf16 planes (6 bytes x k x n of device
+ * multiply-add: on the 4096-dimensional shape it is the faster route from about m = n / 8 on.
+ * The first call with this mode builds the object's planes (4 or 6 bytes x k x n of device
  * memory, freed with the object; call it with the object's device current).
  * The mode is a plain field of the object, read by every hash call when it launches: set it
  * while no other thread is calling into the same object (calls already enqueued keep the mode

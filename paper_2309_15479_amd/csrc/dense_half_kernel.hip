@@ -1,0 +1,504 @@
+// Dense E2LSH projections (Sec. 2.2, Eq. 1) on the fp16 matrix cores of gfx950 with fp32 accuracy,
+// for sums of 128 terms and more: P = V A^T from two-way fp16 splits of both operands scaled by
+// powers of two, and three products.
+//
+// Arithmetic.  x 2^e = x1 + x2 + r with x1 = fp16(x 2^e), x2 = fp16(x 2^e - x1), round to nearest:
+// two 11-bit significands and the sign of the second hold 23 bits, |r| <= 2^-23 of x (2^-25 absolute
+// where x2 is subnormal).  The products a1 v1 + a1 v2 + a2 v1 are exact in fp32, a2 v2 (below 2^-22 of
+// the term) is left out.  Against 64 bits the split is off by 7e-8 (2-norm) at any length, and the
+// accumulation rounds half as often as over the six bf16 products of dense_split_wide_kernel.hip,
+// where every product is added to the same accumulators.  Both together, modelled with one rounding a
+// product of 16 terms, fp16 / bf16: 8.5e-8 / 6.3e-8 at 30 terms, 1.07e-7 / 1.18e-7 at 128, 1.9e-7 /
+// 2.5e-7 at 512, 2.5e-7 / 3.5e-7 at 960; kHalfMinTerms is where the fp16 product is the more accurate one.
+//
+// Scales.  e is a function's (on the host, from its largest coefficient: [2^14, 2^15) after scaling)
+// or a vector's.  A vector's comes from up to 80 of its coordinates, the three stages that start the
+// contraction and two further on: the largest of them goes to [2^8, 2^9), so the others may
+// be 128 times larger before they leave fp16, and whatever is smaller loses at most 2^-33 of the
+// largest.  A vector whose looked-at coordinates are all zero is read through for its largest one.  The
+// loading threads keep the largest coordinate they met: should one have left fp16, the tile is done once
+// more with that vector's scale taken from it.  So a vector's scale depends on the vector alone.
+//
+//   V [N][n] fp32 row-major; A split on the host into two fp16 planes in the order of use:
+//   [function tile of 256][stage of 16 coordinates][plane][row][coordinate] (zero rows up to a multiple
+//   of 256, zero columns up to a multiple of 16), the functions' exponents behind them.
+//
+// Workgroup, tile, placement and the three LDS stages are those of dense_split_wide_kernel.hip: 4 waves,
+// 256 functions x 256 vectors, 4 x 4 blocks of 32 x 32 a wave, everything that is not an MFMA dealt out
+// behind the MFMAs.  A stage is 48 MFMAs a wave here (96 there), which leaves half as many places for
+// 8 global loads, 12 LDS writes, 16 LDS reads and the split of 16 vector elements; it takes 1.25 us of
+// which the matrix pipe is busy 0.8.  The rest is the issue of those instructions by a wave that is alone on
+// its SIMD, and 14 us a tile of first loads, scales and results.
+// Measured against the six bf16 products (same job): 9230 -> 5570 us at N = 1e6, n = 960, k = 1024;
+// 14150 -> 8030 at 2e5, 4096, 2048; 429 -> 217 at 1e4, 4096, 512; 114 -> 64 at 1000, 960, 1024; 77 -> 58 at
+// 1e5, 132, 256; 467 -> 321 at 3e5, 300, 250.  What gave how much at 1e6 x 960: the arithmetic 5930; LDS accesses
+// kept away from the barrier and smaller pieces of work behind the MFMAs 5800; results through LDS into whole
+// lines 5570.  Two and three register sets for the vector and coefficient loads, and the next tile's first loads
+// ahead of the results, cost more in registers spilled around the loop than they hide (6000 to 6500).
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstring>
+#include <type_traits>
+#include <utility>
+#include <vector>
+
+#include "device_utils.h"
+#include "lsh_internal.h"
+
+namespace lsh {
+namespace {
+
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+
+constexpr int TF = 256;    // functions per tile
+constexpr int TVW = 256;   // vectors per tile
+constexpr int NB = 4;      // 32 x 32 blocks of a wave along either axis
+constexpr int KB = 16;     // coordinates per stage = one MFMA step
+constexpr int ROWB = 32;   // bytes per row and plane in a stage: two 16-byte halves, swapped in rows with bit 3 set
+constexpr int A_PLANE = TF * ROWB, V_PLANE = TVW * ROWB;
+constexpr int STAGE = 2 * (A_PLANE + V_PLANE);  // 32768 bytes
+constexpr int kThreadsH = 256;
+constexpr int kStagePlanes = 2 * TF * KB;  // fp16 elements of one function tile's two planes in one stage
+constexpr int kVectorScales = 3 * STAGE;   // LDS offset of the tile's 256 vector exponents
+constexpr int kRedo = kVectorScales + TVW * 4;
+constexpr int kLdsBytesH = kRedo + 16;
+constexpr int kResultRow = 144;            // bytes of a vector's 32 results in LDS on their way out: conflict-free both ways
+constexpr uint32_t kHalfMinTerms = 128;
+constexpr float kLargestHalf = 65504.f;
+constexpr int kVectorTop = 8, kFunctionTop = 14;  // exponent of the largest looked-at coordinate and coefficient after scaling
+
+struct HalfArgs {
+    const float *data;       // [N][n]
+    const uint16_t *planes;  // [kpad / 256][npad / 16][2][256][16] fp16 bit patterns
+    const int *fexp;         // [kpad] exponents the functions were scaled by
+    const float *off;        // [>= kpad]
+    uint64_t N;
+    uint32_t n, npad, k, kpad;
+    float w, inv_w;
+    void *out;               // [N][k]
+};
+
+// exponent e that takes a value's leading bit to 2^top; 2^e is a normal float
+__device__ __forceinline__ int scale_exponent(float largest, int top) {
+    const int biased = (int)((__float_as_uint(largest) >> 23) & 255u);
+    const int e = top + 127 - biased;
+    return largest == 0.f ? 0 : e > 126 ? 126 : e;  // at least top - 128
+}
+
+__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
+
+__device__ __forceinline__ float largest_of(floatx4 v, float so_far) {
+    return fmaxf(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), so_far), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+
+// two elements, scaled and split: hi + lo = x 2^e to 23 bits
+__device__ __forceinline__ void split2(float x0, float x1, float scale, halfx2 &hi, halfx2 &lo) {
+    const floatx2 y = {x0 * scale, x1 * scale};
+    hi = __builtin_convertvector(y, halfx2);
+    const floatx2 r = {__builtin_fmaf(x0, scale, -(float)hi[0]), __builtin_fmaf(x1, scale, -(float)hi[1])};
+    lo = __builtin_convertvector(r, halfx2);
+}
+
+// PROJ: raw projections instead of bucket ids.  POW2: w is a power of two (fma(p, 1/w, b/w) is
+// then the same float as (p + b) / w).  VEC: k is a multiple of 4 (16-byte stores).
+template <bool PROJ, bool POW2, bool VEC>
+__global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a) {
+    extern __shared__ __align__(16) char lds_h[];  // 3 stages x ([2][256][32] coefficients, [2][256][32] vectors), exponents, flag
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lr = lane & 31, lh = lane >> 5;
+    const uint32_t fw = wave & 1, vw = wave >> 1;  // the wave's half of the functions, half of the vectors
+    int *const vector_exp = reinterpret_cast<int *>(lds_h + kVectorScales);
+    volatile int *const redo_flag = reinterpret_cast<int *>(lds_h + kRedo);
+
+    // which (function tile, vector tile) pairs this workgroup takes
+    const uint32_t F = a.kpad / TF;
+    const uint64_t Vt = (a.N + TVW - 1) / TVW;
+    const uint32_t x = blockIdx.x & 7, i = blockIdx.x >> 3, per_xcd = gridDim.x >> 3;
+    uint32_t ft_first, ft_step, reps, rep;
+    if (F >= 8) {
+        ft_first = x; ft_step = 8; reps = 1; rep = 0;
+    } else {
+        ft_first = x % F; ft_step = F;  // one function tile per XCD
+        reps = (8 - ft_first + F - 1) / F;  // XCDs that share it
+        rep = x / F;
+    }
+
+    // loading roles: 16 bytes of the vector tile and of each coefficient plane per stage
+    const uint32_t vr = threadIdx.x >> 2, vq = threadIdx.x & 3;  // vector rows vr + 64 h (h < 4), 4-coordinate piece
+    const uint32_t ar = threadIdx.x >> 1, ah = threadIdx.x & 1;  // coefficient rows ar and ar + 128, 8-coordinate half
+    const uint32_t stages = a.npad / KB;
+
+    // operand read and write offsets inside a stage (half h of row r sits at 16 * (h ^ bit 3 of r))
+    const uint32_t rd_a = (fw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);                // + rb * 32 rows + plane
+    const uint32_t rd_v = 2 * A_PLANE + (vw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);  // + cb * 32 rows + plane
+    const uint32_t wr_a = ar * ROWB + ((ah ^ ((ar >> 3) & 1)) << 4);
+    const uint32_t wr_v = 2 * A_PLANE + vr * ROWB + (((vq >> 1) ^ ((vr >> 3) & 1)) << 4) + ((vq & 1) << 3);
+
+    // as in dense_split_wide_kernel: the function tiles of a vector tile side by side on one XCD
+    const bool by_vector = per_xcd % F == 0 && F <= per_xcd;
+    uint64_t vt_first = (uint64_t)i * reps + rep, vt_step = (uint64_t)per_xcd * reps;
+    if (by_vector) {
+        ft_first = i % F;
+        ft_step = F;  // one function tile per workgroup
+        const uint32_t groups = per_xcd / F;
+        vt_first = x + 8ull * (i / F);
+        vt_step = 8ull * groups;
+    }
+    const bool whole_lines = a.k % 32 == 0;  // non-temporal stores then; of partial lines they are slower (341 against 302 us at k = 252)
+    if (threadIdx.x == 0) *redo_flag = 0;
+    for (uint32_t ft = ft_first; ft < F; ft += ft_step) {
+        // thread t: 16 bytes at 16 t of rows 0-127 of a plane, and of rows 128-255
+        const uint16_t *arow = a.planes + (size_t)ft * stages * kStagePlanes + threadIdx.x * 8;
+        for (uint64_t vt = vt_first; vt < Vt; vt += vt_step) {
+            const float *vrow[4];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                uint64_t row = vt * TVW + vr + h * 64;
+                row = row < a.N ? row : a.N - 1;  // rows beyond the data repeat the last vector (never stored)
+                vrow[h] = a.data + row * a.n + vq * 4;
+            }
+            // Every load is issued unconditionally (the compiler can then count the loads in flight
+            // exactly and wait for the oldest only).  Coordinates beyond n read the vector's first ones
+            // instead: the coefficients are zero there.  Stages beyond the last are read and written to
+            // LDS like others and never contracted.
+            auto load_v = [&](uint32_t s, int h) __attribute__((always_inline)) {
+                const uint32_t k0 = s * KB;
+                return *reinterpret_cast<const floatx4 *>(vrow[h] + (k0 + vq * 4 < a.n ? k0 : 0u));
+            };
+            auto load_a = [&](uint32_t s, int h, int p) __attribute__((always_inline)) {
+                const uint32_t ka = s < stages ? s : stages - 1;
+                return *reinterpret_cast<const uintx4 *>(arow + (size_t)ka * kStagePlanes + p * (TF * KB) + h * 128 * KB);
+            };
+            floatx16 acc[NB][NB];
+            float scale[4], largest[4];
+            int vexp[4];
+            for (uint32_t attempt = 0;; ++attempt) {
+                // stages 0 to 2 and, the first time, the coordinates the scales are taken from: all in flight at once
+                floatx4 gv[3][4];
+                uintx4 ga[3][2][2];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) gv[t][h] = load_v(t, h);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) ga[t][h][p] = load_a(t, h, p);
+                }
+                if (attempt == 0) {
+                    floatx4 far_v[2][4];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int h = 0; h < 4; ++h) far_v[t][h] = load_v(stages * (t + 1) / 3, h);
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        float top = 0.f;
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) top = largest_of(gv[t][h], top);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) top = largest_of(far_v[t][h], top);
+                        top = fmaxf(top, __shfl_xor(top, 1));  // the four threads of a vector are neighbours
+                        top = fmaxf(top, __shfl_xor(top, 2));
+                        if (top == 0.f) {
+                            for (uint32_t s = 3; s < stages; s += 8) {
+#pragma unroll
+                                for (int u = 0; u < 8; ++u) top = largest_of(load_v(s + u, h), top);
+                            }
+                        }
+                        top = fmaxf(top, __shfl_xor(top, 1));
+                        top = fmaxf(top, __shfl_xor(top, 2));
+                        vexp[h] = scale_exponent(top, kVectorTop);
+                        largest[h] = top;
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    scale[h] = power_of_two(vexp[h]);
+                    if (vq == 0) vector_exp[vr + h * 64] = vexp[h];
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    char *stage = lds_h + t * STAGE;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        halfx2 hi[2], lo[2];
+                        split2(gv[t][r][0], gv[t][r][1], scale[r], hi[0], lo[0]);
+                        split2(gv[t][r][2], gv[t][r][3], scale[r], hi[1], lo[1]);
+                        *reinterpret_cast<halfx4 *>(stage + wr_v + r * 64 * ROWB) = halfx4{hi[0][0], hi[0][1], hi[1][0], hi[1][1]};
+                        *reinterpret_cast<halfx4 *>(stage + wr_v + r * 64 * ROWB + V_PLANE) = halfx4{lo[0][0], lo[0][1], lo[1][0], lo[1][1]};
+                    }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) *reinterpret_cast<uintx4 *>(stage + wr_a + r * 128 * ROWB + p * A_PLANE) = ga[t][r][p];
+                }
+                floatx4 v_set[4];
+                uintx4 c_set[2][2];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) v_set[h] = gv[2][h];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) c_set[h][p] = ga[2][h][p];
+#pragma unroll
+                for (int rb = 0; rb < NB; ++rb)
+#pragma unroll
+                    for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[rb][cb][e] = 0.f;
+                lds_barrier();
+
+                // operand registers of the stage being contracted: fa[block][plane], fv[block][plane]
+                halfx8 fa[NB][2], fv[NB][2];
+                auto read_a1 = [&](const char *stage, int b, int p) __attribute__((always_inline)) {
+                    fa[b][p] = *reinterpret_cast<const halfx8 *>(stage + rd_a + b * 32 * ROWB + p * A_PLANE);
+                };
+                auto read_v1 = [&](const char *stage, int b, int p) __attribute__((always_inline)) {
+                    fv[b][p] = *reinterpret_cast<const halfx8 *>(stage + rd_v + b * 32 * ROWB + p * V_PLANE);
+                };
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    read_v1(lds_h, b, 1);
+                    read_a1(lds_h, b, 0);
+                    read_v1(lds_h, b, 0);
+                }
+
+                // One stage.  LDS holds three: s (in the operand registers, but for the low coefficients), s + 1
+                // (written during the previous iteration, read into the freed operand registers during this one)
+                // and s + 2 (written during this one from the load registers, which then take the loads of
+                // stage s + 3).  Products a1 v2 by columns, a1 v1 by rows, a2 v1 by columns: an operand is
+                // refilled when its last product has been issued, 16 MFMAs or more before its first one in the
+                // next stage; a2 is used in every column of the last product and is read during the first one.
+                auto iteration = [&](uint32_t s) __attribute__((always_inline)) {
+                    const char *cur = lds_h + (s % 3) * STAGE;
+                    const char *nxt = lds_h + ((s + 1) % 3) * STAGE;
+                    char *far = lds_h + ((s + 2) % 3) * STAGE;  // last read before the barrier of the iteration before
+                    halfx2 hi[2], lo[2];  // a vector row on its way
+                    // a quarter of the split of row r: two elements to their high or, after that, their low halves
+                    auto split_quarter = [&](int r, int quarter) __attribute__((always_inline)) {
+                        const int e = quarter / 2;
+                        const float x0 = v_set[r][2 * e], x1 = v_set[r][2 * e + 1];
+                        if (quarter % 2 == 0) {
+                            hi[e] = __builtin_convertvector((floatx2{x0 * scale[r], x1 * scale[r]}), halfx2);
+                            largest[r] = fmaxf(fmaxf(fabsf(x0), fabsf(x1)), largest[r]);
+                        } else {
+                            lo[e] = __builtin_convertvector((floatx2{__builtin_fmaf(x0, scale[r], -(float)hi[e][0]),
+                                                                     __builtin_fmaf(x1, scale[r], -(float)hi[e][1])}), halfx2);
+                        }
+                    };
+                    auto write_v = [&](int r, int p) __attribute__((always_inline)) {
+                        *reinterpret_cast<halfx4 *>(far + wr_v + r * 64 * ROWB + p * V_PLANE) =
+                            p == 0 ? halfx4{hi[0][0], hi[0][1], hi[1][0], hi[1][1]} : halfx4{lo[0][0], lo[0][1], lo[1][0], lo[1][1]};
+                    };
+                    auto coefficient = [&](int at, bool load) __attribute__((always_inline)) {
+                        const int r = at / 2, p = at % 2;
+                        if (load) c_set[r][p] = load_a(s + 3, r, p);
+                        else *reinterpret_cast<uintx4 *>(far + wr_a + r * 128 * ROWB + p * A_PLANE) = c_set[r][p];
+                    };
+                    // What goes out after MFMA j (0..15) of product k (0..2): one memory instruction at most, or two
+                    // LDS reads, and a quarter of the split of a vector row beside it.  The LDS accesses that the
+                    // barrier behind product 0 waits for are issued three MFMAs before it or earlier.
+                    auto after = [&](auto K_, auto I_) __attribute__((always_inline)) {
+                        constexpr int k = decltype(K_)::value, j = decltype(I_)::value;
+                        if constexpr (k == 0) {
+                            if constexpr (j < 4) { read_a1(cur, j, 1); split_quarter(0, j); }
+                            if constexpr (j == 4 || j == 5) write_v(0, j - 4);
+                            if constexpr (j == 6) v_set[0] = load_v(s + 3, 0);
+                            if constexpr (j >= 7 && j < 11) split_quarter(1, j - 7);
+                            if constexpr (j == 11 || j == 12) write_v(1, j - 11);
+                            if constexpr (j == 14) v_set[1] = load_v(s + 3, 1);
+                        } else if constexpr (k == 1) {
+                            if constexpr (j % 4 == 3) read_a1(nxt, j / 4, 0);
+                            if constexpr (j < 4) { read_v1(nxt, j, 1); split_quarter(2, j); }
+                            if constexpr (j == 4 || j == 5) write_v(2, j - 4);
+                            if constexpr (j == 6) v_set[2] = load_v(s + 3, 2);
+                            if constexpr (j == 8 || j == 10) coefficient(j / 2 - 4, false);
+                            if constexpr (j == 9 || j == 12) coefficient(j / 3 - 3, true);
+                            if constexpr (j == 13) coefficient(2, false);
+                            if constexpr (j == 14) coefficient(2, true);
+                        } else {
+                            if constexpr (j % 4 == 3) read_v1(nxt, j / 4, 0);
+                            if constexpr (j < 4) split_quarter(3, j);
+                            if constexpr (j == 4 || j == 5) write_v(3, j - 4);
+                            if constexpr (j == 6) v_set[3] = load_v(s + 3, 3);
+                            if constexpr (j == 8) coefficient(3, false);
+                            if constexpr (j == 9) coefficient(3, true);
+                        }
+                    };
+                    auto product = [&](auto K_, auto PA_, auto PV_, auto BY_ROW_) __attribute__((always_inline)) {
+                        constexpr int pa = decltype(PA_)::value, pv = decltype(PV_)::value;
+                        constexpr bool by_row = decltype(BY_ROW_)::value;
+                        [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+                            (([&] {
+                                constexpr int rb = by_row ? I / 4 : I % 4, cb = by_row ? I % 4 : I / 4;
+                                acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[rb][pa], fv[cb][pv], acc[rb][cb], 0, 0, 0);
+                                __builtin_amdgcn_sched_barrier(0);
+                                after(K_, std::integral_constant<int, I>{});
+                                __builtin_amdgcn_sched_barrier(0);
+                            }()), ...);
+                        }(std::make_integer_sequence<int, 16>{});
+                    };
+                    using std::integral_constant;
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(integral_constant<int, 0>{}, integral_constant<int, 0>{}, integral_constant<int, 1>{}, std::false_type{});
+                    lds_barrier();  // stage s + 1 is complete in LDS (the product before touched stage s and the free slot only)
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(integral_constant<int, 1>{}, integral_constant<int, 0>{}, integral_constant<int, 0>{}, std::true_type{});
+                    product(integral_constant<int, 2>{}, integral_constant<int, 1>{}, integral_constant<int, 0>{}, std::false_type{});
+                };
+                for (uint32_t s = 0; s < stages; ++s) iteration(s);
+
+                bool left_half = false;
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 1));
+                    largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 2));
+                    if (largest[h] * scale[h] > kLargestHalf) {
+                        left_half = true;
+                        vexp[h] = scale_exponent(largest[h], kVectorTop);
+                    }
+                }
+                if (attempt == 0 && left_half) *redo_flag = 1;
+                lds_barrier();  // also: the next prologue writes stages that the last iterations read
+                if (attempt > 0 || !*redo_flag) break;
+                lds_barrier();
+                if (threadIdx.x == 0) *redo_flag = 0;  // seen by all; set again behind the barriers of a later prologue only
+            }
+
+            // Epilogue: register 4q + e of block (rb, cb) is function 8q + 4 (l / 32) + e of the
+            // block's 32, vector l % 32.  A block passes through a wave-private piece of LDS (the stages are
+            // free now), from which eight neighbouring lanes take the 32 results of one vector, 128 bytes.
+            int ve[NB];
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb) ve[cb] = vector_exp[vw * 32 * NB + cb * 32 + lr];
+            char *const block = lds_h + wave * (32 * kResultRow);
+#pragma unroll
+            for (int rb = 0; rb < NB; ++rb) {
+                const uint32_t j0 = ft * TF + fw * 32 * NB + rb * 32;
+                const uint32_t j = j0 + 4 * (lane & 7);  // of the results this lane stores
+                intx4 fe[4];
+                floatx4 b4[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    fe[q] = *reinterpret_cast<const intx4 *>(a.fexp + j0 + 8 * q + 4 * lh);  // below kpad
+                    if constexpr (!PROJ) {
+                        b4[q] = *reinterpret_cast<const floatx4 *>(a.off + j0 + 8 * q + 4 * lh);
+                        if constexpr (POW2) b4[q] *= a.inv_w;
+                    }
+                }
+#pragma unroll
+                for (int cb = 0; cb < NB; ++cb) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        uintx4 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float p = __builtin_ldexpf(acc[rb][cb][4 * q + e], -(fe[q][e] + ve[cb]));
+                            if constexpr (PROJ) {
+                                v[e] = __float_as_uint(p);
+                            } else {
+                                const float h = POW2 ? fmaf(p, a.inv_w, b4[q][e]) : (p + b4[q][e]) / a.w;
+                                v[e] = (uint32_t)(int)floorf(h);
+                            }
+                        }
+                        *reinterpret_cast<uintx4 *>(block + lr * kResultRow + q * 32 + lh * 16) = v;
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+                    const uint64_t vec0 = vt * TVW + vw * 32 * NB + cb * 32;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t r = q * 8 + (lane >> 3);
+                        const uintx4 v = *reinterpret_cast<const uintx4 *>(block + r * kResultRow + (lane & 7) * 16);
+                        if (vec0 + r < a.N) {
+                            uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + (vec0 + r) * a.k + j;
+                            if constexpr (VEC) {
+                                if (j < a.k) {
+                                    if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<uintx4 *>(dst));
+                                    else *reinterpret_cast<uintx4 *>(dst) = v;
+                                }
+                            } else {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    if (j + e < a.k) dst[e] = v[e];
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+            lds_barrier();  // the exponents and the results have been read
+        }
+    }
+}
+
+}  // namespace
+
+bool dense_half_used(const lsh_params *p) { return p->m >= kHalfMinTerms; }
+
+// The two fp16 planes of a coefficient matrix [k][n] in the order the kernel reads them,
+// [function tile of 256][stage of 16 coordinates][plane][row][coordinate], zeros beyond k and n, and
+// behind them the exponent (32 bits) of every function.
+void build_half_planes(const float *a, uint32_t k, uint32_t n, uint32_t kpad, uint32_t npad, std::vector<uint16_t> &planes) {
+    const size_t elements = (size_t)2 * kpad * npad;
+    planes.assign(elements + (size_t)2 * kpad, 0);
+    const uint32_t stages = npad / KB;
+    for (uint32_t j = 0; j < k; ++j) {
+        float top = 0.f;
+        for (uint32_t c = 0; c < n; ++c) top = std::fmax(top, std::fabs(a[(size_t)j * n + c]));
+        const int32_t e = top > 0.f && std::isfinite(top) ? kFunctionTop - std::ilogb(top) : 0;
+        std::memcpy(planes.data() + elements + (size_t)2 * j, &e, 4);
+        for (uint32_t c = 0; c < n; ++c) {
+            const float x = std::ldexp(a[(size_t)j * n + c], e);
+            const _Float16 hi = (_Float16)x, lo = (_Float16)(x - (float)hi);
+            const size_t at = ((size_t)(j / TF) * stages + c / KB) * kStagePlanes + (size_t)(j % TF) * KB + c % KB;
+            std::memcpy(planes.data() + at, &hi, 2);
+            std::memcpy(planes.data() + at + TF * KB, &lo, 2);
+        }
+    }
+}
+
+int launch_dense_half(const lsh_params *p, bool proj, const float *d_data, uint64_t N, void *d_out, void *stream) {
+    HalfArgs a;
+    a.data = d_data;
+    a.planes = static_cast<const uint16_t *>(p->d_dense_planes);
+    a.off = p->d_off;
+    a.N = N;
+    a.n = p->n;
+    a.npad = (p->n + KB - 1) / KB * KB;
+    a.k = p->k;
+    a.kpad = (p->k + TF - 1) / TF * TF;
+    a.fexp = reinterpret_cast<const int *>(a.planes + (size_t)2 * a.kpad * a.npad);
+    a.w = p->w;
+    a.inv_w = 1.0f / p->w;
+    a.out = d_out;
+    int exp2 = 0;
+    const bool pw = proj || std::frexp(p->w, &exp2) == 0.5f;
+    const bool vec = p->k % 4 == 0;
+    // one workgroup per CU (97 KB of LDS, all registers), a multiple of 8 so that every XCD gets the same number
+    uint32_t wgs = (uint32_t)(p->num_cus > 0 ? p->num_cus : 256) / 8 * 8;
+    if (wgs < 8) wgs = 8;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+#define LSH_HALF_CASE(P_, W_, V_) \
+    if (proj == P_ && pw == W_ && vec == V_) { \
+        auto fn = &dense_half_kernel<P_, W_, V_>; \
+        if (ensure_lds_limit(reinterpret_cast<const void *>(fn), kLdsBytesH) != LSH_OK) return LSH_ERR_HIP; \
+        hipLaunchKernelGGL(fn, dim3(wgs), dim3(kThreadsH), kLdsBytesH, s, a); \
+    }
+    LSH_HALF_CASE(false, true, true) LSH_HALF_CASE(false, false, true) LSH_HALF_CASE(true, true, true)
+    LSH_HALF_CASE(false, true, false) LSH_HALF_CASE(false, false, false) LSH_HALF_CASE(true, true, false)
+#undef LSH_HALF_CASE
+    return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
+}
+
+}  // namespace lsh

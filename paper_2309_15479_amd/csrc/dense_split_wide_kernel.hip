@@ -397,6 +397,7 @@ bool dense_wide_supported(const lsh_params *p) {
 }
 
 int launch_dense_wide(const lsh_params *p, bool proj, const float *d_data, uint64_t N, void *d_out, void *stream) {
+    if (dense_half_used(p)) return launch_dense_half(p, proj, d_data, N, d_out, stream);
     WideArgs a;
     a.data = d_data;
     a.planes = static_cast<const uint16_t *>(p->d_dense_planes);

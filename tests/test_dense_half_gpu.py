@@ -1,0 +1,83 @@
+"""The dense product from two-way fp16 splits (sums of 128 terms and more, n other than 128) against the
+same sums in 64 bits."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lsh():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2309_15479_amd as lib
+    lib.load_library()
+    return lib
+
+
+def _exact(p, data):
+    a = torch.tensor(p.coeffs(), device="cuda").double().reshape(p.k, p.n)
+    return data.double() @ a.T, data.double().abs() @ a.abs().T
+
+
+def _data(kind, N, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N * 31 + n)
+    x = torch.randn((N, n), generator=g, device="cuda")
+    at = torch.arange(n, device="cuda")
+    if kind == "late":        # nothing in the coordinates a scale is first taken from, but for some vectors
+        x = x * (at >= n - 17) * (torch.arange(N, device="cuda")[:, None] % 7 != 3)
+    elif kind == "rise":      # the last coordinates leave the range the first ones suggest
+        x = x * torch.where(at >= n - 17, 1e4, 1e-3)
+    elif kind == "fall":
+        x = x * torch.where(at >= 16, 1e-5, 1.0)
+    elif kind == "rows":      # every vector of another size
+        x = x * torch.exp(20.0 * torch.randn((N, 1), generator=g, device="cuda"))
+    elif kind == "tiny":
+        x = x * 1e-37
+    elif kind == "huge":
+        x = x * 1e35
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "late", "rise", "fall", "rows", "tiny", "huge"])
+@pytest.mark.parametrize("N,n,k", [(1, 132, 64), (257, 148, 250), (300, 960, 260), (255, 1028, 512)])
+def test_projections(lsh, kind, N, n, k):
+    """Off by at most 2^-22 of sum |a_i v_i| by the split (2^-23 of each operand, rounded pairwise, and the low
+    products left out) and n / 8 * 3 roundings of 2^-24 (the accumulation, one for eight terms and product, all of
+    them at the largest partial sum): 2e-5 at n = 960 in the worst case, a hundredth of that as seen.  The bound
+    here is the repository's 1e-5, and 2e-6 for the distributions that an fp32 sum keeps to that."""
+    data = _data(kind, N, n)
+    print(f"dense fp16 product: {kind} N={N} n={n} k={k}", flush=True)
+    with lsh.LshParams(n, k, n, 4.0, 11) as p:
+        want, size = _exact(p, data)
+        got = lsh.project_e2lsh(p, data).double()
+        p.set_dense_arithmetic(lsh.DENSE_FP32)
+        plain = lsh.project_e2lsh(p, data).double()
+    worst = ((got - want).abs() / size.clamp(min=1e-300)).max().item()
+    assert worst < 2e-6, worst
+    assert (got - want).norm().item() <= 1.5 * (plain - want).norm().item()
+
+
+def test_ids_do_not_depend_on_the_batch(lsh):
+    """A vector's scale is its own: its ids are the same alone, among others, and beside vectors that make
+    their tile be done twice or hold no number at all."""
+    n, k = 964, 300
+    data = _data("normal", 600, n)
+    with lsh.LshParams(n, k, n, 3.0, 12) as p:
+        ids = lsh.hash_e2lsh(p, data)
+        assert torch.equal(lsh.hash_e2lsh(p, data[100:101].clone()), ids[100:101])
+        assert torch.equal(lsh.hash_e2lsh(p, data[37:400].clone()), ids[37:400])
+        odd = data.clone()
+        odd[::5] = _data("rise", 120, n)
+        odd[3] = float("inf")
+        odd[7] = float("nan")
+        odd[11] = 0.0
+        got = lsh.hash_e2lsh(p, odd)
+        same = torch.ones(600, dtype=torch.bool, device="cuda")
+        same[::5] = False
+        same[[3, 7, 11]] = False
+        assert torch.equal(got[same], ids[same])
+        off = torch.tensor(p.offsets(), device="cuda")
+        assert torch.equal(got[11], torch.floor(off / 3.0).int())
