@@ -180,40 +180,52 @@ int launch_offsets_scan(const uint32_t *d_count, uint64_t items, uint64_t *d_par
 // consecutive pairs; wave w of the workgroup owns pairs 1024 w ... 1024 w + 1023 of it, slot i
 // of lane l being pair 64 i + l, so (wave, slot, lane) order is memory order and the ranks
 // below keep equal keys in their original order (ids ascending inside a bucket).  The first
-// pass reads the keys in place from the caller's [N][L] array and numbers the pairs itself.
+// pass takes the keys from where sort_columns put them and numbers the pairs itself.
 constexpr uint32_t kSortThreads = 256, kSortSlots = 16, kSortTile = kSortThreads * kSortSlots;
 constexpr uint32_t kSortWaves = kSortThreads / 64;
 
-template <bool FIRST>
-__device__ __forceinline__ uint64_t sort_key(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L, uint32_t l,
-                                             uint64_t i) {
-    return FIRST ? keys[i * L + l] : keys[(uint64_t)l * N + i];
-}
+// What the first pass starts with: a workgroup takes up to 16 columns of a tile of the caller's rows, counts
+// their first digits and writes the keys column by column, [L][N], so that a wave reads whole pieces of
+// rows and the scatter whole pieces of columns.  (Both read a column of the caller's array before, 8 bytes out of
+// every row: for 1e6 x 32 keys 329 us for the counts and 361 for the scatter; by rows, counts alone, 119.)
+constexpr uint32_t kRowThreads = 1024, kRowColumns = 16, kRowStride = 257;  // a column's bins one bank on from the column before
+constexpr uint32_t kRowLoads = 4, kRowBlock = kRowThreads * kRowLoads;      // keys turned at a time
 
-// Histograms of the first pass: a workgroup counts up to 32 columns of a tile of the caller's rows, so that
-// a wave reads whole pieces of rows (a column at a time, 8 bytes out of every row, took 329 us for 1e6 x 32
-// keys, as long as a scatter; this 119).
-constexpr uint32_t kRowThreads = 1024, kRowColumns = 32, kRowStride = 257;  // a column's bins one bank on from the column before
-
-__global__ __launch_bounds__(kRowThreads) void sort_histogram_rows(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L,
-                                                                    uint32_t columns, uint32_t width, uint32_t tiles,
-                                                                    uint32_t *__restrict__ hist) {
+__global__ __launch_bounds__(kRowThreads) void sort_columns(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L,
+                                                            uint32_t columns, uint32_t width, uint32_t tiles,
+                                                            uint32_t *__restrict__ hist, uint64_t *__restrict__ out) {
     __shared__ uint32_t bins[kRowColumns * kRowStride];
+    __shared__ uint64_t turned[kRowBlock + kRowColumns];  // [column][rows at a time + 1]
     const uint32_t tile = blockIdx.x, l0 = blockIdx.y * columns, here = L - l0 < columns ? L - l0 : columns;
     for (uint32_t b = threadIdx.x; b < kRowColumns * kRowStride; b += kRowThreads) bins[b] = 0;
-    __syncthreads();
-    // width: a power of two, at least `columns` and at most 32
-    const uint32_t column = threadIdx.x & (width - 1), rows = kRowThreads / width;
-    const uint64_t first = (uint64_t)tile * kSortTile;
-    if (column < here) {
-        const uint64_t *at = keys + l0 + column;
-        const uint64_t end = N - first < kSortTile ? N : first + kSortTile;
-        for (uint64_t i = first + threadIdx.x / width; i < end; i += 4 * rows) {
-            uint32_t digit[4];
+    // width: a power of two, at least `columns` and at most 16
+    const uint32_t column = threadIdx.x & (width - 1), row = threadIdx.x / width, step = kRowThreads / width;
+    const uint32_t rows = kRowLoads * step;  // at a time; a tile is `width` times as many
+    const uint64_t first = (uint64_t)tile * kSortTile, end = N - first < kSortTile ? N : first + kSortTile;
+    const uint64_t *at = keys + l0 + (column < here ? column : 0);
+    uint64_t key[kRowLoads];
+    auto load = [&](uint64_t base) __attribute__((always_inline)) {
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) digit[u] = i + u * rows < end ? (uint32_t)at[(i + u * rows) * L] & 255u : 256u;
+        for (uint32_t u = 0; u < kRowLoads; ++u) {
+            const uint64_t i = base + row + u * step;
+            key[u] = at[(i < end ? i : end - 1) * L];
+        }
+    };
+    load(first);
+    for (uint64_t base = first; base < end; base += rows) {
+        __syncthreads();  // the keys before have been written out (and the bins are clear)
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) atomicAdd(&bins[column * kRowStride + digit[u]], 1u);  // word 256 is not read
+        for (uint32_t u = 0; u < kRowLoads; ++u) {
+            turned[column * (rows + 1) + row + u * step] = key[u];
+            if (column < here && base + row + u * step < end) atomicAdd(&bins[column * kRowStride + ((uint32_t)key[u] & 255u)], 1u);
+        }
+        __syncthreads();
+        if (base + rows < end) load(base + rows);
+        const uint32_t rows_here = end - base < rows ? (uint32_t)(end - base) : rows;
+#pragma unroll
+        for (uint32_t u = 0; u < kRowLoads; ++u) {
+            const uint32_t e = threadIdx.x + u * kRowThreads, c = e / rows, r = e & (rows - 1);
+            if (c < here && r < rows_here) out[(uint64_t)(l0 + c) * N + base + r] = turned[c * (rows + 1) + r];
         }
     }
     __syncthreads();
@@ -221,7 +233,9 @@ __global__ __launch_bounds__(kRowThreads) void sort_histogram_rows(const uint64_
         hist[((size_t)l0 * 256 + b) * tiles + tile] = bins[(b >> 8) * kRowStride + (b & 255u)];
 }
 
-// hist[(l * 256 + digit) * tiles + tile] = pairs of the tile with that digit
+// hist[(l * 256 + digit) * tiles + tile] = pairs of the tile with that digit.  Equal keys are neighbours once
+// their lower digits are in order, and a wave that adds 64 of them to one word does so one after the other: the
+// first lane of a run of equal digits adds its length.
 __global__ __launch_bounds__(kSortThreads) void sort_histogram(const uint64_t *__restrict__ keys, uint64_t N,
                                                                 uint32_t shift, uint32_t tiles,
                                                                 uint32_t *__restrict__ hist) {
@@ -236,8 +250,14 @@ __global__ __launch_bounds__(kSortThreads) void sort_histogram(const uint64_t *_
     }
     bins[threadIdx.x] = 0;
     __syncthreads();
+    const uint32_t lane = threadIdx.x & 63;
 #pragma unroll
-    for (uint32_t e = 0; e < kSortSlots; ++e) atomicAdd(&bins[digit[e]], 1u);  // word 256 is not read
+    for (uint32_t e = 0; e < kSortSlots; ++e) {
+        const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)digit[e], 0x138, 0xf, 0xf, false);  // wave_shr:1
+        const uint64_t heads = __ballot(digit[e] != before), later = heads & ~((2ull << lane) - 1);
+        const uint32_t stop = later ? (uint32_t)__builtin_ctzll(later) : 64u;
+        if (digit[e] != before) atomicAdd(&bins[digit[e]], stop - lane);  // word 256 is not read
+    }
     __syncthreads();
     hist[((size_t)l * 256 + threadIdx.x) * tiles + tile] = bins[threadIdx.x];
 }
@@ -278,7 +298,7 @@ __global__ __launch_bounds__(256) void sort_scan(uint32_t *__restrict__ hist, ui
 // registers on this part).
 template <bool FIRST>
 __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__restrict__ keys,
-                                                              const uint32_t *__restrict__ ids, uint64_t N, uint32_t L,
+                                                              const uint32_t *__restrict__ ids, uint64_t N,
                                                               uint32_t shift, uint32_t tiles,
                                                               const uint32_t *__restrict__ offsets,
                                                               const uint32_t *__restrict__ total,
@@ -289,11 +309,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__r
     __shared__ uint32_t wave_total[2][kSortWaves];
     __shared__ uint64_t tile_keys[kSortTile];
     __shared__ uint32_t tile_ids[kSortTile];
-    // first pass: the L workgroups that read one tile of the caller's [N][L] rows run on one XCD (number
-    // modulo 8), one after the other, and find it in its L2 (else every table would fetch the whole array again)
-    const uint32_t at_xcd = blockIdx.x >> 3;
-    const uint32_t l = FIRST ? at_xcd % L : blockIdx.y, tile = FIRST ? at_xcd / L * 8 + (blockIdx.x & 7) : blockIdx.x;
-    if (FIRST && tile >= tiles) return;
+    const uint32_t l = blockIdx.y, tile = blockIdx.x;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (uint32_t w = 0; w < kSortWaves; ++w) counter[w][threadIdx.x] = 0;
     __syncthreads();
@@ -309,7 +325,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter(const uint64_t *__r
 #pragma unroll
     for (uint32_t i = 0; i < kSortSlots; ++i) {
         const uint64_t at = first + (uint64_t)i * 64;
-        key[i] = sort_key<FIRST>(keys, N, L, l, at < N ? at : N - 1);
+        key[i] = keys[(uint64_t)l * N + (at < N ? at : N - 1)];
         id[i] = FIRST ? (uint32_t)at : ids[(uint64_t)l * N + (at < N ? at : N - 1)];
     }
     const uint32_t tile_offset = offsets[((size_t)l * 256 + threadIdx.x) * tiles + tile], digit_total = total[l * 256 + threadIdx.x];
@@ -630,7 +646,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
         (void)hipGetLastError();
         return LSH_ERR_NO_DEVICE;
     }
-    // the first pass launches one workgroup per (tile, table) in a row
+    // the (tile, table) workgroups of a pass are counted in 32 bits
     if (((N + kSortTile - 1) / kSortTile) * L >= (1ull << 31)) return LSH_ERR_UNSUPPORTED;
     lsh_index *ix = new (std::nothrow) lsh_index;
     if (!ix) return LSH_ERR_ALLOC;
@@ -665,7 +681,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
         // eight passes; odd passes write the index's own arrays, so the last one ends there
         for (uint32_t pass = 0; pass < 8; ++pass) {
             const uint32_t shift = 8 * pass;
-            const uint64_t *src_keys = pass == 0 ? d_keys : (pass & 1) ? tmp_keys : ix->d_keys;
+            const uint64_t *src_keys = (pass & 1) ? tmp_keys : ix->d_keys;
             const uint32_t *src_ids = (pass & 1) ? tmp_ids : ix->d_ids;
             uint64_t *dst_keys = (pass & 1) ? ix->d_keys : tmp_keys;
             uint32_t *dst_ids = (pass & 1) ? ix->d_ids : tmp_ids;
@@ -673,18 +689,14 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
                 const uint32_t groups = (L + kRowColumns - 1) / kRowColumns, columns = (L + groups - 1) / groups;
                 uint32_t width = 1;
                 while (width < columns) width *= 2;
-                hipLaunchKernelGGL(sort_histogram_rows, dim3(tiles, groups), dim3(kRowThreads), 0, s, src_keys, N, L, columns,
-                                   width, tiles, hist);
+                hipLaunchKernelGGL(sort_columns, dim3(tiles, groups), dim3(kRowThreads), 0, s, d_keys, N, L, columns, width, tiles,
+                                   hist, ix->d_keys);
             } else {
                 hipLaunchKernelGGL(sort_histogram, grid, block, 0, s, src_keys, N, shift, tiles, hist);
             }
             hipLaunchKernelGGL(sort_scan, dim3(L * 64), dim3(256), 0, s, hist, tiles, L * 256, total);
-            if (pass == 0)
-                hipLaunchKernelGGL(sort_scatter<true>, dim3((tiles + 7) / 8 * 8 * L), block, 0, s, src_keys, src_ids, N, L, shift,
-                                   tiles, hist, total, dst_keys, dst_ids);
-            else
-                hipLaunchKernelGGL(sort_scatter<false>, grid, block, 0, s, src_keys, src_ids, N, L, shift, tiles, hist, total,
-                                   dst_keys, dst_ids);
+            auto scatter = pass == 0 ? sort_scatter<true> : sort_scatter<false>;
+            hipLaunchKernelGGL(scatter, grid, block, 0, s, src_keys, src_ids, N, shift, tiles, hist, total, dst_keys, dst_ids);
         }
         if (hipGetLastError() != hipSuccess) rc = LSH_ERR_HIP;
     }
