@@ -246,16 +246,22 @@ __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledA
         const uint32_t *src = sbase + (size_t)next_block * kBlockWords;
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const uint32_t at = (first_set * QPF + i) * 64 + lane;
-            blk.coef[i] = *reinterpret_cast<const uint4 *>(src + at * 4);
-            blk.off[i] = *reinterpret_cast<const uint2 *>(src + kQuads * 64 * 4 + at * 2);
+            if constexpr (SPLIT) {
+                const uint32_t at = (first_set * QPF + i) * 64 + lane;
+                blk.coef[i] = *reinterpret_cast<const uint4 *>(src + at * 4);
+                blk.off[i] = *reinterpret_cast<const uint2 *>(src + kQuads * 64 * 4 + at * 2);
+            } else {
+                blk.coef[i] = *reinterpret_cast<const uint4 *>(src + (i * 64 + lane) * 4);
+                blk.off[i] = *reinterpret_cast<const uint2 *>(src + U * 64 * 4 + (i * 64 + lane) * 2);
+            }
         }
         next_block = next_block + 1 == sblocks ? 0 : next_block + 1;
     };
     load_block(P);
 
     // function of this lane in set f: sets are kCW apart
-    const uint32_t j0 = ((blockIdx.y * SETS + first_set) * kCW + wave) * 64 + lane;
+    const uint32_t j0 = SPLIT ? ((blockIdx.y * SETS + first_set) * kCW + wave) * 64 + lane
+                              : (blockIdx.y * kCW * FPT + wave) * 64 + lane;
     float bias[FPT];
     uint64_t key_pow[FPT];
 #pragma unroll
