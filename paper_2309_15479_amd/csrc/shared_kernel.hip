@@ -97,6 +97,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
     const uint32_t lane_row = c16 * stride * 4;
     constexpr bool PROJ = EP == 1, KEYS = EP == 2, KAPPA = EP == 3, MDATA = EP == 4, MQUERY = EP == 5;
     constexpr bool NORMS = EP >= 3;
+    constexpr bool kTables = KAPPA && KS >= 32;
     constexpr bool kEarlyStash = EP < 3;
     float bq[RB][4];
     uint32_t fn0[RB];  // first of the lane's four functions, or >= k when it has none
@@ -106,13 +107,14 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
     float kmax[KAPPA ? RB : 1];    // running max of ||S_l(v)||^2 over the vectors this lane has seen
 #pragma unroll
     for (int e = 0; e < RB; ++e) {
-        const uint32_t blk = block0 + e;
+        // the kappa~ pass over long lists takes every table once, by its first block
+        const uint32_t blk = kTables ? (block0 + e) * a.blocks_per_table : block0 + e;
         const bool have = blk < a.nblocks;
         const uint32_t table = blk / a.blocks_per_table, in_table = (blk % a.blocks_per_table) * 16 + q * 4;
         fn0[e] = have && in_table < a.g ? table * a.g + in_table : a.k;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            cf[e][kk] = have ? a.coef[((size_t)blk * KS + kk) * 64 + lane] : 0.f;
+            if constexpr (!KAPPA) cf[e][kk] = have ? a.coef[((size_t)blk * KS + kk) * 64 + lane] : 0.f;
             const uint32_t off = have ? a.sample_off[((size_t)blk * KS + kk) * 4 + q] : 0u;  // < 4 n + 16 < 65536
             if constexpr (kPacked) {
                 if (kk & 1) xo[e][kk / 2] |= off << 16; else xo[e][kk / 2] = off;
@@ -184,8 +186,36 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
 #pragma unroll
                 for (int h = 0; h < KS / 2; ++h) asm volatile("" : "+v"(xo[e][h]));
         }
+        if constexpr (kTables) {
+            // ||S_l(v)||^2 by the operations of the loop below, table after table
+#pragma unroll 1
+            for (uint32_t vb = 0; vb < rows / 16; ++vb) {
+                const uint32_t lane_base = lane_row + vb * 16 * stride * 4;
+#pragma unroll
+                for (int e = 0; e < RB; ++e) {
+                    float nrm = 0.f;
+                    // as above: unpacked where used
+#pragma unroll
+                    for (int h = 0; h < KS / 2; ++h) asm volatile("" : "+v"(xo[e][h]));
+#pragma unroll
+                    for (int k0 = 0; k0 < KS; k0 += 8) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        float x[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const uint32_t pair = xo[e][(k0 + i) / 2];
+                            x[i] = *reinterpret_cast<const float *>(base + (lane_base + ((i & 1) ? pair >> 16 : pair & 0xffffu)));
+                        }
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) nrm = fmaf(x[i], x[i], nrm);
+                    }
+                    const float4v sum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, nrm, float4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    kmax[e] = fmaxf(kmax[e], sum[0]);  // vectors beyond N are zero rows
+                }
+            }
+        }
 #pragma unroll(GEOM ? 8 : 1)
-        for (uint32_t vb = 0; vb < rows / 16; vb += VB) {
+        for (uint32_t vb = 0; vb < (kTables ? 0 : rows / 16); vb += VB) {
             float4v acc[VB][RB];
 #pragma unroll
             for (int u = 0; u < VB; ++u)
@@ -385,8 +415,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
             float v = kmax[e];
 #pragma unroll
             for (int s = 1; s < 16; s *= 2) v = fmaxf(v, __shfl_xor(v, s));
-            if (lane == 0 && block0 + e < a.nblocks)
-                atomicMax(reinterpret_cast<unsigned int *>(a.out) + (block0 + e) / a.blocks_per_table, __float_as_uint(v));
+            const uint32_t table = kTables ? block0 + e : (block0 + e) / a.blocks_per_table;
+            if (lane == 0 && table < a.nblocks / a.blocks_per_table)
+                atomicMax(reinterpret_cast<unsigned int *>(a.out) + table, __float_as_uint(v));
         }
     }
 }
@@ -543,14 +574,30 @@ int launch_shared(const lsh_params *p, int ep, const float *d_data, uint64_t N, 
     a.out = d_out;
     a.staged = pl.staged ? 1 : 0;
     const uint64_t ntiles = (N + pl.rows - 1) / pl.rows;
+    // The kappa~ pass over lists of more than 64 samples: without coefficients a wave has room for the lists
+    // of up to four tables, and every workgroup along the tables reads all of the data.  As long as the tiles
+    // fill the chip: 3e5 vectors, m = 128, 64 tables of 960 dimensions 577 -> 431 us, m = 100, 32 tables of two
+    // blocks, 500 dimensions 662 -> 338; 63 tiles on 63 instead of 252 CUs 27 -> 37 (and lists of 64 samples and
+    // less gain nothing: 217 -> 230 us for 2e5 x 300, 25 tables).
+    uint32_t kblocks = pl.kblocks, tables_per_wave = 1;
+    if (ep == 3 && pl.ksteps == 32) {
+        const uint32_t tables = pl.nblocks / pl.blocks_per_table;
+        auto along = [&] { return (tables + pl.waves * tables_per_wave - 1) / (pl.waves * tables_per_wave); };
+        while (tables_per_wave < 4 && along() > 1 && ntiles * along() > 2ull * p->num_cus) tables_per_wave *= 2;
+        kblocks = along();
+    }
     // persistent workgroups, as many as fit the CUs; a multiple of 8 along x, so that the
     // kblocks workgroups sharing a vector tile land on one XCD
-    uint64_t gx = (uint64_t)p->num_cus * pl.per_cu / pl.kblocks;
+    uint64_t gx = (uint64_t)p->num_cus * pl.per_cu / kblocks;
     gx = gx < 8 ? 8 : gx / 8 * 8;
     if (gx > ntiles) gx = ntiles;
-    dim3 grid((uint32_t)gx, pl.kblocks);
+    dim3 grid((uint32_t)gx, kblocks);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool geom = p->n == 128 && pl.rows == 128 && pl.stride == 132;
+    if (ep == 3 && pl.ksteps == 32 && pl.waves == 16 && !geom) {
+        if (tables_per_wave == 2) return launch(&shared_kernel<32, 2, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
+        if (tables_per_wave == 4) return launch(&shared_kernel<32, 4, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
+    }
 #define LSH_SHARED_EP(KS_, RB_, WAVES_, G_, EP_) \
     if (ep == EP_) return launch(&shared_kernel<KS_, RB_, WAVES_, EP_, G_>, pl.lds_bytes, a, grid, WAVES_ * 64, s);
 #define LSH_SHARED_CASE(KS_, RB_, WAVES_, G_) \
