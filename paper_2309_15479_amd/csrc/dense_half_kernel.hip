@@ -442,6 +442,132 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
     }
 }
 
+// The same product for few vectors, where tiles of 256 x 256 leave most of the chip idle and each of them
+// still walks all stages.  A wave takes 32 functions x 32 vectors with its operands straight from memory, the
+// planes in the order they are stored in and the vectors split in registers: no LDS, no barrier, the
+// loads of kFewSets stages on their way.  Scales, products and their order are those of the kernel above,
+// and so are the results, bit for bit.  Bound by the chain of a stage (three dependent MFMAs, the split) and by 4 KB
+// of loads for every 3 MFMAs, which is why it loses where there are tiles enough.  Tiles / this kernel, by the
+// number of its waves: 8 x 960 x 1024 (32) 60.5 / 14.2 us; 100 x 16000 x 250 (32) 805 / 275; 1000 x 4096 x 512 (512)
+// 211 / 74; 1000 x 960 x 1024 (1024) 64.5 / 21.7; 1e4 x 300 x 250 (2504) 39.0 / 23.5; 4000 x 960 x 1024 (4000) 66 / 79; 8000 x
+// 4096 x 512 (4000) 214 / 291; 3e4 x 132 x 256 (7504) 28.6 / 33.7.  The line is three waves for every SIMD.
+constexpr int kFewSets = 4;
+constexpr uint64_t kFewWaves = 3072;
+
+template <bool PROJ, bool POW2, bool VEC>
+__global__ __launch_bounds__(256) void dense_half_few_kernel(const HalfArgs a) {
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lr = lane & 31, lh = lane >> 5;
+    const uint32_t j0 = (blockIdx.x * 4 + wave) * 32;  // the wave's functions
+    if (j0 >= a.k) return;
+    const uint32_t stages = a.npad / KB;
+    const uint16_t *arow = a.planes + (size_t)(j0 / TF) * stages * kStagePlanes + (j0 % TF + lr) * KB + lh * 8;
+    const uint64_t vec = (uint64_t)blockIdx.y * 32 + lr;
+    const float *vrow = a.data + (vec < a.N ? vec : a.N - 1) * a.n + lh * 8;
+    // as in the kernel above: coordinates beyond n read the vector's first ones, stages beyond the last the last one
+    auto load_v = [&](uint32_t s, floatx4 (&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            v[h] = *reinterpret_cast<const floatx4 *>(vrow + h * 4 + (s * KB + lh * 8 + h * 4 < a.n ? s * KB : 0u));
+    };
+    auto load_a = [&](uint32_t s, halfx8 (&c)[2]) __attribute__((always_inline)) {
+        const uint32_t ka = s < stages ? s : stages - 1;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) c[p] = *reinterpret_cast<const halfx8 *>(arow + (size_t)ka * kStagePlanes + p * (TF * KB));
+    };
+    floatx4 v[kFewSets][2];
+    halfx8 c[kFewSets][2];
+    float largest = 0.f;
+    {
+        floatx4 looked[5][2];
+        const uint32_t at[5] = {0, 1, 2, stages / 3, stages * 2 / 3};
+#pragma unroll
+        for (int t = 0; t < 5; ++t) load_v(at[t], looked[t]);
+#pragma unroll
+        for (int t = 0; t < 5; ++t) largest = largest_of(looked[t][1], largest_of(looked[t][0], largest));
+        largest = fmaxf(largest, __shfl_xor(largest, 32));  // the two lanes of a vector
+        if (largest == 0.f) {
+            for (uint32_t s = 3; s < stages; s += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    floatx4 w[2];
+                    load_v(s + u, w);
+                    largest = largest_of(w[1], largest_of(w[0], largest));
+                }
+            }
+        }
+        largest = fmaxf(largest, __shfl_xor(largest, 32));
+    }
+    int vexp = scale_exponent(largest, kVectorTop);
+    floatx16 acc;
+    for (uint32_t attempt = 0;; ++attempt) {
+        const float scale = power_of_two(vexp);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+        for (int d = 0; d < kFewSets; ++d) {
+            load_v(d, v[d]);
+            load_a(d, c[d]);
+        }
+        for (uint32_t s0 = 0; s0 < stages; s0 += kFewSets) {
+#pragma unroll
+            for (int d = 0; d < kFewSets; ++d) {
+                if (s0 + d < stages) {
+                    halfx8 v1, v2;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        halfx2 hi, lo;
+                        split2(v[d][e / 2][e % 2 * 2], v[d][e / 2][e % 2 * 2 + 1], scale, hi, lo);
+                        v1[2 * e] = hi[0], v1[2 * e + 1] = hi[1];
+                        v2[2 * e] = lo[0], v2[2 * e + 1] = lo[1];
+                    }
+                    largest = largest_of(v[d][1], largest_of(v[d][0], largest));
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v2, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v1, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][1], v1, acc, 0, 0, 0);
+                }
+                load_v(s0 + d + kFewSets, v[d]);
+                load_a(s0 + d + kFewSets, c[d]);
+            }
+        }
+        largest = fmaxf(largest, __shfl_xor(largest, 32));
+        const bool left_half = largest * scale > kLargestHalf;
+        if (attempt > 0 || !__any(left_half)) break;
+        if (left_half) vexp = scale_exponent(largest, kVectorTop);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t j = j0 + 8 * q + 4 * lh;  // < kpad
+        const intx4 fe = *reinterpret_cast<const intx4 *>(a.fexp + j);
+        floatx4 b4 = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (!PROJ) {
+            b4 = *reinterpret_cast<const floatx4 *>(a.off + j);
+            if constexpr (POW2) b4 *= a.inv_w;
+        }
+        uintx4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p = __builtin_ldexpf(acc[4 * q + e], -(fe[e] + vexp));
+            if constexpr (PROJ) {
+                r[e] = __float_as_uint(p);
+            } else {
+                const float h = POW2 ? fmaf(p, a.inv_w, b4[e]) : (p + b4[e]) / a.w;
+                r[e] = (uint32_t)(int)floorf(h);
+            }
+        }
+        if (vec < a.N) {
+            uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + vec * a.k + j;
+            if constexpr (VEC) {
+                if (j < a.k) *reinterpret_cast<uintx4 *>(dst) = r;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (j + e < a.k) dst[e] = r[e];
+            }
+        }
+    }
+}
+
 }  // namespace
 
 bool dense_half_used(const lsh_params *p) { return p->m >= kHalfMinTerms; }
@@ -485,12 +611,16 @@ int launch_dense_half(const lsh_params *p, bool proj, const float *d_data, uint6
     int exp2 = 0;
     const bool pw = proj || std::frexp(p->w, &exp2) == 0.5f;
     const bool vec = p->k % 4 == 0;
+    const uint64_t waves = (N + 31) / 32 * ((p->k + 31) / 32);
+    const bool few = waves <= kFewWaves;
     // one workgroup per CU (97 KB of LDS, all registers), a multiple of 8 so that every XCD gets the same number
     uint32_t wgs = (uint32_t)(p->num_cus > 0 ? p->num_cus : 256) / 8 * 8;
     if (wgs < 8) wgs = 8;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 #define LSH_HALF_CASE(P_, W_, V_) \
-    if (proj == P_ && pw == W_ && vec == V_) { \
+    if (proj == P_ && pw == W_ && vec == V_ && few) { \
+        hipLaunchKernelGGL((dense_half_few_kernel<P_, W_, V_>), dim3((p->k + 127) / 128, (uint32_t)((N + 31) / 32)), dim3(256), 0, s, a); \
+    } else if (proj == P_ && pw == W_ && vec == V_) { \
         auto fn = &dense_half_kernel<P_, W_, V_>; \
         if (ensure_lds_limit(reinterpret_cast<const void *>(fn), kLdsBytesH) != LSH_OK) return LSH_ERR_HIP; \
         hipLaunchKernelGGL(fn, dim3(wgs), dim3(kThreadsH), kLdsBytesH, s, a); \

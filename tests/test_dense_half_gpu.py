@@ -81,3 +81,18 @@ def test_ids_do_not_depend_on_the_batch(lsh):
         assert torch.equal(got[same], ids[same])
         off = torch.tensor(p.offsets(), device="cuda")
         assert torch.equal(got[11], torch.floor(off / 3.0).int())
+
+
+@pytest.mark.parametrize("N,n,k,w", [(40000, 132, 250, 4.0), (15000, 964, 640, 3.0), (12000, 980, 900, 8.0)])
+def test_few_vectors_equal_many(lsh, N, n, k, w):
+    """Few vectors take a kernel of their own: the same numbers, whatever the vectors' scales."""
+    data = _data("normal", N, n)
+    for i, kind in enumerate(("late", "rise", "fall", "rows", "tiny", "huge")):
+        data[i::11] = _data(kind, N, n)[i::11]
+    with lsh.LshParams(n, k, n, w, 13) as p:
+        print(f"dense fp16 product, few against many: n={n} k={k}", flush=True)
+        ids, proj = lsh.hash_e2lsh(p, data), lsh.project_e2lsh(p, data)
+        for first, count in ((0, 1), (31, 33), (N - 257, 257), (5000, 2000)):
+            part = data[first:first + count].clone()
+            assert torch.equal(lsh.project_e2lsh(p, part), proj[first:first + count])
+            assert torch.equal(lsh.hash_e2lsh(p, part), ids[first:first + count])
