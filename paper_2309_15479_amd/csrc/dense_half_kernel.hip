@@ -570,6 +570,34 @@ __global__ __launch_bounds__(256) void dense_half_few_kernel(const HalfArgs a) {
 
 }  // namespace
 
+namespace {
+
+// the fp16 nearest to x (ties to even), |x| below 2^15, and its value: bit arithmetic, since the host's own
+// conversion is a library call per number
+uint16_t to_half(float x, float &value) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    const uint32_t sign = u & 0x80000000u, mag = u ^ sign;
+    uint32_t h, rounded;
+    if (mag >= 0x38800000u) {  // 2^-14: 13 bits of the significand are rounded off
+        rounded = (mag + 0xFFFu + ((mag >> 13) & 1u)) & ~0x1FFFu;
+        h = (rounded >> 13) - (112u << 10);
+    } else {  // a multiple of 2^-24, the spacing of floats at 1/2: the sum rounds to it
+        float s;
+        std::memcpy(&s, &mag, 4);
+        s += 0.5f;
+        std::memcpy(&h, &s, 4);
+        h -= 0x3F000000u;
+        s -= 0.5f;
+        std::memcpy(&rounded, &s, 4);
+    }
+    rounded |= sign;
+    std::memcpy(&value, &rounded, 4);
+    return (uint16_t)(h | (sign >> 16));
+}
+
+}  // namespace
+
 bool dense_half_used(const lsh_params *p) { return p->m >= kHalfMinTerms; }
 
 // The two fp16 planes of a coefficient matrix [k][n] in the order the kernel reads them,
@@ -581,15 +609,20 @@ void build_half_planes(const float *a, uint32_t k, uint32_t n, uint32_t kpad, ui
     const uint32_t stages = npad / KB;
     for (uint32_t j = 0; j < k; ++j) {
         float top = 0.f;
-        for (uint32_t c = 0; c < n; ++c) top = std::fmax(top, std::fabs(a[(size_t)j * n + c]));
-        const int32_t e = top > 0.f && std::isfinite(top) ? kFunctionTop - std::ilogb(top) : 0;
-        std::memcpy(planes.data() + elements + (size_t)2 * j, &e, 4);
         for (uint32_t c = 0; c < n; ++c) {
-            const float x = std::ldexp(a[(size_t)j * n + c], e);
-            const _Float16 hi = (_Float16)x, lo = (_Float16)(x - (float)hi);
+            const float x = std::fabs(a[(size_t)j * n + c]);
+            top = x > top ? x : top;
+        }
+        int32_t e = top > 0.f && std::isfinite(top) ? kFunctionTop - std::ilogb(top) : 0;
+        if (e > 126) e = 126;  // 2^e is a normal float
+        std::memcpy(planes.data() + elements + (size_t)2 * j, &e, 4);
+        const float scale = std::ldexp(1.0f, e);
+        for (uint32_t c = 0; c < n; ++c) {
+            const float x = a[(size_t)j * n + c] * scale;
+            float hi, lo;
             const size_t at = ((size_t)(j / TF) * stages + c / KB) * kStagePlanes + (size_t)(j % TF) * KB + c % KB;
-            std::memcpy(planes.data() + at, &hi, 2);
-            std::memcpy(planes.data() + at + TF * KB, &lo, 2);
+            planes[at] = to_half(x, hi);
+            planes[at + TF * KB] = to_half(x - hi, lo);
         }
     }
 }
