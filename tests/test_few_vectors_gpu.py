@@ -48,3 +48,26 @@ def test_few_vectors_equal_many(lsh, n, k, m, L, w):
                 assert torch.equal(lsh.hash_fastlsh_keys(p, part, L), many["keys"][rows])
                 ids, keys = lsh.hash_fastlsh_ids_keys(p, part, L)
                 assert torch.equal(ids, many["ids"][rows]) and torch.equal(keys, many["keys"][rows])
+
+
+@pytest.mark.parametrize("n,k,m", [(960, 1024, 960), (4096, 2048, 64), (960, 1024, 128)])
+def test_many_captured_after_few(lsh, n, k, m):
+    """A program that has only hashed few vectors so far may capture a launch of many (another kernel, on
+    first use)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    data = torch.randn((9000, n), generator=g, device="cuda")
+    call = lsh.hash_e2lsh if m == n else lsh.hash_fastlsh
+    with lsh.LshParams(n, k, m, 4.0, 21) as p:
+        out = torch.empty((9000, k), dtype=torch.int32, device="cuda")
+        call(p, data[:8].clone())
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call(p, data, out=out)
+        want = call(p, data)
+        for _ in range(3):
+            out.fill_(-7)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
