@@ -45,18 +45,18 @@ CSRC = os.path.join(ROOT, "paper_2309_15479_amd", "csrc")
 # source files still hash to the recorded values; otherwise `traffic` is null.  (FETCH_SIZE counts
 # 64 bytes per read request and these kernels fetch 128-byte lines: a lower bound, see the summary.)
 _KIB = 1024
-_RANGED = {"ranged_kernel.hip": "27e4edf7a84e975a", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
-_STREAMED = {"sampled_kernel.hip": "bea9b29ed7d9a478", "sampled_common.h": "9d6a9ea08ffad892"}
+_RANGED = {"ranged_kernel.hip": "f463328615aec617", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
+_STREAMED = {"sampled_kernel.hip": "df4f64747e76c3a2", "sampled_common.h": "9d6a9ea08ffad892"}
 _SUMMARY = "profiles/hbm_traffic_all_workloads.md"
 MEASURED_TRAFFIC = {
-    "highdim/fastlsh/m64": (1770052 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/fastlsh/m256": (2217169 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/fastlsh/m1024": (4057910 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/e2lsh": (6674183 * _KIB, 2180306 * _KIB, _SUMMARY, {"dense_split_wide_kernel.hip": "f5c3c396883fe4bb"}),
-    "sift/fastlsh/m32": (250604 * _KIB, 2000000 * _KIB, _SUMMARY, _STREAMED),
-    "gist/fastlsh/m128": (2371799 * _KIB, 4000000 * _KIB, _SUMMARY, _STREAMED),
-    "gist/e2lsh": (3704539 * _KIB, 5497154 * _KIB, _SUMMARY, {"dense_split_wide_kernel.hip": "f5c3c396883fe4bb"}),
-    "angular/signs/m512": (58290677 * _KIB, 250024 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m64": (1767065 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m256": (2221315 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m1024": (4060067 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/e2lsh": (4980550 * _KIB, 1631455 * _KIB, _SUMMARY, {"dense_half_kernel.hip": "5c2e3caf3804048f"}),
+    "sift/fastlsh/m32": (250605 * _KIB, 2000000 * _KIB, _SUMMARY, _STREAMED),
+    "gist/fastlsh/m128": (2375589 * _KIB, 4000000 * _KIB, _SUMMARY, _STREAMED),
+    "gist/e2lsh": (3190880 * _KIB, 4068954 * _KIB, _SUMMARY, {"dense_half_kernel.hip": "5c2e3caf3804048f"}),
+    "angular/signs/m512": (56162943 * _KIB, 250022 * _KIB, _SUMMARY, _RANGED),
 }
 
 
