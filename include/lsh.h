@@ -210,11 +210,12 @@ int lsh_hash_e2lsh(const lsh_params_t *params, const float *d_data, uint64_t N,
  * LSH_DENSE_FP32: fp32 MFMA for every dense product, and the gathered fp32 kernels for FastLSH
  * ids, projections, keys and signs at every n.
  * LSH_DENSE_MATRIX: as LSH_DENSE_AUTO, and lsh_hash_fastlsh and lsh_project_fastlsh of an object
- * with m < n and any n that is a multiple of 4 also run as such a product (of fp16 splits if
- * m >= 128, else bf16) over the coefficients written out over all n coordinates (same error bound).  It costs n multiply-adds
+ * with m < n and any n that is a multiple of 4 also run as the six bf16 products over the
+ * coefficients written out over all n coordinates (the error bound of n == 128; coordinates that a
+ * function does not sample have no influence on it, whatever they hold).  It costs n multiply-adds
  * per function where the gather costs m, on matrix cores that are several times faster per
- * multiply-add: on the 4096-dimensional shape it is the faster route from about m = n / 8 on.
- * The first call with this mode builds the object's planes (4 or 6 bytes x k x n of device
+ * multiply-add: on the 4096-dimensional shape it is the faster route from about m = n / 5 on.
+ * The first call with this mode builds the object's planes (6 bytes x k x n of device
  * memory, freed with the object; call it with the object's device current).
  * The mode is a plain field of the object, read by every hash call when it launches: set it
  * while no other thread is calling into the same object (calls already enqueued keep the mode

@@ -508,8 +508,8 @@ int lsh_params_set_dense_arithmetic(lsh_params_t *p, int mode) {
     if (!p || (mode != LSH_DENSE_AUTO && mode != LSH_DENSE_FP32 && mode != LSH_DENSE_MATRIX)) return LSH_ERR_INVALID_ARG;
     if (mode == LSH_DENSE_MATRIX && p->n != 128 && !p->d_dense_planes) {
         // the sampled coefficients written out over all n coordinates (zeros where a function does
-        // not sample, sums where it samples a coordinate more than once), as the planes of
-        // the matrix-core kernels for any n: built on first use
+        // not sample, sums where it samples a coordinate more than once), as the bf16 planes of
+        // the matrix-core kernel for any n: built on first use
         if (p->n % 4 != 0 || (uint64_t)p->k * 4 >= (1ull << 32)) return LSH_ERR_UNSUPPORTED;
         if (p->device < 0) return LSH_ERR_NO_DEVICE;
         int dev = -1;
@@ -523,7 +523,7 @@ int lsh_params_set_dense_arithmetic(lsh_params_t *p, int mode) {
             const uint32_t kpad_wide = (p->k + dense_wide_row_tile() - 1) / dense_wide_row_tile() * dense_wide_row_tile();
             const uint32_t npad = (p->n + dense_wide_col_step() - 1) / dense_wide_col_step() * dense_wide_col_step();
             std::vector<uint16_t> planes;
-            (dense_half_used(p) ? build_half_planes : build_dense_planes)(dense.data(), p->k, p->n, kpad_wide, npad, planes);
+            build_dense_planes(dense.data(), p->k, p->n, kpad_wide, npad, planes);  // m < n: see dense_half_used
             void *d = nullptr;
             if (hipMalloc(&d, planes.size() * sizeof(uint16_t)) != hipSuccess) {
                 (void)hipGetLastError();

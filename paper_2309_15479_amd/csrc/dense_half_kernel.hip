@@ -598,7 +598,10 @@ uint16_t to_half(float x, float &value) {
 
 }  // namespace
 
-bool dense_half_used(const lsh_params *p) { return p->m >= kHalfMinTerms; }
+// Only where every function takes all n coordinates.  A vector's scale comes from all of them, so with m < n (a
+// sampled object under LSH_DENSE_MATRIX) a large coordinate that a function does not sample would push the ones it
+// samples below fp16's range; the bf16 splits have fp32's range and such a coordinate meets coefficient 0.
+bool dense_half_used(const lsh_params *p) { return p->m == p->n && p->m >= kHalfMinTerms; }
 
 // The two fp16 planes of a coefficient matrix [k][n] in the order the kernel reads them,
 // [function tile of 256][stage of 16 coordinates][plane][row][coordinate], zeros beyond k and n, and

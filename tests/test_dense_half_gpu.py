@@ -96,3 +96,28 @@ def test_few_vectors_equal_many(lsh, N, n, k, w):
             part = data[first:first + count].clone()
             assert torch.equal(lsh.project_e2lsh(p, part), proj[first:first + count])
             assert torch.equal(lsh.hash_e2lsh(p, part), ids[first:first + count])
+
+
+@pytest.mark.parametrize("n,k,m,again", [(960, 250, 128, False), (1028, 512, 300, True), (132, 500, 128, False)])
+@pytest.mark.parametrize("large", [1e6, 1e10, 1e30])
+def test_unsampled_coordinates_have_no_influence(lsh, n, k, m, again, large):
+    """Eq. 5 depends on the m coordinates that a function samples alone, also where it runs as a dense product
+    over all n: a large coordinate changes no bit of the functions that do not sample it."""
+    N = 300
+    data = _data("normal", N, n)
+    at = n // 2
+    spoilt = data.clone()
+    spoilt[:, at] = large
+    with lsh.LshParams(n, k, m, 4.0, 17, with_replacement=again) as p:
+        idx = torch.as_tensor(p.indices().astype("int64"), device="cuda").reshape(k, m)
+        without = ~(idx == at).any(1)
+        assert without.any()
+        p.set_dense_arithmetic(lsh.DENSE_MATRIX)
+        print(f"dense product of a sampled object: n={n} k={k} m={m} large={large}", flush=True)
+        assert torch.equal(lsh.project_fastlsh(p, spoilt)[:, without], lsh.project_fastlsh(p, data)[:, without])
+        assert torch.equal(lsh.hash_fastlsh(p, spoilt)[:, without], lsh.hash_fastlsh(p, data)[:, without])
+        a = torch.zeros((k, n), dtype=torch.float64, device="cuda")
+        a.scatter_add_(1, idx, torch.tensor(p.coeffs(), device="cuda").double().reshape(k, m))
+        want, size = spoilt.double() @ a.T, spoilt.double().abs() @ a.abs().T
+        worst = ((lsh.project_fastlsh(p, spoilt).double() - want).abs() / size).max().item()
+        assert worst < 1e-5, worst
