@@ -202,10 +202,12 @@ int lsh_hash_e2lsh(const lsh_params_t *params, const float *d_data, uint64_t N,
  * zero inside which a sign bit is unspecified.  Objects with m == n and another n that is a
  * multiple of 4 run on the matrix cores in lsh_hash_e2lsh and lsh_project_e2lsh too (no products
  * skipped): those with n < 128 by the same six products, those with n > 128 by three products of
- * two-way fp16 splits (23 bits), every vector and function scaled by a power of two of its own first
- * so that nothing leaves fp16.  The split is off by less than 2^-22 of each term |a_i v_i|, or by
- * 2^-33 of the largest coordinate times the largest coefficient where that is more; the sum is rounded half
- * as often and is the closer one to the exact value from 128 terms on.  A vector with an infinite or
+ * two-way fp16 splits (23 bits), every vector and function scaled by a power of two of its own first,
+ * for vectors that many coordinates carry, and by the six products for the others: vectors
+ * of fewer than eight coordinates (of 80 looked at) within 1/128 of the largest, or with one some hundred times
+ * as large as those.  An fp16 split is off by less than 2^-22 of each term |a_i v_i|; the sum is rounded half
+ * as often and is the closer one to the exact value from 128 terms on.  Either way projections stay within
+ * 1e-5 * sum_i |a_i v_i|, and which way a vector goes depends on the vector alone.  A vector with an infinite or
  * NaN coordinate has no defined result, as before.  Any other shape uses fp32 MFMA.
  * LSH_DENSE_FP32: fp32 MFMA for every dense product, and the gathered fp32 kernels for FastLSH
  * ids, projections, keys and signs at every n.

@@ -21,6 +21,8 @@ void free_tables(lsh_params *p) {
     if (p->d_dense) (void)hipFree(p->d_dense);
     if (p->d_dense_planes) (void)hipFree(p->d_dense_planes);
     p->d_dense_planes = nullptr;
+    if (p->d_half_planes) (void)hipFree(p->d_half_planes);
+    p->d_half_planes = nullptr;
     if (p->d_triples) (void)hipFree(p->d_triples);
     if (p->d_list_len) (void)hipFree(p->d_list_len);
     if (p->d_stream) (void)hipFree(p->d_stream);
@@ -175,14 +177,20 @@ int upload_tables(lsh_params *p) {
                                           hipMemcpyHostToDevice) != hipSuccess)
                 rc = LSH_ERR_HIP;
             if (rc == LSH_OK && wide) {
-                // the same matrix split into bf16 or fp16 planes, for the wide matrix-core kernels
+                // the same matrix split into bf16 planes (and fp16 planes), for the wide matrix-core kernels
                 const uint32_t npad = (p->n + dense_wide_col_step() - 1) / dense_wide_col_step() * dense_wide_col_step();
                 std::vector<uint16_t> planes;
-                (dense_half_used(p) ? build_half_planes : build_dense_planes)(p->coef.data(), p->k, p->n, kpad_wide, npad, planes);
-                if (hipMalloc(&p->d_dense_planes, planes.size() * sizeof(uint16_t)) != hipSuccess) rc = LSH_ERR_ALLOC;
-                if (rc == LSH_OK && hipMemcpy(p->d_dense_planes, planes.data(), planes.size() * sizeof(uint16_t),
-                                              hipMemcpyHostToDevice) != hipSuccess)
-                    rc = LSH_ERR_HIP;
+                auto upload = [&](void **dst) {
+                    if (rc == LSH_OK && hipMalloc(dst, planes.size() * sizeof(uint16_t)) != hipSuccess) rc = LSH_ERR_ALLOC;
+                    if (rc == LSH_OK && hipMemcpy(*dst, planes.data(), planes.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess)
+                        rc = LSH_ERR_HIP;
+                };
+                build_dense_planes(p->coef.data(), p->k, p->n, kpad_wide, npad, planes);
+                upload(&p->d_dense_planes);
+                if (dense_half_used(p)) {
+                    build_half_planes(p->coef.data(), p->k, p->n, kpad_wide, npad, planes);
+                    upload(&p->d_half_planes);
+                }
             }
         }
     } catch (const std::bad_alloc &) {

@@ -12,12 +12,25 @@
 // 2.5e-7 at 512, 2.5e-7 / 3.5e-7 at 960; kHalfMinTerms is where the fp16 product is the more accurate one.
 //
 // Scales.  e is a function's (on the host, from its largest coefficient: [2^14, 2^15) after scaling)
-// or a vector's.  A vector's comes from up to 80 of its coordinates, the three stages that start the
-// contraction and two further on: the largest of them goes to [2^8, 2^9), so the others may
-// be 128 times larger before they leave fp16, and whatever is smaller loses at most 2^-33 of the
-// largest.  A vector whose looked-at coordinates are all zero is read through for its largest one.  The
-// loading threads keep the largest coordinate they met: should one have left fp16, the tile is done once
-// more with that vector's scale taken from it.  So a vector's scale depends on the vector alone.
+// or a vector's.  A vector's comes from 80 of its coordinates, the three stages that start the
+// contraction and two further on.  If eight of them are at least an eighth of the largest, the largest goes to
+// [2^5, 2^6), and any other coordinate may be a thousand times larger before it leaves fp16; if eight are at least a 128th,
+// to [2^9, 2^10), with room for 64 times more.  Eight coordinates are 4 and more then, and what any
+// coordinate loses below 2^-24, at most 2^-25, is nothing beside their products.  Such a vector is regular, unless a
+// coordinate leaves fp16.
+//
+// Odd vectors.  In any other vector (sparse, or of coordinates of very different sizes) a few coordinates may
+// carry the sum, and where a function has small coefficients at those, what the others lost would be more than the 1e-5
+// of sum |a_i v_i| that a projection may be off.  Their results come from the exact bf16 splits instead, the
+// same numbers as dense_split_wide_kernel.hip gives: a workgroup puts the odd vectors of kSegment tiles by
+// and contracts them together (dense_wide_tile.h).  Tiles of nearly only odd vectors are not contracted in
+// fp16 at all; their few regular ones are put by, too.  A coordinate that leaves fp16 is met in the contraction, which
+// then was for nothing; a workgroup to which that has happened with half a tile looks at the same place of its later
+// tiles first.  Which way a vector goes, and its scale, depend on the vector alone.
+// N = 2e5, n = 960, k = 1024, us, this kernel / the six bf16 products for all vectors: normal coordinates 1240 / 1980,
+// 30 % of them not zero 1150 / 1890, 10 % (half of the vectors odd) 1930 / 1790, 2 % 1790 / 1710, one per vector 1700 / 1630,
+// ratios of two normal ones 1530 / 2000, columns of sizes from 1 to 10^6 1240 / 1990, one column 10^4 times as large
+// 2140 / 1960 if it is looked at, 2630 / 1980 if not (seven vectors in ten odd, none known before the contraction).
 //
 //   V [N][n] fp32 row-major; A split on the host into two fp16 planes in the order of use:
 //   [function tile of 256][stage of 16 coordinates][plane][row][coordinate] (zero rows up to a multiple
@@ -43,7 +56,7 @@
 #include <utility>
 #include <vector>
 
-#include "device_utils.h"
+#include "dense_wide_tile.h"
 #include "lsh_internal.h"
 
 namespace lsh {
@@ -52,28 +65,38 @@ namespace {
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
-constexpr int TF = 256;    // functions per tile
-constexpr int TVW = 256;   // vectors per tile
-constexpr int NB = 4;      // 32 x 32 blocks of a wave along either axis
-constexpr int KB = 16;     // coordinates per stage = one MFMA step
-constexpr int ROWB = 32;   // bytes per row and plane in a stage: two 16-byte halves, swapped in rows with bit 3 set
-constexpr int A_PLANE = TF * ROWB, V_PLANE = TVW * ROWB;
+// the tile of dense_wide_tile.h
+using wide::floatx16;
+using wide::floatx4;
+using wide::uintx4;
+using wide::TF;
+using wide::TVW;
+using wide::NB;
+using wide::KB;
+using wide::ROWB;
+using wide::A_PLANE;
+using wide::V_PLANE;
 constexpr int STAGE = 2 * (A_PLANE + V_PLANE);  // 32768 bytes
 constexpr int kThreadsH = 256;
 constexpr int kStagePlanes = 2 * TF * KB;  // fp16 elements of one function tile's two planes in one stage
 constexpr int kVectorScales = 3 * STAGE;   // LDS offset of the tile's 256 vector exponents
-constexpr int kRedo = kVectorScales + TVW * 4;
-constexpr int kLdsBytesH = kRedo + 16;
+constexpr uint32_t kSegment = 16;          // tiles after which the odd vectors put by are contracted
+constexpr int kOddList = wide::kLdsBytes;  // LDS offset of their numbers in the segment, 16 bits each
+constexpr int kOddCount = kOddList + (int)kSegment * TVW * 2;  // of the words below
+constexpr int kLdsBytesH = kOddCount + 24;
+constexpr uint32_t kFewRegular = 48;       // a tile with so few regular vectors is not contracted: they are put by as well, for few_block (1.6 us each; the tile 94)
+constexpr uint32_t kFewOdd = 64;           // up to so many by blocks of 32 x 32 (80 us at n = 960), more by tiles (150 us)
 constexpr int kResultRow = 144;            // bytes of a vector's 32 results in LDS on their way out: conflict-free both ways
 constexpr uint32_t kHalfMinTerms = 128;
 constexpr float kLargestHalf = 65504.f;
-constexpr int kVectorTop = 8, kFunctionTop = 14;  // exponent of the largest looked-at coordinate and coefficient after scaling
+constexpr int kFunctionTop = 14;                  // exponent of a function's largest coefficient after scaling
+constexpr int kEvenTop = 5, kUnevenTop = 9;       // of a vector's largest looked-at coordinate, see vector_scale
+constexpr int kRegularCount = 8;                  // looked-at coordinates of 2^2 and more after scaling that make a vector regular
+constexpr float kRegularLeast = 1.17549435e-38f;  // 2^-126, which the largest scale, 2^126, takes to 1
+constexpr int kOdd = 4096;                        // added to the exponent of an odd vector
 
 struct HalfArgs {
     const float *data;       // [N][n]
@@ -84,6 +107,9 @@ struct HalfArgs {
     uint32_t n, npad, k, kpad;
     float w, inv_w;
     void *out;               // [N][k]
+    const uint16_t *exact_planes;  // the bf16 planes, as in wide::Args
+
+    __device__ wide::Args exact() const { return {data, exact_planes, off, N, n, npad, k, kpad, w, inv_w, out}; }
 };
 
 // exponent e that takes a value's leading bit to 2^top; 2^e is a normal float
@@ -99,6 +125,33 @@ __device__ __forceinline__ float largest_of(floatx4 v, float so_far) {
     return fmaxf(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), so_far), fmaxf(fabsf(v[2]), fabsf(v[3])));
 }
 
+// how many are at least an eighth of the largest of all, and in the upper half how many at least a 128th
+__device__ __forceinline__ uint32_t count_large(floatx4 v, float largest) {
+    uint32_t count = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        count += (fabsf(v[e]) >= largest * 0x1p-3f ? 1u : 0u) + (fabsf(v[e]) >= largest * 0x1p-7f ? 0x10000u : 0u);
+    return count;
+}
+
+// The exponent for a vector from its largest looked-at coordinate and their count; kOdd is added if it is odd.
+__device__ __forceinline__ int vector_scale(float largest, uint32_t count) {
+    const bool even = (count & 0xFFFFu) >= kRegularCount, uneven = (count >> 16) >= kRegularCount;
+    return scale_exponent(largest, even ? kEvenTop : kUnevenTop) + (uneven && largest >= kRegularLeast ? 0 : kOdd);
+}
+
+// vectors put by: a list of their numbers in the tiles tile, tile + step, ...
+struct Listed {
+    const uint16_t *list;
+    uint64_t tile, step;
+    uint32_t last, first = 0;
+    __device__ uint64_t wanted(uint32_t i) const {
+        const uint32_t in = list[first + i];
+        return (tile + in / TVW * step) * TVW + in % TVW;
+    }
+    __device__ uint64_t any(uint32_t i) const { return wanted(first + i < last ? i : last - first); }
+};
+
 // two elements, scaled and split: hi + lo = x 2^e to 23 bits
 __device__ __forceinline__ void split2(float x0, float x1, float scale, halfx2 &hi, halfx2 &lo) {
     const floatx2 y = {x0 * scale, x1 * scale};
@@ -109,14 +162,145 @@ __device__ __forceinline__ void split2(float x0, float x1, float scale, halfx2 &
 
 // PROJ: raw projections instead of bucket ids.  POW2: w is a power of two (fma(p, 1/w, b/w) is
 // then the same float as (p + b) / w).  VEC: k is a multiple of 4 (16-byte stores).
+//
+// The same product for few vectors, where tiles of 256 x 256 leave most of the chip idle and each of them
+// still walks all stages.  A wave takes 32 functions x 32 vectors with its operands straight from memory, the
+// planes in the order they are stored in and the vectors split in registers: no LDS, no barrier, the
+// loads of kFewSets stages on their way.  Scales, products and their order are those of the tile kernel below,
+// and so are the results, bit for bit.  Bound by the chain of a stage (three dependent MFMAs, the split) and by 4 KB
+// of loads for every 3 MFMAs, which is why it loses where there are tiles enough.  Tiles / this kernel, by the
+// number of its waves: 8 x 960 x 1024 (32) 60.5 / 14.2 us; 100 x 16000 x 250 (32) 805 / 275; 1000 x 4096 x 512 (512)
+// 211 / 74; 1000 x 960 x 1024 (1024) 64.5 / 21.7; 1e4 x 300 x 250 (2504) 39.0 / 23.5; 4000 x 960 x 1024 (4000) 66 / 79; 8000 x
+// 4096 x 512 (4000) 214 / 291; 3e4 x 132 x 256 (7504) 28.6 / 33.7.  The line is three waves for every SIMD.
+constexpr int kFewSets = 4;
+constexpr uint64_t kFewWaves = 3072;
+
+// Functions j0 ... j0 + 31 (j0 a multiple of 32 below k) against 32 vectors: lanes l and l + 32 take vector `row` and
+// store its results if `store`.
+template <bool PROJ, bool POW2, bool VEC>
+__device__ __forceinline__ void few_block(const HalfArgs &a, uint32_t thread, uint32_t j0, uint64_t row, bool store) {
+    const uint32_t lane = thread & 63, lr = lane & 31, lh = lane >> 5;
+    const uint32_t stages = a.npad / KB;
+    const uint16_t *arow = a.planes + (size_t)(j0 / TF) * stages * kStagePlanes + (j0 % TF + lr) * KB + lh * 8;
+    const float *vrow = a.data + row * a.n + lh * 8;
+    // as in the tile kernel: coordinates beyond n read the vector's first ones, stages beyond the last the last one
+    auto load_v = [&](uint32_t s, floatx4 (&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            v[h] = *reinterpret_cast<const floatx4 *>(vrow + h * 4 + (s * KB + lh * 8 + h * 4 < a.n ? s * KB : 0u));
+    };
+    auto load_a = [&](uint32_t s, halfx8 (&c)[2]) __attribute__((always_inline)) {
+        const uint32_t ka = s < stages ? s : stages - 1;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) c[p] = *reinterpret_cast<const halfx8 *>(arow + (size_t)ka * kStagePlanes + p * (TF * KB));
+    };
+    floatx4 v[kFewSets][2];
+    halfx8 c[kFewSets][2];
+    float largest = 0.f;
+    int vexp;
+    bool odd;
+    {
+        floatx4 looked[5][2];
+        const uint32_t at[5] = {0, 1, 2, stages / 3, stages * 2 / 3};
+#pragma unroll
+        for (int t = 0; t < 5; ++t) load_v(at[t], looked[t]);
+#pragma unroll
+        for (int t = 0; t < 5; ++t) largest = largest_of(looked[t][1], largest_of(looked[t][0], largest));
+        largest = fmaxf(largest, __shfl_xor(largest, 32));  // the two lanes of a vector
+        uint32_t count = 0;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) count += count_large(looked[t][0], largest) + count_large(looked[t][1], largest);
+        count += __shfl_xor(count, 32);
+        vexp = vector_scale(largest, count);
+        odd = vexp >= kOdd / 2;
+        if (odd) vexp = 0;
+    }
+    floatx16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    if (__any(!odd)) {
+        const float scale = power_of_two(vexp);
+#pragma unroll
+        for (int d = 0; d < kFewSets; ++d) {
+            load_v(d, v[d]);
+            load_a(d, c[d]);
+        }
+        for (uint32_t s0 = 0; s0 < stages; s0 += kFewSets) {
+#pragma unroll
+            for (int d = 0; d < kFewSets; ++d) {
+                if (s0 + d < stages) {
+                    halfx8 v1, v2;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        halfx2 hi, lo;
+                        split2(v[d][e / 2][e % 2 * 2], v[d][e / 2][e % 2 * 2 + 1], scale, hi, lo);
+                        v1[2 * e] = hi[0], v1[2 * e + 1] = hi[1];
+                        v2[2 * e] = lo[0], v2[2 * e + 1] = lo[1];
+                    }
+                    largest = largest_of(v[d][1], largest_of(v[d][0], largest));
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v2, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v1, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][1], v1, acc, 0, 0, 0);
+                }
+                load_v(s0 + d + kFewSets, v[d]);
+                load_a(s0 + d + kFewSets, c[d]);
+            }
+        }
+        largest = fmaxf(largest, __shfl_xor(largest, 32));
+        odd |= largest * scale > kLargestHalf;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t j = j0 + 8 * q + 4 * lh;  // < kpad
+        const intx4 fe = *reinterpret_cast<const intx4 *>(a.fexp + j);
+        floatx4 b4 = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (!PROJ) {
+            b4 = *reinterpret_cast<const floatx4 *>(a.off + j);
+            if constexpr (POW2) b4 *= a.inv_w;
+        }
+        uintx4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p = __builtin_ldexpf(acc[4 * q + e], -(fe[e] + vexp));
+            if constexpr (PROJ) {
+                r[e] = __float_as_uint(p);
+            } else {
+                const float h = POW2 ? fmaf(p, a.inv_w, b4[e]) : (p + b4[e]) / a.w;
+                r[e] = (uint32_t)(int)floorf(h);
+            }
+        }
+        if (store) {
+            uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + row * a.k + j;
+            if constexpr (VEC) {
+                if (j < a.k) *reinterpret_cast<uintx4 *>(dst) = r;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (j + e < a.k) dst[e] = r[e];
+            }
+        }
+    }
+    odd = odd && store;
+    if (__any(odd)) wide::block<PROJ, POW2, VEC>(a.exact(), thread, j0, row, odd);  // the same lane stores over its results
+}
+
+template <bool PROJ, bool POW2, bool VEC>
+__global__ __launch_bounds__(256) void dense_half_few_kernel(const HalfArgs a) {
+    const uint32_t j0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 32;  // the wave's functions
+    const uint64_t vec = (uint64_t)blockIdx.y * 32 + (threadIdx.x & 31);
+    if (j0 < a.k) few_block<PROJ, POW2, VEC>(a, threadIdx.x, j0, vec < a.N ? vec : a.N - 1, vec < a.N);
+}
+
 template <bool PROJ, bool POW2, bool VEC>
 __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a) {
-    extern __shared__ __align__(16) char lds_h[];  // 3 stages x ([2][256][32] coefficients, [2][256][32] vectors), exponents, flag
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lr = lane & 31, lh = lane >> 5;
-    const uint32_t fw = wave & 1, vw = wave >> 1;  // the wave's half of the functions, half of the vectors
+    extern __shared__ __align__(16) char lds_h[];  // 3 stages x ([2][256][32] coefficients, [2][256][32] vectors), exponents; odd vectors
     int *const vector_exp = reinterpret_cast<int *>(lds_h + kVectorScales);
-    volatile int *const redo_flag = reinterpret_cast<int *>(lds_h + kRedo);
+    uint16_t *const odd_list = reinterpret_cast<uint16_t *>(lds_h + kOddList);
+    volatile uint32_t *const odd_count = reinterpret_cast<uint32_t *>(lds_h + kOddCount);  // from the front of the list
+    volatile uint32_t *const few_count = odd_count + 1;    // regular vectors of tiles with few of them, from its back
+    volatile uint32_t *const regular_count = odd_count + 2;  // in a tile; two, taken in turn
+    volatile uint32_t *const left_count = odd_count + 4;   // vectors of a tile of which a coordinate left fp16
+    volatile uint32_t *const left_stage = odd_count + 5;   // where one did, of the last tile with many
 
     // which (function tile, vector tile) pairs this workgroup takes
     const uint32_t F = a.kpad / TF;
@@ -131,16 +315,7 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
         rep = x / F;
     }
 
-    // loading roles: 16 bytes of the vector tile and of each coefficient plane per stage
-    const uint32_t vr = threadIdx.x >> 2, vq = threadIdx.x & 3;  // vector rows vr + 64 h (h < 4), 4-coordinate piece
-    const uint32_t ar = threadIdx.x >> 1, ah = threadIdx.x & 1;  // coefficient rows ar and ar + 128, 8-coordinate half
     const uint32_t stages = a.npad / KB;
-
-    // operand read and write offsets inside a stage (half h of row r sits at 16 * (h ^ bit 3 of r))
-    const uint32_t rd_a = (fw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);                // + rb * 32 rows + plane
-    const uint32_t rd_v = 2 * A_PLANE + (vw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);  // + cb * 32 rows + plane
-    const uint32_t wr_a = ar * ROWB + ((ah ^ ((ar >> 3) & 1)) << 4);
-    const uint32_t wr_v = 2 * A_PLANE + vr * ROWB + (((vq >> 1) ^ ((vr >> 3) & 1)) << 4) + ((vq & 1) << 3);
 
     // as in dense_split_wide_kernel: the function tiles of a vector tile side by side on one XCD
     const bool by_vector = per_xcd % F == 0 && F <= per_xcd;
@@ -153,11 +328,28 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
         vt_step = 8ull * groups;
     }
     const bool whole_lines = a.k % 32 == 0;  // non-temporal stores then; of partial lines they are slower (341 against 302 us at k = 252)
-    if (threadIdx.x == 0) *redo_flag = 0;
+    if (threadIdx.x < 6) odd_count[threadIdx.x] = 0;
+    lds_barrier();
+    uint32_t turn = 0;  // of the two counts
     for (uint32_t ft = ft_first; ft < F; ft += ft_step) {
-        // thread t: 16 bytes at 16 t of rows 0-127 of a plane, and of rows 128-255
-        const uint16_t *arow = a.planes + (size_t)ft * stages * kStagePlanes + threadIdx.x * 8;
+        uint32_t tiles = 0;  // since the odd vectors were last contracted
         for (uint64_t vt = vt_first; vt < Vt; vt += vt_step) {
+            uint32_t thread = threadIdx.x;
+            asm volatile("" : "+v"(thread));  // or every address made from it would be held through all tiles, in memory
+            const uint32_t lane = thread & 63, wave = __builtin_amdgcn_readfirstlane(thread >> 6);
+            const uint32_t lr = lane & 31, lh = lane >> 5;
+            const uint32_t fw = wave & 1, vw = wave >> 1;  // the wave's half of the functions, half of the vectors
+            // loading roles: 16 bytes of the vector tile and of each coefficient plane per stage
+            const uint32_t vr = thread >> 2, vq = thread & 3;  // vector rows vr + 64 h (h < 4), 4-coordinate piece
+            const uint32_t ar = thread >> 1, ah = thread & 1;  // coefficient rows ar and ar + 128, 8-coordinate half
+
+            // operand read and write offsets inside a stage (half h of row r sits at 16 * (h ^ bit 3 of r))
+            const uint32_t rd_a = (fw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);                // + rb * 32 rows + plane
+            const uint32_t rd_v = 2 * A_PLANE + (vw * 32 * NB + lr) * ROWB + ((lh ^ ((lr >> 3) & 1)) << 4);  // + cb * 32 rows + plane
+            const uint32_t wr_a = ar * ROWB + ((ah ^ ((ar >> 3) & 1)) << 4);
+            const uint32_t wr_v = 2 * A_PLANE + vr * ROWB + (((vq >> 1) ^ ((vr >> 3) & 1)) << 4) + ((vq & 1) << 3);
+            // thread t: 16 bytes at 16 t of rows 0-127 of a plane, and of rows 128-255
+            const uint16_t *arow = a.planes + (size_t)ft * stages * kStagePlanes + thread * 8;
             const float *vrow[4];
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
@@ -179,9 +371,9 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
             };
             floatx16 acc[NB][NB];
             float scale[4], largest[4];
-            int vexp[4];
-            for (uint32_t attempt = 0;; ++attempt) {
-                // stages 0 to 2 and, the first time, the coordinates the scales are taken from: all in flight at once
+            bool contracted;
+            {
+                // stages 0 to 2 and the coordinates the scales are taken from: all in flight at once
                 floatx4 gv[3][4];
                 uintx4 ga[3][2][2];
 #pragma unroll
@@ -193,38 +385,48 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
 #pragma unroll
                         for (int p = 0; p < 2; ++p) ga[t][h][p] = load_a(t, h, p);
                 }
-                if (attempt == 0) {
-                    floatx4 far_v[2][4];
+                floatx4 far_v[2][4];
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < 2; ++t)
 #pragma unroll
-                        for (int h = 0; h < 4; ++h) far_v[t][h] = load_v(stages * (t + 1) / 3, h);
+                    for (int h = 0; h < 4; ++h) far_v[t][h] = load_v(stages * (t + 1) / 3, h);
+                float there[4] = {0.f, 0.f, 0.f, 0.f};  // where many of an earlier tile's vectors left fp16: they turn out odd at once
+                const uint32_t before = __builtin_amdgcn_readfirstlane(*left_stage);
+                if (before) {
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) there[h] = largest_of(load_v(before, h), 0.f);
 #pragma unroll
                     for (int h = 0; h < 4; ++h) {
-                        float top = 0.f;
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) top = largest_of(gv[t][h], top);
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) top = largest_of(far_v[t][h], top);
-                        top = fmaxf(top, __shfl_xor(top, 1));  // the four threads of a vector are neighbours
-                        top = fmaxf(top, __shfl_xor(top, 2));
-                        if (top == 0.f) {
-                            for (uint32_t s = 3; s < stages; s += 8) {
-#pragma unroll
-                                for (int u = 0; u < 8; ++u) top = largest_of(load_v(s + u, h), top);
-                            }
-                        }
-                        top = fmaxf(top, __shfl_xor(top, 1));
-                        top = fmaxf(top, __shfl_xor(top, 2));
-                        vexp[h] = scale_exponent(top, kVectorTop);
-                        largest[h] = top;
+                        there[h] = fmaxf(there[h], __shfl_xor(there[h], 1));
+                        there[h] = fmaxf(there[h], __shfl_xor(there[h], 2));
                     }
                 }
+                uint32_t regular = 0;
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    scale[h] = power_of_two(vexp[h]);
-                    if (vq == 0) vector_exp[vr + h * 64] = vexp[h];
+                    float top = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) top = largest_of(gv[t][h], top);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) top = largest_of(far_v[t][h], top);
+                    top = fmaxf(top, __shfl_xor(top, 1));  // the four threads of a vector are neighbours
+                    top = fmaxf(top, __shfl_xor(top, 2));
+                    uint32_t count = 0;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) count += count_large(gv[t][h], top);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) count += count_large(far_v[t][h], top);
+                    count += __shfl_xor(count, 1);
+                    count += __shfl_xor(count, 2);
+                    int e = vector_scale(top, count);
+                    if (e < kOdd / 2 && there[h] * power_of_two(e) > kLargestHalf) e += kOdd;
+                    regular += __popcll(__ballot(vq == 0 && e < kOdd / 2));
+                    scale[h] = power_of_two(e < kOdd / 2 ? e : 0);
+                    largest[h] = top;
+                    if (vq == 0) vector_exp[vr + h * 64] = e;
                 }
+                if (lane == 0) atomicAdd(const_cast<uint32_t *>(regular_count) + turn, regular);
+                if (thread == 0) *left_count = 0;
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     char *stage = lds_h + t * STAGE;
@@ -355,215 +557,134 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
                     product(integral_constant<int, 1>{}, integral_constant<int, 0>{}, integral_constant<int, 0>{}, std::true_type{});
                     product(integral_constant<int, 2>{}, integral_constant<int, 1>{}, integral_constant<int, 0>{}, std::false_type{});
                 };
-                for (uint32_t s = 0; s < stages; ++s) iteration(s);
-
-                bool left_half = false;
+                contracted = __builtin_amdgcn_readfirstlane(regular_count[turn]) > kFewRegular;
+                bool mine = false;  // a coordinate that this thread brings in of row vr left fp16
+                if (contracted) {
+                    for (uint32_t s = 0; s < stages; ++s) iteration(s);
+                    mine = largest[0] * scale[0] > kLargestHalf;
+                    uint32_t left = 0;
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 1));
-                    largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 2));
-                    if (largest[h] * scale[h] > kLargestHalf) {
-                        left_half = true;
-                        vexp[h] = scale_exponent(largest[h], kVectorTop);
+                    for (int h = 0; h < 4; ++h) {
+                        largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 1));
+                        largest[h] = fmaxf(largest[h], __shfl_xor(largest[h], 2));
+                        const bool leaves = vq == 0 && largest[h] * scale[h] > kLargestHalf;
+                        if (leaves) vector_exp[vr + h * 64] = kOdd;
+                        left += __popcll(__ballot(leaves));
+                    }
+                    if (lane == 0 && left) atomicAdd(const_cast<uint32_t *>(left_count), left);
+                }
+                lds_barrier();  // also: the next prologue writes stages that the last iterations read
+                if (contracted && __builtin_amdgcn_readfirstlane(*left_count) >= TVW / 2 && __any(mine)) {
+                    for (uint32_t s = 3; s < stages; s += 4) {
+                        floatx4 w[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) w[u] = load_v(s + u, 0);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (mine && s + u < stages && largest_of(w[u], 0.f) * scale[0] > kLargestHalf) *left_stage = s + u;
                     }
                 }
-                if (attempt == 0 && left_half) *redo_flag = 1;
-                lds_barrier();  // also: the next prologue writes stages that the last iterations read
-                if (attempt > 0 || !*redo_flag) break;
-                lds_barrier();
-                if (threadIdx.x == 0) *redo_flag = 0;  // seen by all; set again behind the barriers of a later prologue only
+            }
+            turn ^= 1;
+            if (thread == 0) regular_count[turn] = 0;  // added to again behind the barrier that ends this tile
+            if (vt * TVW + thread < a.N) {
+                const uint16_t in = (uint16_t)(tiles * TVW + thread);
+                if (vector_exp[thread] >= kOdd / 2) odd_list[atomicAdd(const_cast<uint32_t *>(odd_count), 1u)] = in;
+                else if (!contracted) odd_list[kSegment * TVW - 1 - atomicAdd(const_cast<uint32_t *>(few_count), 1u)] = in;
             }
 
-            // Epilogue: register 4q + e of block (rb, cb) is function 8q + 4 (l / 32) + e of the
+            // Epilogue (odd vectors' results are stored over later): register 4q + e of block (rb, cb) is function 8q + 4 (l / 32) + e of the
             // block's 32, vector l % 32.  A block passes through a wave-private piece of LDS (the stages are
             // free now), from which eight neighbouring lanes take the 32 results of one vector, 128 bytes.
-            int ve[NB];
+            if (contracted) {
+                int ve[NB];
 #pragma unroll
-            for (int cb = 0; cb < NB; ++cb) ve[cb] = vector_exp[vw * 32 * NB + cb * 32 + lr];
-            char *const block = lds_h + wave * (32 * kResultRow);
+                for (int cb = 0; cb < NB; ++cb) ve[cb] = vector_exp[vw * 32 * NB + cb * 32 + lr];
+                char *const block = lds_h + wave * (32 * kResultRow);
 #pragma unroll
-            for (int rb = 0; rb < NB; ++rb) {
-                const uint32_t j0 = ft * TF + fw * 32 * NB + rb * 32;
-                const uint32_t j = j0 + 4 * (lane & 7);  // of the results this lane stores
-                intx4 fe[4];
-                floatx4 b4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    fe[q] = *reinterpret_cast<const intx4 *>(a.fexp + j0 + 8 * q + 4 * lh);  // below kpad
-                    if constexpr (!PROJ) {
-                        b4[q] = *reinterpret_cast<const floatx4 *>(a.off + j0 + 8 * q + 4 * lh);
-                        if constexpr (POW2) b4[q] *= a.inv_w;
-                    }
-                }
-#pragma unroll
-                for (int cb = 0; cb < NB; ++cb) {
+                for (int rb = 0; rb < NB; ++rb) {
+                    const uint32_t j0 = ft * TF + fw * 32 * NB + rb * 32;
+                    const uint32_t j = j0 + 4 * (lane & 7);  // of the results this lane stores
+                    intx4 fe[4];
+                    floatx4 b4[4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        uintx4 v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float p = __builtin_ldexpf(acc[rb][cb][4 * q + e], -(fe[q][e] + ve[cb]));
-                            if constexpr (PROJ) {
-                                v[e] = __float_as_uint(p);
-                            } else {
-                                const float h = POW2 ? fmaf(p, a.inv_w, b4[q][e]) : (p + b4[q][e]) / a.w;
-                                v[e] = (uint32_t)(int)floorf(h);
-                            }
+                        fe[q] = *reinterpret_cast<const intx4 *>(a.fexp + j0 + 8 * q + 4 * lh);  // below kpad
+                        if constexpr (!PROJ) {
+                            b4[q] = *reinterpret_cast<const floatx4 *>(a.off + j0 + 8 * q + 4 * lh);
+                            if constexpr (POW2) b4[q] *= a.inv_w;
                         }
-                        *reinterpret_cast<uintx4 *>(block + lr * kResultRow + q * 32 + lh * 16) = v;
                     }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-                    const uint64_t vec0 = vt * TVW + vw * 32 * NB + cb * 32;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t r = q * 8 + (lane >> 3);
-                        const uintx4 v = *reinterpret_cast<const uintx4 *>(block + r * kResultRow + (lane & 7) * 16);
-                        if (vec0 + r < a.N) {
-                            uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + (vec0 + r) * a.k + j;
-                            if constexpr (VEC) {
-                                if (j < a.k) {
-                                    if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<uintx4 *>(dst));
-                                    else *reinterpret_cast<uintx4 *>(dst) = v;
+                    for (int cb = 0; cb < NB; ++cb) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            uintx4 v;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float p = __builtin_ldexpf(acc[rb][cb][4 * q + e], -(fe[q][e] + ve[cb]));
+                                if constexpr (PROJ) {
+                                    v[e] = __float_as_uint(p);
+                                } else {
+                                    const float h = POW2 ? fmaf(p, a.inv_w, b4[q][e]) : (p + b4[q][e]) / a.w;
+                                    v[e] = (uint32_t)(int)floorf(h);
                                 }
-                            } else {
+                            }
+                            *reinterpret_cast<uintx4 *>(block + lr * kResultRow + q * 32 + lh * 16) = v;
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+                        const uint64_t vec0 = vt * TVW + vw * 32 * NB + cb * 32;
 #pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (j + e < a.k) dst[e] = v[e];
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t r = q * 8 + (lane >> 3);
+                            const uintx4 v = *reinterpret_cast<const uintx4 *>(block + r * kResultRow + (lane & 7) * 16);
+                            if (vec0 + r < a.N) {
+                                uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + (vec0 + r) * a.k + j;
+                                if constexpr (VEC) {
+                                    if (j < a.k) {
+                                        if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<uintx4 *>(dst));
+                                        else *reinterpret_cast<uintx4 *>(dst) = v;
+                                    }
+                                } else {
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e)
+                                        if (j + e < a.k) dst[e] = v[e];
+                                }
                             }
                         }
+                        __builtin_amdgcn_wave_barrier();
                     }
-                    __builtin_amdgcn_wave_barrier();
                 }
             }
             lds_barrier();  // the exponents and the results have been read
-        }
-    }
-}
-
-// The same product for few vectors, where tiles of 256 x 256 leave most of the chip idle and each of them
-// still walks all stages.  A wave takes 32 functions x 32 vectors with its operands straight from memory, the
-// planes in the order they are stored in and the vectors split in registers: no LDS, no barrier, the
-// loads of kFewSets stages on their way.  Scales, products and their order are those of the kernel above,
-// and so are the results, bit for bit.  Bound by the chain of a stage (three dependent MFMAs, the split) and by 4 KB
-// of loads for every 3 MFMAs, which is why it loses where there are tiles enough.  Tiles / this kernel, by the
-// number of its waves: 8 x 960 x 1024 (32) 60.5 / 14.2 us; 100 x 16000 x 250 (32) 805 / 275; 1000 x 4096 x 512 (512)
-// 211 / 74; 1000 x 960 x 1024 (1024) 64.5 / 21.7; 1e4 x 300 x 250 (2504) 39.0 / 23.5; 4000 x 960 x 1024 (4000) 66 / 79; 8000 x
-// 4096 x 512 (4000) 214 / 291; 3e4 x 132 x 256 (7504) 28.6 / 33.7.  The line is three waves for every SIMD.
-constexpr int kFewSets = 4;
-constexpr uint64_t kFewWaves = 3072;
-
-template <bool PROJ, bool POW2, bool VEC>
-__global__ __launch_bounds__(256) void dense_half_few_kernel(const HalfArgs a) {
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lr = lane & 31, lh = lane >> 5;
-    const uint32_t j0 = (blockIdx.x * 4 + wave) * 32;  // the wave's functions
-    if (j0 >= a.k) return;
-    const uint32_t stages = a.npad / KB;
-    const uint16_t *arow = a.planes + (size_t)(j0 / TF) * stages * kStagePlanes + (j0 % TF + lr) * KB + lh * 8;
-    const uint64_t vec = (uint64_t)blockIdx.y * 32 + lr;
-    const float *vrow = a.data + (vec < a.N ? vec : a.N - 1) * a.n + lh * 8;
-    // as in the kernel above: coordinates beyond n read the vector's first ones, stages beyond the last the last one
-    auto load_v = [&](uint32_t s, floatx4 (&v)[2]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            v[h] = *reinterpret_cast<const floatx4 *>(vrow + h * 4 + (s * KB + lh * 8 + h * 4 < a.n ? s * KB : 0u));
-    };
-    auto load_a = [&](uint32_t s, halfx8 (&c)[2]) __attribute__((always_inline)) {
-        const uint32_t ka = s < stages ? s : stages - 1;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) c[p] = *reinterpret_cast<const halfx8 *>(arow + (size_t)ka * kStagePlanes + p * (TF * KB));
-    };
-    floatx4 v[kFewSets][2];
-    halfx8 c[kFewSets][2];
-    float largest = 0.f;
-    {
-        floatx4 looked[5][2];
-        const uint32_t at[5] = {0, 1, 2, stages / 3, stages * 2 / 3};
-#pragma unroll
-        for (int t = 0; t < 5; ++t) load_v(at[t], looked[t]);
-#pragma unroll
-        for (int t = 0; t < 5; ++t) largest = largest_of(looked[t][1], largest_of(looked[t][0], largest));
-        largest = fmaxf(largest, __shfl_xor(largest, 32));  // the two lanes of a vector
-        if (largest == 0.f) {
-            for (uint32_t s = 3; s < stages; s += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    floatx4 w[2];
-                    load_v(s + u, w);
-                    largest = largest_of(w[1], largest_of(w[0], largest));
-                }
-            }
-        }
-        largest = fmaxf(largest, __shfl_xor(largest, 32));
-    }
-    int vexp = scale_exponent(largest, kVectorTop);
-    floatx16 acc;
-    for (uint32_t attempt = 0;; ++attempt) {
-        const float scale = power_of_two(vexp);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-        for (int d = 0; d < kFewSets; ++d) {
-            load_v(d, v[d]);
-            load_a(d, c[d]);
-        }
-        for (uint32_t s0 = 0; s0 < stages; s0 += kFewSets) {
-#pragma unroll
-            for (int d = 0; d < kFewSets; ++d) {
-                if (s0 + d < stages) {
-                    halfx8 v1, v2;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        halfx2 hi, lo;
-                        split2(v[d][e / 2][e % 2 * 2], v[d][e / 2][e % 2 * 2 + 1], scale, hi, lo);
-                        v1[2 * e] = hi[0], v1[2 * e + 1] = hi[1];
-                        v2[2 * e] = lo[0], v2[2 * e + 1] = lo[1];
+            if (++tiles < kSegment && vt + vt_step < Vt) continue;
+            const uint32_t odd = __builtin_amdgcn_readfirstlane(*odd_count), few = __builtin_amdgcn_readfirstlane(*few_count);
+            if (odd + few) {
+                __syncthreads();  // what the waves stored for odd vectors is where it belongs, and gets stored over
+                uint32_t thread = threadIdx.x;
+                asm volatile("" : "+v"(thread));  // as above
+                const wide::Args x = a.exact();
+                const Listed listed{odd_list, vt - (tiles - 1) * vt_step, vt_step, odd - 1};
+                auto blocks = [&](uint32_t first, uint32_t count, auto run) {  // 32 functions x 32 vectors a wave
+                    for (uint32_t b = thread >> 6; b < (count + 31) / 32 * 8; b += 4) {
+                        const uint32_t j0 = __builtin_amdgcn_readfirstlane(ft * TF + (b & 7) * 32), at = (b >> 3) * 32 + (thread & 31);
+                        if (j0 < a.k) run(j0, listed.wanted(first + (at < count ? at : count - 1)), at < count);
                     }
-                    largest = largest_of(v[d][1], largest_of(v[d][0], largest));
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v2, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][0], v1, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[d][1], v1, acc, 0, 0, 0);
+                };
+                blocks(kSegment * TVW - few, few, [&](uint32_t j0, uint64_t row, bool store) { few_block<PROJ, POW2, VEC>(a, thread, j0, row, store); });
+                if (odd <= kFewOdd) {
+                    blocks(0, odd, [&](uint32_t j0, uint64_t row, bool store) { wide::block<PROJ, POW2, VEC>(x, thread, j0, row, store); });
+                } else {
+                    for (Listed rows = listed; rows.first < odd; rows.first += TVW)
+                        wide::tile<PROJ, POW2, VEC>(x, lds_h, thread, ft, rows, odd - rows.first);
                 }
-                load_v(s0 + d + kFewSets, v[d]);
-                load_a(s0 + d + kFewSets, c[d]);
+                __syncthreads();
+                if (threadIdx.x == 0) *odd_count = 0, *few_count = 0;
+                lds_barrier();
             }
-        }
-        largest = fmaxf(largest, __shfl_xor(largest, 32));
-        const bool left_half = largest * scale > kLargestHalf;
-        if (attempt > 0 || !__any(left_half)) break;
-        if (left_half) vexp = scale_exponent(largest, kVectorTop);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t j = j0 + 8 * q + 4 * lh;  // < kpad
-        const intx4 fe = *reinterpret_cast<const intx4 *>(a.fexp + j);
-        floatx4 b4 = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (!PROJ) {
-            b4 = *reinterpret_cast<const floatx4 *>(a.off + j);
-            if constexpr (POW2) b4 *= a.inv_w;
-        }
-        uintx4 r;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float p = __builtin_ldexpf(acc[4 * q + e], -(fe[e] + vexp));
-            if constexpr (PROJ) {
-                r[e] = __float_as_uint(p);
-            } else {
-                const float h = POW2 ? fmaf(p, a.inv_w, b4[e]) : (p + b4[e]) / a.w;
-                r[e] = (uint32_t)(int)floorf(h);
-            }
-        }
-        if (vec < a.N) {
-            uint32_t *dst = reinterpret_cast<uint32_t *>(a.out) + vec * a.k + j;
-            if constexpr (VEC) {
-                if (j < a.k) *reinterpret_cast<uintx4 *>(dst) = r;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (j + e < a.k) dst[e] = r[e];
-            }
+            tiles = 0;
         }
     }
 }
@@ -633,7 +754,8 @@ void build_half_planes(const float *a, uint32_t k, uint32_t n, uint32_t kpad, ui
 int launch_dense_half(const lsh_params *p, bool proj, const float *d_data, uint64_t N, void *d_out, void *stream) {
     HalfArgs a;
     a.data = d_data;
-    a.planes = static_cast<const uint16_t *>(p->d_dense_planes);
+    a.planes = static_cast<const uint16_t *>(p->d_half_planes);
+    a.exact_planes = static_cast<const uint16_t *>(p->d_dense_planes);
     a.off = p->d_off;
     a.N = N;
     a.n = p->n;

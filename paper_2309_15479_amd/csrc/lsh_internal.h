@@ -105,7 +105,8 @@ struct lsh_params {
     float *d_off = nullptr;            // [kpad]
     float *d_dense = nullptr;          // [kpad_dense][n]: row j = a_j written out over all n coordinates; m == n or n == 128, else null
     uint32_t kpad_dense = 0;
-    void *d_dense_planes = nullptr;    // m == n, n != 128: the same matrix as three bf16 planes, [kpad / 256][npad / 16][3][256][16], or two fp16 planes (dense_half_used)
+    void *d_dense_planes = nullptr;    // m == n, n != 128: the same matrix as three bf16 planes, [kpad / 256][npad / 16][3][256][16]
+    void *d_half_planes = nullptr;     // and as two fp16 planes where dense_half_used, see build_half_planes
     int dense_arithmetic = LSH_DENSE_AUTO;  // see lsh_params_set_dense_arithmetic
     // one sample per table: operand tables of the shared-sample kernel (null when unsupported)
     lsh::SharedPlan shared_plan;
@@ -199,8 +200,8 @@ uint32_t dense_wide_col_step();
 void build_dense_planes(const float *a, uint32_t k, uint32_t n, uint32_t kpad, uint32_t npad,
                         std::vector<uint16_t> &planes);
 int launch_dense_wide(const lsh_params *p, bool proj, const float *d_data, uint64_t N, void *d_out, void *stream);
-// the same product from two-way fp16 splits (dense_half_kernel.hip), for objects with sums long enough:
-// d_dense_planes then holds the planes that build_half_planes makes, on the same tiles
+// the same product from two-way fp16 splits where the vectors allow it (dense_half_kernel.hip), for objects with
+// sums long enough: they hold d_half_planes beside d_dense_planes
 bool dense_half_used(const lsh_params *p);
 void build_half_planes(const float *a, uint32_t k, uint32_t n, uint32_t kpad, uint32_t npad,
                        std::vector<uint16_t> &planes);

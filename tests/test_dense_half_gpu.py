@@ -121,3 +121,59 @@ def test_unsampled_coordinates_have_no_influence(lsh, n, k, m, again, large):
         want, size = spoilt.double() @ a.T, spoilt.double().abs() @ a.abs().T
         worst = ((lsh.project_fastlsh(p, spoilt).double() - want).abs() / size).max().item()
         assert worst < 1e-5, worst
+
+
+def _odd(kind, N, n):
+    """Vectors that few of their coordinates carry."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N * 17 + n)
+    x = torch.randn((N, n), generator=g, device="cuda")
+    at = torch.randint(0, n, (N, 1), generator=g, device="cuda")
+    if kind == "one":
+        return torch.zeros_like(x).scatter_(1, at, torch.exp2(torch.round(3 * x[:, :1])))
+    if kind == "sparse":
+        return x * (torch.rand((N, n), generator=g, device="cuda") < 5.0 / n)
+    if kind == "small beside one":
+        return x.scatter_(1, at, 1e10)
+    if kind == "powers":       # every coordinate of another size
+        return x * torch.exp(40.0 * torch.randn((N, n), generator=g, device="cuda")).clamp(1e-34, 1e30)
+    if kind == "least":        # no scale takes these to the usual size
+        return x * 2e-38
+    if kind == "column":       # one column of another unit, not looked at for a scale; some vectors without it
+        x[torch.arange(N, device="cuda") % 50 != 7, n // 2 + 5] *= 1e7
+        return x
+    if kind == "nearly all":
+        x[torch.arange(N, device="cuda") % 23 != 5] = _odd("one", N, n)[torch.arange(N, device="cuda") % 23 != 5]
+        return x
+    assert kind == "mixed"
+    x[::3] = _odd("one", N, n)[::3]
+    x[1::37] = _odd("small beside one", N, n)[1::37]
+    x[2::41] = 0.0
+    return x
+
+
+@pytest.mark.parametrize("kind", ["one", "sparse", "small beside one", "powers", "least", "column", "nearly all", "mixed"])
+@pytest.mark.parametrize("N,n,k,w", [(20000, 960, 1024, 4.0), (3000, 4096, 2048, 3.0), (700, 260, 250, 3.0), (150001, 260, 250, 4.0)])
+def test_vectors_of_few_coordinates(lsh, kind, N, n, k, w):
+    """A function may give such a vector's largest coordinates small coefficients: all that the splits lose must stay
+    below 1e-5 of that small sum of |a_i v_i| too, for every function and vector.  (Without products of their own
+    they are off by up to 2e-5 of it here.)  The same numbers in a launch of few vectors and of many, and beside
+    other vectors; of a single coordinate, a power of two here, the product itself."""
+    data = _odd(kind, N, n)
+    print(f"dense fp16 product, vectors of few coordinates: {kind} N={N} n={n} k={k}", flush=True)
+    with lsh.LshParams(n, k, n, w, 19) as p:
+        got, ids = lsh.project_e2lsh(p, data), lsh.hash_e2lsh(p, data)
+        for i in range(0, N, 4000):
+            want, size = _exact(p, data[i:i + 4000])
+            worst = ((got[i:i + 4000].double() - want).abs() / size.clamp(min=1e-300)).max().item()
+            assert worst < 1e-5, worst
+            if kind == "one":
+                assert torch.equal(got[i:i + 4000], want.float())
+            off = torch.tensor(p.offsets(), device="cuda").double()
+            edge = ((want + off) / w) - ((want + off) / w).round()
+            clear = (edge.abs() > 1e-4 + 1e-5 * size / w) & (want.abs() / w < 2e9)
+            assert torch.equal(ids[i:i + 4000][clear], torch.floor((want + off) / w)[clear].int())
+        for first, count in ((0, 1), (31, 33), (N - 257, 257), (5, 64)):
+            part = data[first:first + count].clone()
+            assert torch.equal(lsh.project_e2lsh(p, part), got[first:first + count])
+            assert torch.equal(lsh.hash_e2lsh(p, part), ids[first:first + count])
