@@ -9,7 +9,11 @@
 // accumulation rounds half as often as over the six bf16 products of dense_split_wide_kernel.hip,
 // where every product is added to the same accumulators.  Both together, modelled with one rounding a
 // product of 16 terms, fp16 / bf16: 8.5e-8 / 6.3e-8 at 30 terms, 1.07e-7 / 1.18e-7 at 128, 1.9e-7 /
-// 2.5e-7 at 512, 2.5e-7 / 3.5e-7 at 960; kHalfMinTerms is where the fp16 product is the more accurate one.
+// 2.5e-7 at 512, 2.5e-7 / 3.5e-7 at 960.  Measured, fp16 / bf16: normal coordinates 1.53e-7 / 1.74e-7 at 132 terms, 1.93 /
+// 2.40 at 256, 3.5 / 4.7 at 960; whole numbers below 256, of which two of the bf16 terms are zero, 1.14 / 1.13 at 132, 1.211 /
+// 1.208 at 160, 1.263 / 1.270 at 176, 2.8 / 3.0 at 960.  kHalfMinTerms is where the fp16 product is the more accurate
+// one, but for those whole numbers, where they are even up to 170 terms (1 % apart at most).  Below 1e-36, where bf16 terms
+// are lost, it is the only one that keeps to 1e-5 of sum |a_i v_i|.
 //
 // Scales.  e is a function's (on the host, from its largest coefficient: [2^14, 2^15) after scaling)
 // or a vector's.  A vector's comes from 80 of its coordinates, the three stages that start the
