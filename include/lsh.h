@@ -205,7 +205,8 @@ int lsh_hash_e2lsh(const lsh_params_t *params, const float *d_data, uint64_t N,
  * two-way fp16 splits (23 bits), every vector and function scaled by a power of two of its own first,
  * for vectors that many coordinates carry, and by the six products for the others: vectors
  * of fewer than eight coordinates (of 80 looked at) within 1/128 of the largest, or with one some hundred times
- * as large as those.  An fp16 split is off by less than 2^-22 of each term |a_i v_i|; the sum is rounded half
+ * as large as those.  An fp16 split is off by less than 2^-21 of each term |a_i v_i|
+ * (2^-23 for either operand, 2^-22 for the product of the low terms, which is left out); the sum is rounded half
  * as often and is the closer one to the exact value from 128 terms on.  Either way projections stay within
  * 1e-5 * sum_i |a_i v_i|, and which way a vector goes depends on the vector alone.  A vector with an infinite or
  * NaN coordinate has no defined result, as before.  Any other shape uses fp32 MFMA.

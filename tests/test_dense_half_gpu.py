@@ -44,10 +44,10 @@ def _data(kind, N, n):
 @pytest.mark.parametrize("kind", ["normal", "late", "rise", "fall", "rows", "tiny", "huge"])
 @pytest.mark.parametrize("N,n,k", [(1, 132, 64), (257, 148, 250), (300, 960, 260), (255, 1028, 512)])
 def test_projections(lsh, kind, N, n, k):
-    """Off by at most 2^-22 of sum |a_i v_i| by the split (2^-23 of each operand, rounded pairwise, and the low
-    products left out) and n / 8 * 3 roundings of 2^-24 (the accumulation, one for eight terms and product, all of
-    them at the largest partial sum): 2e-5 at n = 960 in the worst case, a hundredth of that as seen.  The bound
-    here is the repository's 1e-5, and 2e-6 for the distributions that an fp32 sum keeps to that."""
+    """Off by at most 2^-21 of sum |a_i v_i| by the split (2^-23 for each operand, and 2^-22 for the product of the
+    low terms, which is left out) and n / 16 * 3 roundings of 2^-24 (the accumulation, one for sixteen terms and
+    product, all of them at the largest partial sum): 1.1e-5 at n = 960 in the worst case, a thirtieth of that as seen.
+    The bound here is 2e-6, which an fp32 sum of these distributions keeps to."""
     data = _data(kind, N, n)
     print(f"dense fp16 product: {kind} N={N} n={n} k={k}", flush=True)
     with lsh.LshParams(n, k, n, 4.0, 11) as p:
@@ -177,3 +177,35 @@ def test_vectors_of_few_coordinates(lsh, kind, N, n, k, w):
             part = data[first:first + count].clone()
             assert torch.equal(lsh.project_e2lsh(p, part), got[first:first + count])
             assert torch.equal(lsh.hash_e2lsh(p, part), ids[first:first + count])
+
+
+def test_bound_of_a_split(lsh):
+    """Vectors made for one function each: the eight looked-at coordinates at which the split of the function's
+    coefficient and of 1 + 2^-11 - 2^-21 + 2^-23 loses most, with the signs that add the losses up.  More than 2^-22 of the
+    sum is lost, and no more than 2^-21 and the roundings of the accumulation (24 products of eight equal terms at
+    most, each off by 2^-24 of the sum)."""
+    import numpy as np
+    n, k = 960, 512
+    looked = np.concatenate([np.arange(48), np.arange(320, 336), np.arange(640, 656)])
+    with lsh.LshParams(n, k, n, 4.0, 23) as p:
+        a = p.coeffs().reshape(k, n).astype(np.float64)
+        v = 1 + 2.0 ** -11 - 2.0 ** -21 + 2.0 ** -23
+        assert np.float32(v) == v
+        scaled = a * 2.0 ** (14 - np.floor(np.log2(np.abs(a).max(1, keepdims=True))))
+
+        def terms(x):
+            high = x.astype(np.float16).astype(np.float64)
+            return high, (x - high).astype(np.float16).astype(np.float64)
+
+        (a1, a2), (v1, v2) = terms(scaled), terms(np.float64(v * 32))
+        loss = (a1 * v1 + a1 * v2 + a2 * v1 - scaled * v * 32) / np.abs(scaled * v * 32)
+        data = np.zeros((k, n), dtype=np.float32)
+        for j in range(k):
+            at = looked[np.argsort(-np.abs(loss[j, looked]))[:8]]
+            data[j, at] = v * np.sign(loss[j, at])  # the term is off by loss * |term|: signs that make all losses positive
+        print("dense fp16 product: largest losses of a split", flush=True)
+        got = lsh.project_e2lsh(p, torch.tensor(data, device="cuda")).cpu().numpy().astype(np.float64)
+    exact = (data.astype(np.float64) * a).sum(1)
+    off = (np.diagonal(got) - exact) / (np.abs(data) * np.abs(a)).sum(1)
+    assert off.max() > 2.0 ** -22, off.max()
+    assert np.abs(off).max() < 2.0 ** -21 + 24 * 2.0 ** -24, np.abs(off).max()
