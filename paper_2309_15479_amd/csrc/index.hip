@@ -717,7 +717,7 @@ void lsh_index_destroy(lsh_index_t *ix) {
     const bool switched = ix->device >= 0 && hipGetDevice(&prev) == hipSuccess && prev != ix->device &&
                           hipSetDevice(ix->device) == hipSuccess;
     // work on any stream may still read the tables: wait for the device, as hipFree does
-    if (hipDeviceSynchronize() == hipSuccess) lsh::index_memory_give(ix->device, ix->tables);
+    if (lsh::index_memory_wait()) lsh::index_memory_give(ix->device, ix->tables);
     else (void)hipFree(ix->tables.ptr);
     lsh::index_memory_leave(ix->device);
     if (switched) (void)hipSetDevice(prev);

@@ -147,6 +147,15 @@ void index_memory_give_scratch(int device, const IndexBlock &block, hipStream_t 
     m.idle_bytes += block.bytes;
 }
 
+bool index_memory_wait() {
+    // hipFree waits for all work on the device and may be called while a stream captures in relaxed mode, or in
+    // another thread; hipDeviceSynchronize would invalidate the capture
+    void *token = nullptr;
+    const bool ok = hipMalloc(&token, 4) == hipSuccess && hipFree(token) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
 void index_memory_give(int device, const IndexBlock &block) {
     if (!block.ptr) return;
     std::vector<Idle> over;

@@ -28,6 +28,8 @@ void index_memory_leave(int device);
 bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t stream, IndexBlock &out);
 // work on `stream` enqueued so far may still use the block; does not wait
 void index_memory_give_scratch(int device, const IndexBlock &block, hipStream_t stream);
+// waits until all work enqueued on the current device is done; false: it could not be waited for
+bool index_memory_wait();
 // nothing on the device uses the block any more
 void index_memory_give(int device, const IndexBlock &block);
 

@@ -112,6 +112,61 @@ except RuntimeError:
 """
 
 
+def test_destroying_an_index_waits_for_work_on_any_stream(lsh):
+    """Another stream may still read the tables: their memory is used again only after that."""
+    keys = _random_keys(20000, 3, 5000, 9)
+    indexes = [lsh.LshIndex(keys), lsh.LshIndex(keys)]
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    big = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(100):
+            big = big @ big * 1e-2
+        done.record()
+    assert not done.query()
+    indexes.pop().close()
+    assert done.query()
+    indexes.pop().close()
+
+
+_DESTROY_IN_CAPTURE = """
+import threading
+import torch
+import paper_2309_15479_amd as lsh
+keys = torch.randint(0, 5000, (20000, 3), device="cuda")
+indexes = [lsh.LshIndex(keys) for _ in range(3)]
+data = torch.randn((1000, 128), device="cuda")
+out = torch.empty((1000, 64), dtype=torch.int32, device="cuda")
+with lsh.LshParams(128, 64, 32, 4.0, 1) as p:
+    want = lsh.hash_fastlsh(p, data, out=out).clone()
+    torch.cuda.synchronize()
+    for mode in ("relaxed", "thread_local"):
+        ix = indexes.pop()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode=mode):
+            lsh.hash_fastlsh(p, data, out=out)
+            if mode == "relaxed":
+                ix.close()
+            else:
+                other = threading.Thread(target=ix.close)
+                other.start()
+                other.join()
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+        print(mode, "captured", flush=True)
+"""
+
+
+def test_destroying_an_index_leaves_a_capture_alone(lsh):
+    """As freeing memory does: in the capturing thread in relaxed mode, in another one in the others."""
+    r = subprocess.run([sys.executable, "-c", _DESTROY_IN_CAPTURE], capture_output=True, text=True, timeout=100,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert "relaxed captured" in r.stdout and "thread_local captured" in r.stdout, r.stdout + r.stderr
+
+
 def test_build_is_refused_under_capture(lsh):
     """Memory that earlier builds left must not make a capture take what it may not hold (in a process
     of its own: the refused call invalidates the capture and what the stream does after it)."""
