@@ -2,9 +2,7 @@
 #include "index_memory.h"
 
 #include <cstdint>
-#include <map>
 #include <mutex>
-#include <vector>
 
 namespace lsh {
 namespace {
@@ -14,53 +12,86 @@ struct Idle {
     hipEvent_t last_use;  // null: nothing uses the block
 };
 
+// Fixed arrays: nothing here may throw (the callers are C entries), or be destroyed while an index that a program
+// holds to its end still needs it.
+constexpr int kDevices = 64;     // on others nothing is kept
+constexpr uint32_t kIdle = 256;  // blocks kept at most
+
 struct DeviceMemory {
     uint64_t live = 0;
     size_t idle_bytes = 0;
     size_t scratch_bytes = 0;  // scratch in use: it comes back to the idle blocks
-    std::vector<Idle> idle;  // oldest first
+    uint32_t idle_count = 0;
+    Idle idle[kIdle] = {};  // oldest first
+
+    Idle remove(uint32_t i) {
+        const Idle out = idle[i];
+        for (--idle_count; i < idle_count; ++i) idle[i] = idle[i + 1];
+        idle_bytes -= out.block.bytes;
+        return out;
+    }
+    // returns the oldest block if there is no room for one more
+    Idle add(const Idle &i) {
+        const Idle out = idle_count == kIdle ? remove(0) : Idle{};
+        idle[idle_count++] = i;
+        idle_bytes += i.block.bytes;
+        return out;
+    }
 };
 
 std::mutex mu;
-std::map<int, DeviceMemory> memory;
+DeviceMemory memory[kDevices];
+
+DeviceMemory *kept(int device) { return device >= 0 && device < kDevices ? &memory[device] : nullptr; }
 
 void release(const Idle &i) {
+    if (!i.block.ptr) return;
     (void)hipFree(i.block.ptr);  // waits for the device
     if (i.last_use) (void)hipEventDestroy(i.last_use);
 }
 
-void forget_scratch(int device, bool scratch, size_t bytes) {
-    if (!scratch) return;
-    std::lock_guard<std::mutex> lock(mu);
-    memory[device].scratch_bytes -= bytes;
+// idle blocks, oldest first, until the rest satisfies `enough`
+template <typename Enough>
+void release_until(DeviceMemory &m, Enough enough) {
+    for (;;) {
+        Idle i;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            if (!m.idle_count || enough()) return;
+            i = m.remove(0);
+        }
+        release(i);
+    }
 }
 
-std::vector<Idle> take_all(DeviceMemory &m) {
-    std::vector<Idle> all;
-    all.swap(m.idle);
-    m.idle_bytes = 0;
-    return all;
+void forget_scratch(DeviceMemory *m, bool scratch, size_t bytes) {
+    if (!m || !scratch) return;
+    std::lock_guard<std::mutex> lock(mu);
+    m->scratch_bytes -= bytes;
 }
 
 }  // namespace
 
 void index_memory_enter(int device) {
+    DeviceMemory *m = kept(device);
+    if (!m) return;
     std::lock_guard<std::mutex> lock(mu);
-    ++memory[device].live;
+    ++m->live;
 }
 
 void index_memory_leave(int device) {
-    std::vector<Idle> all;
+    DeviceMemory *m = kept(device);
+    if (!m) return;
     {
         std::lock_guard<std::mutex> lock(mu);
-        DeviceMemory &m = memory[device];
-        if (--m.live == 0) all = take_all(m);
+        --m->live;
     }
-    for (const Idle &i : all) release(i);
+    release_until(*m, [&] { return m->live != 0; });
 }
 
 bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t stream, IndexBlock &out) {
     bytes = (bytes + 65535) / 65536 * 65536;
+    DeviceMemory *const m = kept(device);
     Idle found = {};
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
@@ -73,25 +104,24 @@ bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t strea
         out = IndexBlock();
         return false;
     }
-    {
+    if (m) {
         std::lock_guard<std::mutex> lock(mu);
-        DeviceMemory &m = memory[device];
-        size_t best = m.idle.size();
-        for (size_t i = 0; i < m.idle.size(); ++i) {
-            const size_t have = m.idle[i].block.bytes;
+        uint32_t best = kIdle;
+        for (uint32_t i = 0; i < m->idle_count; ++i) {
+            const size_t have = m->idle[i].block.bytes;
             if (have < bytes || have / 2 > bytes) continue;  // not more than twice what is asked for
-            if (best == m.idle.size() || have < m.idle[best].block.bytes) best = i;
+            if (best == kIdle || have < m->idle[best].block.bytes) best = i;
         }
-        if (best != m.idle.size()) {
-            found = m.idle[best];
-            m.idle.erase(m.idle.begin() + best);
-            m.idle_bytes -= found.block.bytes;
-            if (scratch) m.scratch_bytes += found.block.bytes;
-        } else if (scratch && m.idle_bytes + m.scratch_bytes + bytes > kIdleLimit) {
+        if (best != kIdle) {
+            found = m->remove(best);
+            if (scratch) m->scratch_bytes += found.block.bytes;
+        } else if (scratch && m->idle_bytes + m->scratch_bytes + bytes > kIdleLimit) {
             out.stream_ordered = true;
         } else if (scratch) {
-            m.scratch_bytes += bytes;
+            m->scratch_bytes += bytes;
         }
+    } else {
+        out.stream_ordered = scratch;
     }
     if (found.block.ptr) {
         if (found.last_use) {  // the work that used it last, on whatever stream, comes first
@@ -100,7 +130,7 @@ bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t strea
             (void)hipEventDestroy(found.last_use);
             if (!ok) {
                 (void)hipFree(found.block.ptr);
-                forget_scratch(device, scratch, found.block.bytes);
+                forget_scratch(m, scratch, found.block.bytes);
                 return false;
             }
         }
@@ -113,15 +143,10 @@ bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t strea
     };
     if (allocate()) return true;
     (void)hipGetLastError();
-    std::vector<Idle> all;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        all = take_all(memory[device]);
-    }
-    for (const Idle &i : all) release(i);
+    if (m) release_until(*m, [] { return false; });
     if (allocate()) return true;
     (void)hipGetLastError();
-    forget_scratch(device, scratch && !out.stream_ordered, bytes);
+    forget_scratch(m, scratch && !out.stream_ordered, bytes);
     out = IndexBlock();
     return false;
 }
@@ -132,19 +157,22 @@ void index_memory_give_scratch(int device, const IndexBlock &block, hipStream_t 
         (void)hipFreeAsync(block.ptr, stream);
         return;
     }
+    DeviceMemory *const m = kept(device);  // not null: scratch of other devices is stream-ordered
     hipEvent_t ev = nullptr;
     if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess || hipEventRecord(ev, stream) != hipSuccess) {
         if (ev) (void)hipEventDestroy(ev);
         (void)hipGetLastError();
         (void)hipFree(block.ptr);  // waits for the device
-        forget_scratch(device, true, block.bytes);
+        forget_scratch(m, true, block.bytes);
         return;
     }
-    std::lock_guard<std::mutex> lock(mu);
-    DeviceMemory &m = memory[device];
-    m.scratch_bytes -= block.bytes;
-    m.idle.push_back({block, ev});
-    m.idle_bytes += block.bytes;
+    Idle out;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        m->scratch_bytes -= block.bytes;
+        out = m->add({block, ev});
+    }
+    release(out);
 }
 
 bool index_memory_wait() {
@@ -158,19 +186,18 @@ bool index_memory_wait() {
 
 void index_memory_give(int device, const IndexBlock &block) {
     if (!block.ptr) return;
-    std::vector<Idle> over;
+    DeviceMemory *const m = kept(device);
+    if (!m) {
+        (void)hipFree(block.ptr);
+        return;
+    }
+    Idle out;
     {
         std::lock_guard<std::mutex> lock(mu);
-        DeviceMemory &m = memory[device];
-        m.idle.push_back({block, nullptr});
-        m.idle_bytes += block.bytes;
-        while (!m.idle.empty() && m.idle_bytes + m.scratch_bytes > kIdleLimit) {
-            over.push_back(m.idle.front());
-            m.idle_bytes -= m.idle.front().block.bytes;
-            m.idle.erase(m.idle.begin());
-        }
+        out = m->add({block, nullptr});
     }
-    for (const Idle &i : over) release(i);
+    release(out);
+    release_until(*m, [&] { return m->idle_bytes + m->scratch_bytes <= kIdleLimit; });
 }
 
 }  // namespace lsh
