@@ -295,7 +295,8 @@ int lsh_time_launches(const lsh_params_t *params, int which, const void *d_in, u
  * LSH index (Sec. 3.2): L hash tables of <key, id> pairs and the lookup of a query's L buckets.
  * A table is the vector ids sorted by key (stable: ids ascending inside a bucket), a bucket a
  * contiguous run of them found by binary search; 12 bytes per vector and table of device
- * memory, owned by the index object.
+ * memory (up to an eighth more, and 64 KB, where memory of an earlier index is used again), owned by the
+ * index object.
  *
  * lsh_index_build: d_keys [N][L] (device, as written by lsh_pack_keys or
  *   lsh_hash_fastlsh_keys), N < 2^31, L <= 65535.  Sorts all L columns together on `stream`

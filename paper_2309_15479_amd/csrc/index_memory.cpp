@@ -109,7 +109,8 @@ bool index_memory_take(int device, size_t bytes, bool scratch, hipStream_t strea
         uint32_t best = kIdle;
         for (uint32_t i = 0; i < m->idle_count; ++i) {
             const size_t have = m->idle[i].block.bytes;
-            if (have < bytes || have / 2 > bytes) continue;  // not more than twice what is asked for
+            // scratch, back after the build, takes up to twice what is asked for; tables stay as long as their index
+            if (have < bytes || have - bytes > (scratch ? bytes : bytes / 8)) continue;
             if (best == kIdle || have < m->idle[best].block.bytes) best = i;
         }
         if (best != kIdle) {
