@@ -188,7 +188,7 @@ bool index_memory_wait() {
 void index_memory_give(int device, const IndexBlock &block) {
     if (!block.ptr) return;
     DeviceMemory *const m = kept(device);
-    if (!m) {
+    if (!m || block.bytes > kIdleLimit) {
         (void)hipFree(block.ptr);
         return;
     }

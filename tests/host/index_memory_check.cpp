@@ -96,10 +96,29 @@ static void slack() {
     CHECK(stub.bytes == 0 && stub.events == 0);
 }
 
+// beyond the limit the oldest blocks go; a block that alone exceeds it goes by itself
+static void limit() {
+    index_memory_enter(0);
+    IndexBlock b[4];
+    for (int i = 0; i < 4; ++i) b[i] = take((300 + 50 * i) * MB, false);  // 1500 MB together
+    for (const IndexBlock &i : b) index_memory_give(0, i);
+    IndexBlock large = take(3000 * MB, false);
+    index_memory_give(0, large);
+    CHECK(stub.frees == 1 && stub.bytes == 1500 * MB);
+    IndexBlock more = take(700 * MB, false);
+    index_memory_give(0, more);  // 2200 MB: the oldest, 300 MB, goes
+    CHECK(stub.frees == 2 && stub.bytes == 1900 * MB);
+    index_memory_give(0, take(350 * MB, false));
+    CHECK(stub.frees == 2);
+    index_memory_leave(0);
+    CHECK(stub.bytes == 0);
+}
+
 int main(int, char **argv) {
     if (!std::strcmp(argv[1], "reuse")) reuse();
     else if (!std::strcmp(argv[1], "no_exceptions")) no_exceptions();
     else if (!std::strcmp(argv[1], "slack")) slack();
+    else if (!std::strcmp(argv[1], "limit")) limit();
     else return 2;
     CHECK(stub.wrong == 0);
     return failed != 0;
