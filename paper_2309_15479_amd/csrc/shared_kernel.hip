@@ -593,7 +593,8 @@ int launch_shared(const lsh_params *p, int ep, const float *d_data, uint64_t N, 
     if (gx > ntiles) gx = ntiles;
     dim3 grid((uint32_t)gx, kblocks);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const bool geom = p->n == 128 && pl.rows == 128 && pl.stride == 132;
+    // the instances with the geometry of n = 128 built in are for lists of up to 64 samples; longer ones take the general one
+    const bool geom = p->n == 128 && pl.rows == 128 && pl.stride == 132 && pl.ksteps <= 16;
     if (ep == 3 && pl.ksteps == 32 && pl.waves == 16 && !geom) {
         if (tables_per_wave == 2) return launch(&shared_kernel<32, 2, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
         if (tables_per_wave == 4) return launch(&shared_kernel<32, 4, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
