@@ -42,9 +42,9 @@ def test_probe_finds_both_ends_of_every_bucket(lsh, N, L, distinct):
 
 
 # n: fewer pieces than a group of 8 lanes, partial pieces, several turns of a wave, around and above
-# the largest query kept in LDS; Q on each side of 256 and of 1000 queries
+# the largest query kept in LDS; Q on each side of 256, 768 and 1024 queries, soon done or not
 @pytest.mark.parametrize("n,N,L,Q,distinct,shift", [(4, 50, 1, 3, 7, 0), (24, 5000, 3, 257, 4, 0), (30, 3000, 5, 20, 2, 0),
-                                                    (24, 500, 2, 1001, 9, 0), (128, 2500, 300, 9, 50, 0), (128, 400, 6, 5, 3, 1),
+                                                    (24, 500, 2, 1001, 9, 0), (260, 300, 2, 769, 5, 0), (260, 300, 2, 1025, 5, 0), (128, 2500, 300, 9, 50, 0), (128, 400, 6, 5, 3, 1),
                                                     (960, 1500, 40, 30, 12, 0), (11264, 60, 3, 4, 3, 0),
                                                     (11268, 60, 3, 4, 3, 0), (16367, 40, 2, 3, 2, 0)])
 @pytest.mark.parametrize("limit", [0, 1, 96, 1100])
