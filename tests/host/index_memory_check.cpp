@@ -114,11 +114,95 @@ static void limit() {
     CHECK(stub.bytes == 0);
 }
 
+// scratch beyond the limit is stream-ordered and never kept; what is in use counts
+static void scratch_limit() {
+    index_memory_enter(0);
+    IndexBlock a = take(900 * MB, true), b = take(900 * MB, true), c = take(900 * MB, true);
+    CHECK(!a.stream_ordered && !b.stream_ordered && c.stream_ordered);
+    index_memory_give_scratch(0, c, s);
+    CHECK(stub.frees == 1);
+    index_memory_give_scratch(0, a, s);
+    IndexBlock t = take(400 * MB, false);
+    index_memory_give(0, t);  // 900 kept, 900 in use and 400 more: the 900 kept go
+    CHECK(stub.frees == 2 && stub.bytes == 1300 * MB);
+    index_memory_give_scratch(0, b, s);
+    IndexBlock d = take(900 * MB, true);
+    CHECK(d.ptr == b.ptr && !d.stream_ordered);
+    index_memory_give_scratch(0, d, s);
+    index_memory_leave(0);
+    CHECK(stub.bytes == 0 && stub.events == 0);
+    index_memory_enter(0);  // nothing is counted any more
+    a = take(1000 * MB, true), b = take(1000 * MB, true);
+    CHECK(!a.stream_ordered && !b.stream_ordered);
+    index_memory_give_scratch(0, a, s);
+    index_memory_give_scratch(0, b, s);
+    index_memory_leave(0);
+    CHECK(stub.bytes == 0 && stub.events == 0);
+}
+
+// when memory runs out the kept blocks go before a build is refused, and a refused one leaves no trace
+static void out_of_memory() {
+    stub.most = 2000 * MB;
+    index_memory_enter(0);
+    IndexBlock a = take(800 * MB, false), b = take(700 * MB, true);
+    index_memory_give(0, a);
+    index_memory_give_scratch(0, b, s);
+    IndexBlock t = take(1500 * MB, false);  // both go
+    CHECK(stub.frees == 2 && stub.events == 0);
+    IndexBlock x;
+    CHECK(!index_memory_take(0, 1000 * MB, true, s, x) && !x.ptr);
+    CHECK(!index_memory_take(0, 1000 * MB, false, s, x) && !x.ptr);
+    index_memory_give(0, t);
+    index_memory_leave(0);
+    CHECK(stub.bytes == 0);
+    stub.most = SIZE_MAX;
+    index_memory_enter(0);
+    a = take(1000 * MB, true), b = take(1000 * MB, true);  // nothing is counted any more
+    CHECK(!a.stream_ordered && !b.stream_ordered);
+    index_memory_give_scratch(0, a, s);
+    index_memory_give_scratch(0, b, s);
+    index_memory_leave(0);
+    CHECK(stub.bytes == 0 && stub.events == 0);
+}
+
+// indexes built and destroyed by several threads: no block is with two of them, and all go in the end
+static void threads() {
+    static std::mutex in_use_mu;
+    static std::map<void *, int> in_use;
+    auto hold = [](const IndexBlock &b, int by) {
+        std::lock_guard<std::mutex> lock(in_use_mu);
+        int &user = in_use[b.ptr];
+        if (by && user) ++failed;
+        user = by;
+    };
+    auto work = [&](int seed) {
+        for (int i = 0; i < 300; ++i) {
+            index_memory_enter(0);
+            IndexBlock t, x;
+            const size_t n = (size_t)(20 + (seed * 37 + i * 13) % 400) * MB;
+            if (!index_memory_take(0, n, false, s, t) || !index_memory_take(0, n + 5 * MB, true, s, x)) ++failed;
+            hold(t, seed), hold(x, seed);
+            hold(x, 0);
+            index_memory_give_scratch(0, x, s);
+            hold(t, 0);
+            index_memory_give(0, t);
+            index_memory_leave(0);
+        }
+    };
+    std::vector<std::thread> all;
+    for (int i = 1; i <= 6; ++i) all.emplace_back(work, i);
+    for (std::thread &t : all) t.join();
+    CHECK(stub.bytes == 0 && stub.events == 0);
+}
+
 int main(int, char **argv) {
     if (!std::strcmp(argv[1], "reuse")) reuse();
     else if (!std::strcmp(argv[1], "no_exceptions")) no_exceptions();
     else if (!std::strcmp(argv[1], "slack")) slack();
     else if (!std::strcmp(argv[1], "limit")) limit();
+    else if (!std::strcmp(argv[1], "scratch_limit")) scratch_limit();
+    else if (!std::strcmp(argv[1], "out_of_memory")) out_of_memory();
+    else if (!std::strcmp(argv[1], "threads")) threads();
     else return 2;
     CHECK(stub.wrong == 0);
     return failed != 0;

@@ -1,5 +1,9 @@
 """Launches of few vectors deal a tile's functions (and sub-tiles) to more workgroups than launches of
 many do, out of the same lists: a vector's results are the same numbers either way."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -50,24 +54,36 @@ def test_few_vectors_equal_many(lsh, n, k, m, L, w):
                 assert torch.equal(ids, many["ids"][rows]) and torch.equal(keys, many["keys"][rows])
 
 
+_CAPTURED = """
+import sys
+import torch
+import paper_2309_15479_amd as lsh
+n, k, m = (int(x) for x in sys.argv[1:])
+g = torch.Generator(device="cuda")
+g.manual_seed(m)
+data = torch.randn((9000, n), generator=g, device="cuda")
+call = lsh.hash_e2lsh if m == n else lsh.hash_fastlsh
+with lsh.LshParams(n, k, m, 4.0, 21) as p:
+    out = torch.empty((9000, k), dtype=torch.int32, device="cuda")
+    call(p, data[:8].clone())
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(p, data, out=out)
+    want = call(p, data)
+    for _ in range(3):
+        out.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    print("captured", flush=True)
+"""
+
+
 @pytest.mark.parametrize("n,k,m", [(960, 1024, 960), (4096, 2048, 64), (960, 1024, 128)])
 def test_many_captured_after_few(lsh, n, k, m):
-    """A program that has only hashed few vectors so far may capture a launch of many (another kernel, on
-    first use)."""
-    g = torch.Generator(device="cuda")
-    g.manual_seed(m)
-    data = torch.randn((9000, n), generator=g, device="cuda")
-    call = lsh.hash_e2lsh if m == n else lsh.hash_fastlsh
-    with lsh.LshParams(n, k, m, 4.0, 21) as p:
-        out = torch.empty((9000, k), dtype=torch.int32, device="cuda")
-        call(p, data[:8].clone())
-        torch.cuda.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            call(p, data, out=out)
-        want = call(p, data)
-        for _ in range(3):
-            out.fill_(-7)
-            graph.replay()
-            torch.cuda.synchronize()
-            assert torch.equal(out, want)
+    """A program that has only hashed few vectors so far may capture a launch of many: another kernel, on
+    first use, whose limits are raised inside the capture (they are raised once a process, hence a fresh one)."""
+    r = subprocess.run([sys.executable, "-c", _CAPTURED, str(n), str(k), str(m)], capture_output=True, text=True, timeout=100,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0 and "captured" in r.stdout, r.stdout + r.stderr

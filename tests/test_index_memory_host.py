@@ -22,7 +22,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["reuse", "no_exceptions", "slack", "limit"])
+@pytest.mark.parametrize("check", ["reuse", "no_exceptions", "slack", "limit", "scratch_limit", "out_of_memory", "threads"])
 def test_index_memory(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr

@@ -12,6 +12,8 @@ torch = pytest.importorskip("torch")
     (500, 800, 100, 40),     # two blocks of functions a table, the last waves idle
     (260, 136, 65, 34),      # tables of four functions, two and a bit for every wave
     (964, 128, 90, 16),      # one table a wave already
+    (500, 640, 100, 32),     # two tables a wave
+    (960, 80, 128, 20),      # the same, the last waves with one table and none
 ])
 def test_kappa_of_all_equals_largest_of_parts(n, k, m, L):
     if not torch.cuda.is_available():
