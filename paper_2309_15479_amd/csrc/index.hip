@@ -610,15 +610,16 @@ void launch_nearest(const lsh_index *ix, const float *d_data, const float *d_que
     const uint32_t pieces = pieces4 ? n / 4 : n;
     uint32_t group_lanes = 8;
     while (group_lanes < 64 && group_lanes < pieces) group_lanes *= 2;
-    // Up to a query for each of the 256 CUs: a workgroup as large as can be for each.  More of them: half of that, of
-    // which a CU runs three at a time.  Beyond 768 queries a quarter, where it pays: if a query is soon done (what a
-    // workgroup spends around its candidates weighs more then), or if the queries fit in one round of four a CU
-    // and a vector takes whole waves.  With 256, 512, 1024 threads, us: about 480 candidates a query of 960
-    // dimensions, 128 queries 35, 21, 17; 400: 41, 32, 36; 900: 61, 65, 72; 1300: 92, 85, 105; 4000: 228, 224, 271; 96 candidates of
-    // 128 dimensions, 512: 12.3, 12.6, 15.0; 1024: 14, 20, 30; 4000: 40, 57, 103; about 900 of them, 400: 94, 53, 54; 900: 113, 89, 92;
-    // 4000: 250, 228, 330.
-    const bool soon_done = (uint64_t)limit * n <= 1u << 16, one_round = Q <= 1024 && group_lanes == 64;
-    const uint32_t threads = Q <= 256 ? kNearestThreads : Q <= 768 || !(soon_done || one_round) ? kNearestThreads / 2 : kNearestThreads / 4;
+    // Up to a query for each of the 256 CUs: a workgroup as large as can be for each.  Up to three a CU, as many as run
+    // at a time: half of that.  Beyond four a CU, the most of a quarter that run at a time: a quarter, because what a workgroup
+    // spends around its candidates weighs most when they are few, and how many there are is on the device.  Between the two a
+    // quarter where it fits all: limits that a query is soon done with, and vectors of whole waves.  With 256, 512,
+    // 1024 threads, us: about 480 candidates a query of 960 dimensions, 128 queries 35, 21, 17; 400: 41, 32, 36; 900: 61, 65, 72;
+    // 1300: 92, 85, 105; 4000: 228, 224, 271; 42 of them, few distinct, 4096: 25, 46; 96 candidates of 128 dimensions, 512:
+    // 12.3, 12.6, 15.0; 1024: 14, 20, 30; 4000: 40, 57, 103; about 900 of them, 400: 94, 53, 54; 900: 113, 89, 92; 4000: 250, 228, 330.
+    const bool soon_done = (uint64_t)limit * n <= 1u << 16, whole_waves = group_lanes == 64;
+    const uint32_t threads = Q <= 256 ? kNearestThreads
+                             : Q <= 768 || (Q <= 1024 && !soon_done && !whole_waves) ? kNearestThreads / 2 : kNearestThreads / 4;
     auto launch = [&](auto kernel, uint32_t lds) {
         hipLaunchKernelGGL(kernel, dim3((uint32_t)Q), dim3(threads), lds, s, ix->d_ids, ix->N, ix->L, d_data, d_queries, n,
                            group_lanes, d_start, d_count, limit, d_best_id, d_best_score);
