@@ -11,9 +11,10 @@ whole path over that batch, inputs and outputs resident in HBM:
 `value` is hashes per second over the whole step (4 * N * k hash evaluations per step).  Per-kernel
 times come from HIP events recorded on the launch stream inside the timed region.  Outside the
 timed region the other paper-shaped workloads (tiny, SIFT-shaped, GIST-shaped, angular) are timed
-call by call and reported in `configs`, each with its rooflines, and sampled rows of every output
-are compared with the CPU oracle (mismatch counts, boundary-excluded fraction, fraction of
-projections within a plain relative 1e-5).  Prints ONE JSON line.
+call by call, and sampled rows of every output are compared with the CPU oracle (mismatch counts,
+boundary-excluded fraction, fraction of projections within a plain relative 1e-5).  Prints ONE JSON
+line, with the time of every call and the number of mismatches over all; the calls one by one, each with
+its rooflines, its parity and its shapes, go to standard error as a line that starts with "configs: ".
 """
 import argparse
 import hashlib
@@ -430,6 +431,11 @@ class Bench:
             best, dist2 = ix.nearest(data, queries, start, count)
             torch.cuda.synchronize()
             candidates = int(count.to(torch.int64).sum().item())
+            # an id met in several of a query's buckets is listed again, and its vector read once
+            off_all, cand_all = ix.candidates(start, count)
+            query = torch.repeat_interleave(torch.arange(Q, device=self.dev), (off_all[L::L] - off_all[:-L:L]).to(torch.int64))
+            distinct = int(torch.unique(query * N + cand_all.to(torch.int64)).numel())
+            del off_all, cand_all, query
             found_source = float((best.to(torch.int64) == rows).float().mean().item())
             parity = None
             if not self.args.no_parity:
@@ -465,8 +471,9 @@ class Bench:
                         roofline=hbm_roofline(N * L * 8 * 32, build_ms)))
         out.append(dict(base, call="lsh_index_probe", queries=Q, ms=probe_ms, parity=parity))
         out.append(dict(base, call="lsh_index_nearest", queries=Q, ms=nearest_ms, candidates=candidates,
-                        dtype="f32", queries_whose_source_vector_is_returned=found_source,
-                        roofline=hbm_roofline(candidates * 4 * n, nearest_ms)))
+                        distinct_candidates=distinct, dtype="f32", queries_whose_source_vector_is_returned=found_source,
+                        # the list, the queries and every distinct candidate's vector read once
+                        roofline=hbm_roofline(candidates * 4 + (Q + distinct) * 4 * n, nearest_ms)))
         return out
 
     def graph_entry(self, wl, data):
@@ -628,6 +635,36 @@ class Bench:
         return result
 
 
+def calls_ms(configs):
+    """The time of every call in milliseconds, by workload, call and variant."""
+    out = {}
+    for e in configs:
+        name = e["call"].replace("lsh_hash_", "").replace("lsh_", "")
+        if "m" in e:
+            name += f" m={e['m']}"
+        if "variant" in e:
+            name += " shared"
+        out.setdefault(e["workload"], {})[name] = round(e["ms"], 4)
+        if "matrix_core_route_ms" in e:
+            out[e["workload"]][name + " matrix"] = round(e["matrix_core_route_ms"], 4)
+        if "matrix_core_route" in e:
+            out[e["workload"]][name + " matrix"] = round(e["matrix_core_route"]["ms"], 4)
+    return out
+
+
+def mismatches(configs):
+    """What was compared with the oracle over all calls, and what differed outside the boundary bands."""
+    checked = wrong = 0
+    for e in configs:
+        for p in (e.get("parity"), (e.get("matrix_core_route") or {}).get("parity")):
+            for key, value in (p or {}).items():
+                if key.endswith("_checked") and key != "rows_checked":
+                    checked += value
+                elif key.endswith("_mismatches_outside_band") or key.endswith("_mismatches") or key.startswith("ids_differing"):
+                    wrong += value
+    return {"checked": checked, "mismatches_outside_bands": wrong}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -664,8 +701,9 @@ def main():
         if name in only:
             configs.extend(b.config(name))
 
+    print("configs: " + json.dumps(configs), file=sys.stderr, flush=True)
     if head is None:
-        print(json.dumps({"configs": configs}))
+        print(json.dumps({"calls_ms": calls_ms(configs), "parity": mismatches(configs)}))
         return
     N, k, n = head["N"], head["k"], head["n"]
     hashes_per_step = 4.0 * N * k
@@ -692,7 +730,8 @@ def main():
         "fastlsh_speedup_over_e2lsh": {leg: head["ms"]["e2lsh"] / v for leg, v in head["ms"].items() if leg != "e2lsh"},
         "dominant_kernel": head["dominant"],
         "roofline": head["roofline"],
-        "configs": configs,
+        "calls_ms": calls_ms(configs),
+        "parity": mismatches(configs),
         "paper_context": "the paper reports up to ~80x faster hash evaluation than E2LSH at n=4096, m=30 on a "
                          "6-core laptop CPU (Sec. 6, Experiment 1); other hardware, not a target",
     }
