@@ -300,7 +300,7 @@ int lsh_time_launches(const lsh_params_t *params, int which, const void *d_in, u
  *
  * lsh_index_build: d_keys [N][L] (device, as written by lsh_pack_keys or
  *   lsh_hash_fastlsh_keys), N < 2^31, L <= 65535.  Sorts all L columns together on `stream`
- *   (a stable radix sort of this library, eight passes of 8 bits, the keys read in place) and
+ *   (a stable radix sort of this library, eight passes of 8 bits, from a copy of the keys column by column) and
  *   does not wait: d_keys must stay alive until the stream has passed the build, and the index
  *   may be used by later work on the same stream (or after synchronising).  A second buffer of
  *   12 bytes per pair serves as scratch.  While any index is alive on a device, the memory of

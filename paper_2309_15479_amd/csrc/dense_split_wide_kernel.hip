@@ -26,6 +26,8 @@
 // instruction or the split of one vector element after each (scheduling barriers keep that
 // order); one LDS-only barrier per stage.
 //
+// The tile itself is in dense_wide_tile.h; dense_half_kernel.hip uses it, too.
+//
 // Placement: workgroup g runs on XCD g % 8.  XCD x takes the vector tiles x, x + 8, ...; the
 // F function tiles of a vector tile go to F workgroups of that XCD, which walk the stages in
 // step, so a vector stage is fetched into the XCD's L2 once and the other F - 1 workgroups hit
