@@ -98,7 +98,7 @@ constexpr uint32_t kHalfMinTerms = 128;
 constexpr float kLargestHalf = 65504.f;
 constexpr int kFunctionTop = 14;                  // exponent of a function's largest coefficient after scaling
 constexpr int kEvenTop = 5, kUnevenTop = 9;       // of a vector's largest looked-at coordinate, see vector_scale
-constexpr int kRegularCount = 8;                  // looked-at coordinates of 2^2 and more after scaling that make a vector regular
+constexpr uint32_t kRegularCount = 8;                  // looked-at coordinates of 2^2 and more after scaling that make a vector regular
 constexpr float kRegularLeast = 1.17549435e-38f;  // 2^-126, which the largest scale, 2^126, takes to 1
 constexpr int kOdd = 4096;                        // added to the exponent of an odd vector
 
@@ -405,28 +405,48 @@ __global__ __launch_bounds__(kThreadsH) void dense_half_kernel(const HalfArgs a)
                         there[h] = fmaxf(there[h], __shfl_xor(there[h], 2));
                     }
                 }
+                // The largest of two halves of a thread's coordinates: if the least of a vector's eight is an eighth of
+                // their largest, as it nearly always is, nothing needs counting (2 % of the time at n = 300).
+                uint32_t count[4];
+                bool sure = true;
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    float half[2] = {0.f, 0.f};
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) half[p] = fmaxf(fmaxf(fabsf(gv[t][h][2 * p]), fabsf(gv[t][h][2 * p + 1])), half[p]);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) half[p] = fmaxf(fmaxf(fabsf(far_v[t][h][2 * p]), fabsf(far_v[t][h][2 * p + 1])), half[p]);
+                    }
+                    float top = fmaxf(half[0], half[1]), least = fminf(half[0], half[1]);
+                    top = fmaxf(top, __shfl_xor(top, 1));  // the four threads of a vector are neighbours
+                    least = fminf(least, __shfl_xor(least, 1));
+                    top = fmaxf(top, __shfl_xor(top, 2));
+                    least = fminf(least, __shfl_xor(least, 2));
+                    largest[h] = top;
+                    count[h] = kRegularCount | kRegularCount << 16;
+                    sure = sure && least >= top * 0x1p-3f;
+                }
+                if (!__all(sure)) {
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        count[h] = 0;
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) count[h] += count_large(gv[t][h], largest[h]);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) count[h] += count_large(far_v[t][h], largest[h]);
+                        count[h] += __shfl_xor(count[h], 1);
+                        count[h] += __shfl_xor(count[h], 2);
+                    }
+                }
                 uint32_t regular = 0;
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    float top = 0.f;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) top = largest_of(gv[t][h], top);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) top = largest_of(far_v[t][h], top);
-                    top = fmaxf(top, __shfl_xor(top, 1));  // the four threads of a vector are neighbours
-                    top = fmaxf(top, __shfl_xor(top, 2));
-                    uint32_t count = 0;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) count += count_large(gv[t][h], top);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) count += count_large(far_v[t][h], top);
-                    count += __shfl_xor(count, 1);
-                    count += __shfl_xor(count, 2);
-                    int e = vector_scale(top, count);
+                    int e = vector_scale(largest[h], count[h]);
                     if (e < kOdd / 2 && there[h] * power_of_two(e) > kLargestHalf) e += kOdd;
                     regular += __popcll(__ballot(vq == 0 && e < kOdd / 2));
                     scale[h] = power_of_two(e < kOdd / 2 ? e : 0);
-                    largest[h] = top;
                     if (vq == 0) vector_exp[vr + h * 64] = e;
                 }
                 if (lane == 0) atomicAdd(const_cast<uint32_t *>(regular_count) + turn, regular);
