@@ -48,16 +48,16 @@ CSRC = os.path.join(ROOT, "paper_2309_15479_amd", "csrc")
 _KIB = 1024
 _RANGED = {"ranged_kernel.hip": "f463328615aec617", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
 _STREAMED = {"sampled_kernel.hip": "df4f64747e76c3a2", "sampled_common.h": "9d6a9ea08ffad892"}
-_HALF = {"dense_half_kernel.hip": "6cf7f5401e877e13", "dense_wide_tile.h": "4593d80dcc31c64a"}
+_HALF = {"dense_half_kernel.hip": "15fa3b3442606604", "dense_wide_tile.h": "4593d80dcc31c64a"}
 _SUMMARY = "profiles/hbm_traffic_all_workloads.md"
 MEASURED_TRAFFIC = {
     "highdim/fastlsh/m64": (1767065 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
     "highdim/fastlsh/m256": (2221315 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
     "highdim/fastlsh/m1024": (4060067 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/e2lsh": (4947338 * _KIB, 1633774 * _KIB, _SUMMARY, _HALF),
+    "highdim/e2lsh": (4947326 * _KIB, 1633771 * _KIB, _SUMMARY, _HALF),
     "sift/fastlsh/m32": (250605 * _KIB, 2000000 * _KIB, _SUMMARY, _STREAMED),
     "gist/fastlsh/m128": (2375589 * _KIB, 4000000 * _KIB, _SUMMARY, _STREAMED),
-    "gist/e2lsh": (3084813 * _KIB, 4080555 * _KIB, _SUMMARY, _HALF),
+    "gist/e2lsh": (3079718 * _KIB, 4080556 * _KIB, _SUMMARY, _HALF),
     "angular/signs/m512": (56162943 * _KIB, 250022 * _KIB, _SUMMARY, _RANGED),
 }
 
