@@ -48,7 +48,7 @@ CSRC = os.path.join(ROOT, "paper_2309_15479_amd", "csrc")
 _KIB = 1024
 _RANGED = {"ranged_kernel.hip": "f463328615aec617", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
 _STREAMED = {"sampled_kernel.hip": "df4f64747e76c3a2", "sampled_common.h": "9d6a9ea08ffad892"}
-_HALF = {"dense_half_kernel.hip": "15fa3b3442606604", "dense_wide_tile.h": "4593d80dcc31c64a"}
+_HALF = {"dense_half_kernel.hip": "2b20f5f3b2ee4dac", "dense_wide_tile.h": "4593d80dcc31c64a"}
 _SUMMARY = "profiles/hbm_traffic_all_workloads.md"
 MEASURED_TRAFFIC = {
     "highdim/fastlsh/m64": (1767065 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),

@@ -91,14 +91,14 @@ constexpr uint32_t kSegment = 16;          // tiles after which the odd vectors 
 constexpr int kOddList = wide::kLdsBytes;  // LDS offset of their numbers in the segment, 16 bits each
 constexpr int kOddCount = kOddList + (int)kSegment * TVW * 2;  // of the words below
 constexpr int kLdsBytesH = kOddCount + 24;
-constexpr uint32_t kFewRegular = 48;       // a tile with so few regular vectors is not contracted: they are put by as well, for few_block (1.6 us each; the tile 94)
+constexpr uint32_t kFewRegular = 48;       // a tile of so few regular vectors is not contracted (94 us): they are put by, too, for few_block (1.6 us each)
 constexpr uint32_t kFewOdd = 64;           // up to so many by blocks of 32 x 32 (80 us at n = 960), more by tiles (150 us)
 constexpr int kResultRow = 144;            // bytes of a vector's 32 results in LDS on their way out: conflict-free both ways
 constexpr uint32_t kHalfMinTerms = 128;
 constexpr float kLargestHalf = 65504.f;
 constexpr int kFunctionTop = 14;                  // exponent of a function's largest coefficient after scaling
 constexpr int kEvenTop = 5, kUnevenTop = 9;       // of a vector's largest looked-at coordinate, see vector_scale
-constexpr uint32_t kRegularCount = 8;                  // looked-at coordinates of 2^2 and more after scaling that make a vector regular
+constexpr uint32_t kRegularCount = 8;             // looked-at coordinates of 2^2 and more after scaling that make a vector regular
 constexpr float kRegularLeast = 1.17549435e-38f;  // 2^-126, which the largest scale, 2^126, takes to 1
 constexpr int kOdd = 4096;                        // added to the exponent of an odd vector
 
@@ -795,7 +795,7 @@ int launch_dense_half(const lsh_params *p, bool proj, const float *d_data, uint6
     const bool vec = p->k % 4 == 0;
     const uint64_t waves = (N + 31) / 32 * ((p->k + 31) / 32);
     const bool few = waves <= kFewWaves;
-    // one workgroup per CU (97 KB of LDS, all registers), a multiple of 8 so that every XCD gets the same number
+    // one workgroup per CU (152 KB of LDS, all registers), a multiple of 8 so that every XCD gets the same number
     uint32_t wgs = (uint32_t)(p->num_cus > 0 ? p->num_cus : 256) / 8 * 8;
     if (wgs < 8) wgs = 8;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);

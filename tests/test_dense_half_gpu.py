@@ -61,8 +61,8 @@ def test_projections(lsh, kind, N, n, k):
 
 
 def test_ids_do_not_depend_on_the_batch(lsh):
-    """A vector's scale is its own: its ids are the same alone, among others, and beside vectors that make
-    their tile be done twice or hold no number at all."""
+    """A vector's scale is its own: its ids are the same alone, among others, and beside vectors that are
+    contracted apart or hold no number at all."""
     n, k = 964, 300
     data = _data("normal", 600, n)
     with lsh.LshParams(n, k, n, 3.0, 12) as p:
