@@ -300,10 +300,10 @@ int lsh_time_launches(const lsh_params_t *params, int which, const void *d_in, u
  *
  * lsh_index_build: d_keys [N][L] (device, as written by lsh_pack_keys or
  *   lsh_hash_fastlsh_keys), N < 2^31, L <= 65535.  Sorts all L columns together on `stream`
- *   (a stable radix sort of this library, eight passes of 8 bits, from a copy of the keys column by column) and
- *   does not wait: d_keys must stay alive until the stream has passed the build, and the index
+ *   (a stable sort of this library: by buckets between sampled splitters up to N = 2^20, by eight passes of 8 bits
+ *   beyond) and does not wait: d_keys must stay alive until the stream has passed the build, and the index
  *   may be used by later work on the same stream (or after synchronising).  A second buffer of
- *   12 bytes per pair serves as scratch.  While any index is alive on a device, the memory of
+ *   about 12 bytes per pair serves as scratch.  While any index is alive on a device, the memory of
  *   destroyed ones and of scratch is kept for the next build, up to 2 GiB; the destruction of the
  *   last one gives it back.
  * lsh_index_destroy: waits for the device, as hipFree does (work on any stream may still read the

@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblsh.so")
 SOURCES = ["api.hip", "sampled_kernel.hip", "ranged_kernel.hip", "shared_kernel.hip", "shared_ranged_kernel.hip", "dense_kernel.hip",
-           "dense_split_kernel.hip", "dense_split_wide_kernel.hip", "dense_half_kernel.hip", "pack_kernel.hip", "index.hip", "index_memory.cpp", "params_host.cpp", "schedule.cpp",
+           "dense_split_kernel.hip", "dense_split_wide_kernel.hip", "dense_half_kernel.hip", "pack_kernel.hip", "index.hip", "index_sort.hip", "index_memory.cpp", "params_host.cpp", "schedule.cpp",
            "collision_law.cpp", "selfcheck.cpp"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

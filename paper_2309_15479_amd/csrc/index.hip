@@ -3,8 +3,8 @@
 //
 // The paper fixes what a table holds (every vector's id under its key H_l(v)) and how a query
 // uses it (fetch the L buckets H_1(u) .. H_L(u), evaluate the candidates), not a layout.  Here a
-// table is the vector ids sorted by key (a stable radix sort of N <key, id> pairs, ids
-// ascending inside a bucket; all tables are sorted together by the kernels below): a bucket is a contiguous run of the sorted ids, found by binary
+// table is the vector ids sorted by key (a stable sort of N <key, id> pairs, ids
+// ascending inside a bucket; all tables are sorted together, by index_sort.hip or by the kernels below): a bucket is a contiguous run of the sorted ids, found by binary
 // search of the sorted keys.  No chains, no resizing, 12 bytes per vector and table.
 //
 //   build      keys [N][L] -> per table: sorted keys [N], ids in key order [N]
@@ -20,6 +20,7 @@
 #include <new>
 
 #include "index_memory.h"
+#include "index_sort.h"
 #include "lsh.h"
 
 struct lsh_index {
@@ -174,6 +175,7 @@ int launch_offsets_scan(const uint32_t *d_count, uint64_t items, uint64_t *d_par
     return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
 }
 
+// Tables of more than 2^20 pairs (the others: index_sort.hip).
 // Stable least-significant-digit radix sort of all L key columns at once (one grid row per
 // table): eight passes of 8 bits.  A pass is three launches: per-tile digit histograms, an
 // exclusive scan of every table's and digit's counts over the tiles, and the scatter.  A tile is 4096
@@ -659,7 +661,9 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const uint32_t tiles = (uint32_t)((N + kSortTile - 1) / kSortTile);
     const size_t pairs = (size_t)L * N;
+    const bool by_buckets = lsh::bucket_sort_takes(N, L);
     // scratch: the other half of the ping-pong, and the (digit, tile) counts of every table
+    const size_t scratch_bytes = by_buckets ? lsh::bucket_sort_scratch(N, L) : pairs * 12 + (size_t)L * 256 * (tiles + 1) * 4;
     lsh::IndexBlock scratch;
     uint64_t *tmp_keys = nullptr;
     uint32_t *tmp_ids = nullptr, *hist = nullptr, *total = nullptr;
@@ -670,7 +674,7 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
     }
     lsh::index_memory_enter(ix->device);
     if (!lsh::index_memory_take(ix->device, pairs * 12, false, s, ix->tables)) rc = LSH_ERR_ALLOC;
-    if (rc == LSH_OK && !lsh::index_memory_take(ix->device, pairs * 12 + (size_t)L * 256 * (tiles + 1) * 4, true, s, scratch))
+    if (rc == LSH_OK && !lsh::index_memory_take(ix->device, scratch_bytes, true, s, scratch))
         rc = LSH_ERR_ALLOC;
     if (rc == LSH_OK) {
         ix->d_keys = static_cast<uint64_t *>(ix->tables.ptr);
@@ -680,7 +684,10 @@ int lsh_index_build(const uint64_t *d_keys, uint64_t N, uint32_t L, void *stream
         hist = tmp_ids + pairs;
         total = hist + (size_t)L * 256 * tiles;
     }
-    if (rc == LSH_OK) {
+    if (rc == LSH_OK && by_buckets) {
+        lsh::launch_bucket_sort(d_keys, N, L, scratch.ptr, ix->d_keys, ix->d_ids, s);
+        if (hipGetLastError() != hipSuccess) rc = LSH_ERR_HIP;
+    } else if (rc == LSH_OK) {
         const dim3 grid(tiles, L), block(kSortThreads);
         // eight passes; odd passes write the index's own arrays, so the last one ends there
         for (uint32_t pass = 0; pass < 8; ++pass) {

@@ -53,6 +53,47 @@ def _random_keys(N, L, distinct, seed):
     return torch.gather(pool, 0, torch.randint(0, distinct, (N, L), generator=g, device="cuda"))
 
 
+def _keys_of(kind, N, L, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    some = lambda *shape: torch.randint(-2 ** 63, 2 ** 63 - 1, shape, generator=g, device="cuda")
+    below = lambda k: torch.randint(0, k, (N, L), generator=g, device="cuda")
+    if kind == "random":
+        return some(N, L)
+    if kind == "one":
+        return torch.full((N, L), -5, device="cuda")
+    if kind == "half":          # one key half of the time
+        return torch.where(below(2) == 0, some(N, L), torch.full((N, L), 77, device="cuda"))
+    if kind == "few":           # the keys of tables of one function: ids, negative ones as 32 unsigned bits
+        return (below(20) - 10) & 0xFFFFFFFF
+    if kind == "groups":        # keys that agree in all functions but the last
+        return some(max(1, N // 40), L)[below(max(1, N // 40)), torch.arange(L, device="cuda")] + ((below(5) - 2) & 0xFFFFFFFF)
+    if kind == "ends":
+        return torch.tensor([0, -1, -2, 2 ** 63 - 1, -2 ** 63], device="cuda")[below(5)]
+    return (torch.arange(N, device="cuda")[:, None] * 3 + torch.arange(L, device="cuda")) * (1 if kind == "rising" else -1)
+
+
+# around a tile of 4096 rows, buckets of one workgroup's 4096 and 8192 pairs, four tables at a time, and the line between
+# the two sorts at 2^20
+@pytest.mark.parametrize("kind", ["random", "one", "half", "few", "groups", "ends", "rising", "falling"])
+@pytest.mark.parametrize("N,L", [(1, 1), (2, 5), (4095, 2), (4096, 3), (4097, 4), (8193, 1), (70001, 6), (300000, 1),
+                                 (2 ** 20, 1), (2 ** 20 + 1, 1)])
+def test_tables_of_all_kinds_of_keys(lsh, kind, N, L):
+    print(f"{kind} N={N} L={L}", flush=True)
+    keys = _keys_of(kind, N, L, N + L).contiguous()
+    with lsh.LshIndex(keys) as ix:
+        _check(lsh, ix, keys, f"{kind} N={N} L={L}")
+
+
+def test_keys_on_no_boundary_of_16_bytes(lsh):
+    keys = _random_keys(9001, 2, 4000, 3)
+    moved = torch.empty(keys.numel() + 1, dtype=torch.int64, device="cuda")[1:].view(9001, 2)
+    moved.copy_(keys)
+    assert moved.data_ptr() % 16 == 8
+    with lsh.LshIndex(moved) as ix:
+        _check(lsh, ix, keys, "keys at 8 modulo 16")
+
+
 def test_tables_built_in_memory_of_earlier_indexes(lsh):
     """Indexes of several sizes built, used and dropped in turn: each must be whole while others come
     and go in the memory that earlier ones and their scratch left behind."""
