@@ -529,6 +529,153 @@ __global__ __launch_bounds__(kThreadsS, 2) void dense_split_kernel(const SplitAr
     for (int piece = 0; piece < 8; ++piece) store_piece(std::false_type{}, t_prev, piece);
 }
 
+struct KeyPowers {  // C^0, C^4, ... C^28
+    uint64_t of[8];
+};
+constexpr KeyPowers key_powers() {
+    KeyPowers p = {};
+    uint64_t power = 1;
+    for (int i = 0; i < 8; ++i) {
+        p.of[i] = power;
+        for (int e = 0; e < 4; ++e) power *= kKeyMultiplier;
+    }
+    return p;
+}
+__constant__ const KeyPowers kKeyPowers = key_powers();
+
+// Few vectors.  The kernel above takes 9 to 12 us for any launch of one tile a workgroup: every wave brings in and splits the
+// coefficients of its functions, the whole tile is split ahead of the first product, and each of up to eight active
+// waves then forms 96 products in a row.  Here a wave takes one block of 32 functions x 32 vectors, 48 products, and
+// splits its coefficients step by step among them; the vectors are split by the waves that share them.
+// FW of the four waves of a workgroup lie along the functions, 4 / FW along the vectors.  The
+// products of a result and their order are those of the kernel above, and so are all bits.  Keys of 8 queries (k = 512)
+// 12.0 -> 5.8 us, ids of 10000 vectors (k = 64) 8.0 -> 6.5, signs of 1000 (k = 512) 13.3 -> 4.8; an empty launch takes 1.5 to 2.
+template <int EP, bool POW2, int FW>
+__global__ __launch_bounds__(256) void dense_split_few_kernel(const SplitArgs a, uint32_t function_groups) {
+    constexpr bool SIGNS = EP == kSigns, KEYS = EP == kKeys || EP == kIdsKeys;
+    constexpr int NSPLIT = SIGNS ? 2 : 3, VW = 4 / FW, kRows = 32 * VW, kPlane = kRows * ROWB;
+    __shared__ __align__(16) char lds[NSPLIT * kPlane];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
+    const uint32_t wf = (blockIdx.x % function_groups * FW + wave % FW) * 32;
+    const uint64_t row0 = (uint64_t)(blockIdx.x / function_groups) * kRows;
+    const bool active = wf < a.k;  // whole wave
+
+    floatx4 coef[2 * KSTEPS];
+    if (active) {
+        const float *row = a.a + (size_t)(wf + lr) * SN + 8 * lh;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) {
+            coef[2 * s] = *reinterpret_cast<const floatx4 *>(row + 16 * s);
+            coef[2 * s + 1] = *reinterpret_cast<const floatx4 *>(row + 16 * s + 4);
+        }
+    }
+    // with the first loads: what the results need (read at the end, each is a trip to memory of its own)
+    floatx4 offset[4];
+    uint64_t weight[4];  // power of C of the place that a lane's four functions have in their table
+    if (active) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (EP != kProj && !SIGNS) offset[q] = *reinterpret_cast<const floatx4 *>(a.off + wf + 8 * q + 4 * lh);
+            if constexpr (KEYS) weight[q] = kKeyPowers.of[a.g / 4 - 1 - ((2 * q + lh) & (a.g / 4 - 1))];  // g: a power of two
+        }
+    }
+    {
+        const uint32_t piece = threadIdx.x & 31, first = threadIdx.x >> 5;
+        floatx4 raw[4 * VW];
+#pragma unroll
+        for (int q = 0; q < 4 * VW; ++q) {
+            uint64_t vec = row0 + first + 8 * q;
+            vec = vec < a.N ? vec : a.N - 1;
+            raw[q] = *reinterpret_cast<const floatx4 *>(a.data + vec * SN + piece * 4);
+        }
+#pragma unroll
+        for (int q = 0; q < 4 * VW; ++q) {
+            bf16x4 h[3];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                __bf16 x1, x2, x3;
+                split3(raw[q][e], x1, x2, x3);
+                h[0][e] = x1, h[1][e] = x2, h[2][e] = x3;
+            }
+#pragma unroll
+            for (int p = 0; p < NSPLIT; ++p)
+                *reinterpret_cast<bf16x4 *>(lds + p * kPlane + (first + 8 * q) * ROWB + piece * 8) = h[p];
+        }
+    }
+    __syncthreads();
+    if (!active) return;
+
+    const char *const mine = lds + (wave / FW * 32 + lr) * ROWB + lh * 16;
+    floatx16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KSTEPS; ++s) {
+        bf16x8 c[3], d[NSPLIT];
+#pragma unroll
+        for (int p = 0; p < NSPLIT; ++p) d[p] = *reinterpret_cast<const bf16x8 *>(mine + p * kPlane + s * 32);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            __bf16 x1, x2, x3;
+            split3(coef[2 * s + e / 4][e % 4], x1, x2, x3);
+            c[0][e] = x1, c[1][e] = x2, c[2][e] = x3;
+        }
+        auto product = [&](int pc, int pd) { acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c[pc], d[pd], acc, 0, 0, 0); };
+        if constexpr (NSPLIT == 3) {
+            product(2, 0);
+            product(1, 1);
+            product(0, 2);
+        }
+        product(1, 0);
+        product(0, 1);
+        product(0, 0);
+    }
+
+    const uint64_t vec = row0 + wave / FW * 32 + lr;
+    if constexpr (SIGNS) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) bits |= (acc[i] >= 0.f ? 1u : 0u) << (8 * (i / 4) + (i % 4));
+        bits <<= 4 * lh;
+        bits |= (uint32_t)__shfl_xor((int)bits, 32);
+        if (lh == 0 && vec < a.N) reinterpret_cast<uint32_t *>(a.out)[vec * (a.k / 32) + wf / 32] = bits;
+    } else {
+        uint64_t part[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uintx4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float p = acc[4 * q + e];
+                if constexpr (EP == kProj) v[e] = __float_as_uint(p);
+                else v[e] = (uint32_t)(int)floorf(POW2 ? fmaf(p, a.inv_w, offset[q][e] * a.inv_w) : (p + offset[q][e]) / a.w);
+            }
+            if constexpr (EP != kKeys)
+                if (vec < a.N) *reinterpret_cast<uintx4 *>(reinterpret_cast<uint32_t *>(a.out) + vec * a.k + wf + 8 * q + 4 * lh) = v;
+            if constexpr (KEYS) {
+                part[q] = (((v[0] * kKeyMultiplier + v[1]) * kKeyMultiplier + v[2]) * kKeyMultiplier + v[3]) * weight[q];
+            }
+        }
+        if constexpr (KEYS) {
+            uint64_t *const row = reinterpret_cast<uint64_t *>(EP == kIdsKeys ? a.out2 : a.out) + vec * (a.k / a.g) + wf / a.g;
+            if (a.g == 4) {  // uniform; table 2 q + l / 32
+                if (vec < a.N)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) row[2 * q + lh] = part[q];
+            } else {
+                // tables of 8, 16, 32 functions: 1, 2, 4 of the parts, in both lanes of a vector
+#pragma unroll
+                for (int q = 0; q < 4; ++q) part[q] += __shfl_xor(part[q], 32);
+                if (lh == 0 && vec < a.N) {
+                    if (a.g == 8) row[0] = part[0], row[1] = part[1], row[2] = part[2], row[3] = part[3];
+                    else if (a.g == 16) row[0] = part[0] + part[1], row[1] = part[2] + part[3];
+                    else row[0] = part[0] + part[1] + part[2] + part[3];
+                }
+            }
+        }
+    }
+}
+
 }  // namespace
 
 bool dense_split_supported(const lsh_params *p) {
@@ -561,6 +708,26 @@ int launch_dense_split(const lsh_params *p, int ep, const float *d_data, uint64_
     a.out2 = d_out2;
     int exp2 = 0;
     const bool pw = (ep != kIds && ep != kKeys && ep != kIdsKeys) || std::frexp(p->w, &exp2) == 0.5f;  // only ids and keys divide
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    // Blocks of 32 functions x 32 vectors, a wave each: up to one a SIMD, or two where the functions take more than one slice (their
+    // waves all split the same tiles there).  us, tiles / blocks, ids of 2048 functions: 32 vectors 10.2 / 6.0, 300 11.5 / 6.3,
+    // 1000 (2048 blocks) 12.0 / 9.4, 2000 13.0 / 14.9; of 512: 2000 11.2 / 6.5, 4000 11.8 / 9.3, 8000 13.0 / 14.8; of 128: 8000 8.7 / 6.6,
+    // 16000 9.0 / 9.2; of 64: 1000 7.2 / 6.3, 16000 8.3 / 7.0.
+    const uint64_t blocks = (N + 31) / 32 * (p->k / 32);
+    if (blocks <= (p->k >= 512 ? 2048 : 1024)) {
+        const int along = p->k >= 128 ? 4 : 2;
+        const uint32_t groups = (p->k + 32 * along - 1) / (32 * along);
+        const uint64_t vector_groups = (N + 128 / along - 1) / (128 / along);
+#define LSH_FEW_CASE(E_, W_) \
+    if (ep == E_ && pw == W_) { \
+        auto fn = along == 4 ? &dense_split_few_kernel<E_, W_, 4> : &dense_split_few_kernel<E_, W_, 2>; \
+        hipLaunchKernelGGL(fn, dim3((uint32_t)(vector_groups * groups)), dim3(256), 0, s, a, groups); \
+    }
+        LSH_FEW_CASE(kIds, true) LSH_FEW_CASE(kIds, false) LSH_FEW_CASE(kProj, true) LSH_FEW_CASE(kSigns, true)
+        LSH_FEW_CASE(kKeys, true) LSH_FEW_CASE(kKeys, false) LSH_FEW_CASE(kIdsKeys, true) LSH_FEW_CASE(kIdsKeys, false)
+#undef LSH_FEW_CASE
+        return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
+    }
     const uint32_t block_funcs = kFuncsPerBlock * (ep == kSigns ? 2 : 1);
     const uint32_t slices = (p->k + block_funcs - 1) / block_funcs;
     // one workgroup per CU (102 KB of LDS); every XCD needs a workgroup per slice of functions
@@ -568,7 +735,6 @@ int launch_dense_split(const lsh_params *p, int ep, const float *d_data, uint64_
     if (wgs < 8) wgs = 8;
     while (wgs / 8 < slices) wgs += 8;
     const uint32_t lds_bytes = kLdsBytes;  // two tiles, their level words, the waves' staging blocks
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 #define LSH_SPLIT_CASE(E_, W_) \
     if (ep == E_ && pw == W_) { \
         auto fn = &dense_split_kernel<E_, W_>; \

@@ -54,6 +54,31 @@ def test_few_vectors_equal_many(lsh, n, k, m, L, w):
                 assert torch.equal(ids, many["ids"][rows]) and torch.equal(keys, many["keys"][rows])
 
 
+@pytest.mark.parametrize("k,m,L,w", [(32, 30, 8, 4.0), (64, 128, 8, 3.0), (96, 32, 6, 2.0), (160, 32, 5, 0.7), (512, 32, 32, 512.0)])
+def test_few_vectors_of_128_dimensions_equal_many(lsh, k, m, L, w):
+    """A block of 32 functions x 32 vectors a wave: the bits of whole tiles, whose products of zero terms are skipped."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    N = 40000                      # beyond 1024 such blocks (2048 from 512 functions on)
+    data = torch.randn((N, 128), generator=g, device="cuda")
+    data[N // 2:] = (data[N // 2:] * 40).round()
+    with lsh.LshParams(128, k, m, w, 5) as p:
+        many = {"ids": lsh.hash_fastlsh(p, data), "proj": lsh.project_fastlsh(p, data), "signs": lsh.hash_signs(p, data),
+                "keys": lsh.hash_fastlsh_keys(p, data, L)}
+        for first, count in ((0, 1), (7, 31), (20000, 33), (19990, 64), (100, 1001), (23000, 2048)):
+            print(f"few vectors of 128: k={k} m={m} first={first} count={count}", flush=True)
+            part = data[first:first + count].clone()
+            rows = slice(first, first + count)
+            assert torch.equal(lsh.hash_fastlsh(p, part), many["ids"][rows])
+            assert torch.equal(lsh.project_fastlsh(p, part), many["proj"][rows])
+            assert torch.equal(lsh.hash_signs(p, part), many["signs"][rows])
+            assert torch.equal(lsh.hash_fastlsh_keys(p, part, L), many["keys"][rows])
+            ids, keys = lsh.hash_fastlsh_ids_keys(p, part, L)
+            assert torch.equal(ids, many["ids"][rows]) and torch.equal(keys, many["keys"][rows])
+            if m == 128:
+                assert torch.equal(lsh.hash_e2lsh(p, part), lsh.hash_e2lsh(p, data)[rows])
+
+
 _CAPTURED = """
 import sys
 import torch
