@@ -12,6 +12,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "liblsh.so")
 _lib = None
+_torch = None   # the module, once load_library() has run
 
 LSH_OK = 0
 SAMPLE_WITHOUT_REPLACEMENT = 0
@@ -50,7 +51,7 @@ def library_path():
 
 def load_library():
     """Loads liblsh.so (built by paper_2309_15479_amd/build.py); raises if it is missing."""
-    global _lib
+    global _lib, _torch
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -58,7 +59,8 @@ def load_library():
             f"{_LIB_PATH} not found: build it with `python -m paper_2309_15479_amd.build` "
             "(there is no fallback implementation)")
     try:
-        import torch  # noqa: F401  -- so that liblsh binds to the HIP runtime torch already loaded
+        import torch  # so that liblsh binds to the HIP runtime torch already loaded
+        _torch = torch
     except ImportError:
         pass
     lib = ctypes.CDLL(_LIB_PATH)
@@ -225,25 +227,34 @@ class LshParams:
         return dict(n=n.value, k=k.value, m=m.value, flags=fl.value, w=w.value, seed=seed.value)
 
 
+# What a call costs the host, us, where the launch itself takes 2.7: torch.cuda.current_stream() 2.8 (it makes a Stream
+# object; the raw handle 0.2), torch.empty 1.7 (empty_strided 1.3), an `import torch` in each of five functions 1.3.
+# hash_fastlsh of 256 vectors 9.3 -> 6.1, as much as its kernel takes; a request of three calls (hash, probe, nearest) 31 -> 22.
 def _stream(stream):
     if stream is not None:
         return ctypes.c_void_p(int(stream))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _torch is None:
+        load_library()
+    c = _torch._C
+    return ctypes.c_void_p(c._cuda_getCurrentRawStream(c._cuda_getDevice()))
 
 
 def _dev_in(t, dtype, cols):
-    import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+    if _torch is None:
+        load_library()
+    if not (isinstance(t, _torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
             and t.dim() == 2 and t.shape[1] == cols):
         raise ValueError(f"expected a contiguous CUDA tensor [N,{cols}] of {dtype}")
     return t
 
 
+def _new(rows, cols, dtype, device):
+    return _torch.empty_strided((rows, cols), (cols, 1), dtype=dtype, device=device)
+
+
 def _out(data, N, cols, dtype, out):
-    import torch
     if out is None:
-        return torch.empty((N, cols), dtype=dtype, device=data.device)
+        return _new(N, cols, dtype, data.device)
     _dev_in(out, dtype, cols)
     if out.shape[0] != N:
         raise ValueError("output has the wrong number of rows")
@@ -251,51 +262,45 @@ def _out(data, N, cols, dtype, out):
 
 
 def _hash_call(name, params, data, cols, dtype, out, stream):
-    import torch
-    _dev_in(data, torch.float32, params.n)
+    _dev_in(data, _torch.float32, params.n)
     N = data.shape[0]
     out = _out(data, N, cols, dtype, out)
-    fn = getattr(load_library(), name)
-    _check(fn(params.handle, data.data_ptr(), N, out.data_ptr(), _stream(stream)), name)
+    status = getattr(_lib, name)(params.handle, data.data_ptr(), N, out.data_ptr(), _stream(stream))
+    if status != LSH_OK:
+        raise LshError(status, name)
     return out
 
 
 def hash_fastlsh(params, data, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_hash_fastlsh", params, data, params.k, torch.int32, out, stream)
+    return _hash_call("lsh_hash_fastlsh", params, data, params.k, _torch.int32, out, stream)
 
 
 def hash_e2lsh(params, data, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_hash_e2lsh", params, data, params.k, torch.int32, out, stream)
+    return _hash_call("lsh_hash_e2lsh", params, data, params.k, _torch.int32, out, stream)
 
 
 def hash_signs(params, data, out=None, stream=None):
     """Packed sign bits as int64 words [N, ceil(k/64)] (bit patterns of the uint64 words)."""
-    import torch
-    return _hash_call("lsh_hash_signs", params, data, (params.k + 63) // 64, torch.int64, out, stream)
+    return _hash_call("lsh_hash_signs", params, data, (params.k + 63) // 64, _torch.int64, out, stream)
 
 
 def project_fastlsh(params, data, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_project_fastlsh", params, data, params.k, torch.float32, out, stream)
+    return _hash_call("lsh_project_fastlsh", params, data, params.k, _torch.float32, out, stream)
 
 
 def project_e2lsh(params, data, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_project_e2lsh", params, data, params.k, torch.float32, out, stream)
+    return _hash_call("lsh_project_e2lsh", params, data, params.k, _torch.float32, out, stream)
 
 
 def mips_kappa(params, data, out=None, accumulate=False, stream=None):
     """kappa~_l^2 = max_i ||S_l(v_i)||^2, float32 [L]; accumulate=True only raises what `out` holds."""
-    import torch
-    _dev_in(data, torch.float32, params.n)
+    _dev_in(data, _torch.float32, params.n)
     L = params.shared_tables()
     if out is None:
         if accumulate:
             raise ValueError("accumulate needs the array to raise")
-        out = torch.empty(L, dtype=torch.float32, device=data.device)
-    if not (out.is_cuda and out.dtype == torch.float32 and out.is_contiguous() and out.numel() == L):
+        out = _torch.empty(L, dtype=_torch.float32, device=data.device)
+    if not (out.is_cuda and out.dtype == _torch.float32 and out.is_contiguous() and out.numel() == L):
         raise ValueError(f"expected a contiguous CUDA float32 tensor of {L} elements")
     _check(load_library().lsh_mips_kappa(params.handle, data.data_ptr(), data.shape[0], int(bool(accumulate)),
                                          out.data_ptr(), _stream(stream)), "lsh_mips_kappa")
@@ -303,9 +308,8 @@ def mips_kappa(params, data, out=None, accumulate=False, stream=None):
 
 
 def _mips_data_call(name, params, data, kappa2, dtype, out, stream):
-    import torch
-    _dev_in(data, torch.float32, params.n)
-    if not (kappa2.is_cuda and kappa2.dtype == torch.float32 and kappa2.is_contiguous()
+    _dev_in(data, _torch.float32, params.n)
+    if not (kappa2.is_cuda and kappa2.dtype == _torch.float32 and kappa2.is_contiguous()
             and kappa2.numel() == params.shared_tables()):
         raise ValueError("kappa2: expected the float32 CUDA tensor [L] of mips_kappa")
     N = data.shape[0]
@@ -316,41 +320,35 @@ def _mips_data_call(name, params, data, kappa2, dtype, out, stream):
 
 
 def hash_mips_data(params, data, kappa2, out=None, stream=None):
-    import torch
-    return _mips_data_call("lsh_hash_mips_data", params, data, kappa2, torch.int32, out, stream)
+    return _mips_data_call("lsh_hash_mips_data", params, data, kappa2, _torch.int32, out, stream)
 
 
 def project_mips_data(params, data, kappa2, out=None, stream=None):
-    import torch
-    return _mips_data_call("lsh_project_mips_data", params, data, kappa2, torch.float32, out, stream)
+    return _mips_data_call("lsh_project_mips_data", params, data, kappa2, _torch.float32, out, stream)
 
 
 def hash_mips_query(params, queries, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_hash_mips_query", params, queries, params.k, torch.int32, out, stream)
+    return _hash_call("lsh_hash_mips_query", params, queries, params.k, _torch.int32, out, stream)
 
 
 def project_mips_query(params, queries, out=None, stream=None):
-    import torch
-    return _hash_call("lsh_project_mips_query", params, queries, params.k, torch.float32, out, stream)
+    return _hash_call("lsh_project_mips_query", params, queries, params.k, _torch.float32, out, stream)
 
 
 def pack_keys(params, buckets, L, out=None, stream=None):
     """64-bit keys as int64 [N, L] (bit patterns of the uint64 keys)."""
-    import torch
-    _dev_in(buckets, torch.int32, params.k)
+    _dev_in(buckets, _torch.int32, params.k)
     N = buckets.shape[0]
-    out = _out(buckets, N, L, torch.int64, out)
+    out = _out(buckets, N, L, _torch.int64, out)
     _check(load_library().lsh_pack_keys(params.handle, buckets.data_ptr(), N, L, out.data_ptr(),
                                         _stream(stream)), "lsh_pack_keys")
     return out
 
 
 def hash_fastlsh_keys(params, data, L, out=None, stream=None):
-    import torch
-    _dev_in(data, torch.float32, params.n)
+    _dev_in(data, _torch.float32, params.n)
     N = data.shape[0]
-    out = _out(data, N, L, torch.int64, out)
+    out = _out(data, N, L, _torch.int64, out)
     _check(load_library().lsh_hash_fastlsh_keys(params.handle, data.data_ptr(), N, L, out.data_ptr(),
                                                 _stream(stream)), "lsh_hash_fastlsh_keys")
     return out
@@ -358,11 +356,10 @@ def hash_fastlsh_keys(params, data, L, out=None, stream=None):
 
 def hash_fastlsh_ids_keys(params, data, L, out_ids=None, out_keys=None, stream=None):
     """Bucket ids [N, k] (int32) and compound keys [N, L] (uint64 bit patterns in int64) in one call."""
-    import torch
-    _dev_in(data, torch.float32, params.n)
+    _dev_in(data, _torch.float32, params.n)
     N = data.shape[0]
-    out_ids = _out(data, N, params.k, torch.int32, out_ids)
-    out_keys = _out(data, N, L, torch.int64, out_keys)
+    out_ids = _out(data, N, params.k, _torch.int32, out_ids)
+    out_keys = _out(data, N, L, _torch.int64, out_keys)
     _check(load_library().lsh_hash_fastlsh_ids_keys(params.handle, data.data_ptr(), N, L, out_ids.data_ptr(),
                                                     out_keys.data_ptr(), _stream(stream)), "lsh_hash_fastlsh_ids_keys")
     return out_ids, out_keys
@@ -408,11 +405,10 @@ class LshIndex:
 
     def probe(self, qkeys, stream=None):
         """Bucket of every (query, table): (start [Q, L], count [Q, L]) int32 tensors (uint32 bits)."""
-        import torch
-        assert qkeys.is_cuda and qkeys.dtype == torch.int64 and qkeys.is_contiguous() and qkeys.shape[1] == self.L
+        assert qkeys.is_cuda and qkeys.dtype == _torch.int64 and qkeys.is_contiguous() and qkeys.shape[1] == self.L
         Q = qkeys.shape[0]
-        start = torch.empty((Q, self.L), dtype=torch.int32, device=qkeys.device)
-        count = torch.empty((Q, self.L), dtype=torch.int32, device=qkeys.device)
+        start = _new(Q, self.L, _torch.int32, qkeys.device)
+        count = _new(Q, self.L, _torch.int32, qkeys.device)
         _check(load_library().lsh_index_probe(self.handle, qkeys.data_ptr(), Q, start.data_ptr(), count.data_ptr(),
                                               _stream(stream)), "lsh_index_probe")
         return start, count
@@ -443,13 +439,13 @@ class LshIndex:
         return self._best("lsh_index_nearest", data, queries, start, count, max_candidates, stream)
 
     def _best(self, name, data, queries, start, count, max_candidates, stream):
-        import torch
-        assert data.is_cuda and data.dtype == torch.float32 and data.is_contiguous() and data.shape[0] == self.N
-        assert queries.is_cuda and queries.dtype == torch.float32 and queries.is_contiguous()
+        assert data.is_cuda and data.dtype == _torch.float32 and data.is_contiguous() and data.shape[0] == self.N
+        assert queries.is_cuda and queries.dtype == _torch.float32 and queries.is_contiguous()
         Q, n = queries.shape
         assert data.shape[1] == n and start.shape == (Q, self.L)
-        best = torch.empty(Q, dtype=torch.int32, device=data.device)
-        dist = torch.empty(Q, dtype=torch.float32, device=data.device)
+        device = data.device
+        best = _torch.empty_strided((Q,), (1,), dtype=_torch.int32, device=device)
+        dist = _torch.empty_strided((Q,), (1,), dtype=_torch.float32, device=device)
         _check(getattr(load_library(), name)(self.handle, data.data_ptr(), queries.data_ptr(), n,
                                              start.data_ptr(), count.data_ptr(), Q, max_candidates,
                                              best.data_ptr(), dist.data_ptr(), _stream(stream)), name)
