@@ -313,6 +313,153 @@ __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledA
     }
 }
 
+// Few vectors.  The kernel above takes as long for one tile as its stages take one after the other: sixteen barriers and
+// what is between them at n = 4096, on as many CUs as the tile has sets of functions.  Here a workgroup brings four
+// vectors in whole, all loads in flight at once and one barrier behind them, and its waves then work through the
+// lists of a set of 64 functions each, without another one; the same lists in the same order, so the same
+// sums.  An entry names a slot of the ring: the range it means is the one among those readable in its stage, s .. s + 6, that has the slot.
+// [coordinate][4 vectors] floats of LDS, a tile's stages of 256 coordinates: up to kFewStages.
+constexpr uint32_t kFewStages = 160 * 1024 / (kC * 16), kFewAhead = 8;
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+
+template <int EP, bool VEC>
+__global__ __launch_bounds__(512) void ranged_few_kernel(const SampledArgs a, const uint32_t *__restrict__ barriers,
+                                                         const uint2 *__restrict__ streams, uint32_t groups,
+                                                         uint32_t qpf_log2) {
+    extern __shared__ __align__(16) char lds[];
+    const uint32_t waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint64_t row0 = (uint64_t)(blockIdx.x / groups) * 4;
+    const uint32_t set = (blockIdx.x % groups) * waves + wave;  // functions 64 set .. 64 set + 63
+    const bool active = set * 64 < a.k;
+
+    // the lists of this wave: set f of stream (y, cw), quads of entries block after block
+    const uint32_t y = set / (kCW * a.fpt), f = set / kCW % a.fpt, cw = set % kCW;
+    const uint32_t *const bar = barriers + (size_t)y * a.bar_stride;
+    const uint32_t block_quads = a.fpt << qpf_log2, block_words = block_quads * 64 * 6;
+    uint32_t quads = 0;
+    const uint32_t *lists = nullptr;
+    if (active) {
+        const uint2 si = streams[y * kCW + cw];
+        lists = reinterpret_cast<const uint32_t *>(a.triples) + (size_t)si.x * block_words;
+        quads = si.y << qpf_log2;
+    }
+    uint4 coef[kFewAhead];
+    uint2 slot[kFewAhead];
+    auto request = [&](uint32_t q, int d) __attribute__((always_inline)) {
+        q = min(q, quads - 1);
+        const uint32_t *const block = lists + (size_t)(q >> qpf_log2) * block_words;
+        const uint32_t of_block = (f << qpf_log2) + (q & ((1u << qpf_log2) - 1));  // uniform
+        coef[d] = *reinterpret_cast<const uint4 *>(block + of_block * 256 + lane * 4);
+        slot[d] = *reinterpret_cast<const uint2 *>(block + block_quads * 256 + of_block * 128 + lane * 2);
+    };
+    const uint32_t j = set * 64 + lane, blocks = quads >> qpf_log2;
+    float bias = 0.f;
+    uint64_t key_pow = 1;
+    uint32_t counts = 0;  // of barriers, of block `lane` of the next 64
+    if (active) {
+        counts = bar[min(lane, blocks - 1)];
+#pragma unroll
+        for (uint32_t d = 0; d < kFewAhead; ++d) request(d, d);
+        bias = a.off[j];
+    }
+    {
+        const float *const rows = a.data + row0 * a.n;
+        const uint32_t rows_valid = (uint32_t)min((uint64_t)4, a.N - row0), pieces = a.stages * kPieces;
+        constexpr uint32_t kTogether = 16;
+        for (uint32_t p0 = wave; p0 < pieces; p0 += waves * kTogether) {
+            float x[kTogether][4];
+#pragma unroll
+            for (uint32_t u = 0; u < kTogether; ++u) {
+                const uint32_t p = p0 + u * waves;
+                if (p < pieces) load_raw<VEC>(rows, rows_valid, a.n, 0, p * 64, a.n, lane, x[u]);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kTogether; ++u) {
+                const uint32_t p = p0 + u * waves;
+                if (p < pieces) {
+                    slot_from_raw<VEC>(x[u]);
+                    const bool inside = p * 64 + lane < a.n;
+                    const floatx4 v = {inside ? x[u][0] : 0.f, inside ? x[u][1] : 0.f, inside ? x[u][2] : 0.f,
+                                       inside ? x[u][3] : 0.f};
+                    *reinterpret_cast<floatx4 *>(lds + (p * 64 + lane) * 16) = v;
+                }
+            }
+        }
+    }
+    if (EP == (int)Epilogue::Keys || EP == (int)Epilogue::IdsKeys) {
+        uint32_t t = j % a.g;
+        if (a.g >= 4) t |= 3;  // as above
+        for (uint32_t e = 0; e + 1 + t < a.g; ++e) key_pow *= kKeyMultiplier;
+    }
+    __syncthreads();
+    if (!active) return;
+
+    float acc[1][4] = {};
+    floatx4 x[2][4];
+    // Lane l: the stage of block l of the 64 at hand (a scalar load per block is a wait per block).
+    uint32_t stages = 0, stage = 0;
+    auto read_quad = [&](uint32_t q, int d) __attribute__((always_inline)) {
+        const uint32_t block = q >> qpf_log2;
+        if ((q & ((64u << qpf_log2) - 1)) == 0) {
+#pragma unroll
+            for (uint32_t step = 1; step < 64; step <<= 1) {
+                const uint32_t up = __shfl_up(counts, step);
+                if (lane >= step) counts += up;
+            }
+            stages = stage + counts;
+            stage = __builtin_amdgcn_readlane(stages, 63);
+            counts = bar[min(block + 64 + lane, blocks - 1)];
+        }
+        // 1024 x (range modulo 8) + coordinate -> 256 x range + coordinate, two numbers at a time.  (Padding entries name
+        // the stage's own slot: LDS holds zeros for stages without a range.)
+        const uint32_t now = __builtin_amdgcn_readlane(stages, block & 63);
+        const uint32_t pair[2] = {slot[d].x, slot[d].y};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const ushortx2 since = __builtin_bit_cast(ushortx2, pair[h]) - (unsigned short)(now << 10);
+            const ushortx2 far = (since & (unsigned short)0x1C00) >> (unsigned short)2;
+            const uint32_t at = __builtin_bit_cast(uint32_t, (since & (unsigned short)0xFF) + far + (unsigned short)(now << 8));
+            x[d & 1][2 * h] = *reinterpret_cast<const floatx4 *>(lds + ((at & 0xFFFF) << 4));
+            x[d & 1][2 * h + 1] = *reinterpret_cast<const floatx4 *>(lds + (at >> 16 << 4));
+        }
+    };
+    read_quad(0, 0);
+    // No test around a request: the compiler's count of those in flight is then exact (with tests it waited for the newest one,
+    // a trip to L2 a quad).  Quads beyond the last one are the last one again, times zero.
+    auto eight = [&](auto last_tag, uint32_t q0) __attribute__((always_inline)) {
+#pragma unroll
+        for (uint32_t d = 0; d < kFewAhead; ++d) {
+            const uint32_t q = q0 + d;
+            // the reads of a quad go out ahead of the multiply-adds of the quad before
+            __builtin_amdgcn_sched_barrier(0);
+            read_quad(q + 1, (d + 1) % kFewAhead);
+            __builtin_amdgcn_sched_barrier(0);
+            const bool real = !decltype(last_tag)::value || q < quads;
+            const float c[4] = {real ? __uint_as_float(coef[d].x) : 0.f, real ? __uint_as_float(coef[d].y) : 0.f,
+                                real ? __uint_as_float(coef[d].z) : 0.f, real ? __uint_as_float(coef[d].w) : 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[0][r] = fmaf(c[e], x[d & 1][e][r], acc[0][r]);
+            if constexpr (!decltype(last_tag)::value) request(q + kFewAhead, d);
+        }
+    };
+    uint32_t q0 = 0;
+    for (; q0 + kFewAhead < quads; q0 += kFewAhead) eight(std::false_type{}, q0);
+    eight(std::true_type{}, q0);
+    finish<4, 1, EP>(a, row0, j, acc, bias, key_pow);
+}
+
+template <int EP>
+int launch_few(const SampledArgs &a, uint32_t qpf, uint32_t waves, hipStream_t stream) {
+    const uint32_t lds_bytes = a.stages * kC * 16, groups = ((a.k + 63) / 64 + waves - 1) / waves;
+    auto fn = (a.n & 3) == 0 ? &ranged_few_kernel<EP, true> : &ranged_few_kernel<EP, false>;
+    if (ensure_lds_limit(reinterpret_cast<const void *>(fn), lds_bytes) != LSH_OK) return LSH_ERR_HIP;
+    hipLaunchKernelGGL(fn, dim3((uint32_t)((a.N + 3) / 4) * groups), dim3(waves * 64), lds_bytes, stream, a, a.list_len, a.stream,
+                       groups, qpf == 4 ? 2u : qpf == 2 ? 1u : 0u);
+    return hipGetLastError() == hipSuccess ? LSH_OK : LSH_ERR_HIP;
+}
+
 template <typename Kernel>
 int launch(Kernel fn, const SampledArgs &args, dim3 grid, hipStream_t stream) {
     if (ensure_lds_limit(reinterpret_cast<const void *>(fn), kLdsBytes) != LSH_OK) return LSH_ERR_HIP;
@@ -464,6 +611,21 @@ int launch_ranged(const lsh_params *p, Epilogue ep, const float *d_data, uint64_
     const bool split = pl.fpt > 1 && ntiles * pl.kblocks * pl.fpt <= (uint64_t)p->num_cus;
     const dim3 grid((uint32_t)gx, pl.kblocks, split ? pl.fpt : 1);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    // Fewer still: four vectors a workgroup, while every workgroup has a CU, with four sets of functions each, or eight.  us, one of
+    // the sets at a time / four / eight: 100 vectors of 4096 dimensions, 2048 functions, m = 64 17.8 / 11.5 / 12.0, m = 256
+    // 35 / 21 / 23, m = 1024 97 / 55 / 63; 200 of them at m = 64 18.5 / 15.7 / 12.4, 400 (beyond) 19.0 / 28 / 24; 300 vectors of 8192
+    // dimensions, 1024 functions, m = 128 30 / 34 / 18.
+    const uint64_t few_tiles = (N + 3) / 4, real_sets = (p->k + 63) / 64, cus = (uint64_t)p->num_cus;
+    const uint32_t few_waves = few_tiles * ((real_sets + 3) / 4) <= cus ? 4 : 8;
+    if (pl.stages <= kFewStages && few_tiles * ((real_sets + few_waves - 1) / few_waves) <= cus) {
+        switch (ep) {
+            case Epilogue::Ids: return launch_few<(int)Epilogue::Ids>(a, pl.qpf, few_waves, s);
+            case Epilogue::Proj: return launch_few<(int)Epilogue::Proj>(a, pl.qpf, few_waves, s);
+            case Epilogue::Signs: return launch_few<(int)Epilogue::Signs>(a, pl.qpf, few_waves, s);
+            case Epilogue::IdsKeys: return launch_few<(int)Epilogue::IdsKeys>(a, pl.qpf, few_waves, s);
+            default: return launch_few<(int)Epilogue::Keys>(a, pl.qpf, few_waves, s);
+        }
+    }
 #define LSH_RANGED_CASE(F_, Q_, EP_) \
     case F_ * 8 + Q_: \
         if (split) return launch(&sampled_ranged_kernel<F_, Q_, EP_, (F_ > 1)>, a, grid, s); \

@@ -26,6 +26,8 @@ def lsh():
     (2100, 1024, 100, 64, 4.0),    # two, and blocks of two quads
     (2500, 4000, 70, 250, 4.0),    # two workgroups along the functions already
     (4096, 512, 64, 32, 8.0),      # one: nothing to deal out
+    (8200, 320, 100, 40, 4.0),     # forty stages: whole vectors of four just fit LDS
+    (10500, 200, 70, 25, 4.0),     # forty-eight: they do not
     (960, 1024, 128, 64, 1.0),     # whole-vector tiles of eight sub-tiles
     (403, 250, 100, 125, 0.75),    # the same, nothing a multiple of anything
     (1500, 700, 100, 175, 2.0),    # tiles of four sub-tiles
