@@ -9,7 +9,7 @@
 // and the multiply-adds move from the vector ALU to the matrix cores.
 //
 // Mapping.  A workgroup of 16 waves walks tiles of `rows` vectors (persistent, double-buffered
-// in LDS as [vector][n + 4] floats, next tile prefetched HBM -> registers during the
+// in LDS as [vector][n + 2] floats, next tile prefetched HBM -> registers during the
 // contraction).  A wave owns RB blocks of 16 consecutive functions (a block lies inside one
 // table) and keeps their coefficients in registers for the whole launch.  Per block and 16
 // vectors it issues KS = ceil(m / 4) `v_mfma_f32_16x16x4_f32`:
@@ -17,10 +17,13 @@
 //   column operand B[kq][c] = v_{vector c}[S_l[4*kk + kq]]         lane = c + 16*kq   (one 4-byte LDS read)
 //   result         D[4*q + r][c] in register r of lane c + 16*q: four consecutive functions
 //                  of one vector per lane, so ids leave as 16-byte stores.
-// The tile's row stride n + 4 puts the 16 vectors of a read 4 banks apart when n is a multiple
-// of 64 (conflict-free for one coordinate; two coordinates of a step collide when they are
-// equal modulo 4, which the host avoids by choosing which samples share a step).  The 4 pad
-// floats of a row are kept zero: samples beyond m read them.
+// A 4-byte read is served 32 lanes at a time from 32 banks (measured: 0.9 ns a wave's read and CU without conflicts, 1.7 with
+// pairs of lanes in one bank, on words 64 apart or 32).  The tile's row stride n + 2, twice an odd number, puts the 16 vectors
+// of a step's coordinate into all banks of one parity, and the host deals the samples so that lane groups 0 and 1, and 2 and
+// 3, read coordinates of different parity.  (With n + 4 vectors c and c + 8 shared a bank whatever the coordinates.)
+// Tile rows begin on 8 bytes: their pieces are written as two halves by one instruction.  The 2 pad floats of a row are
+// kept zero: samples beyond m read the first.  kappa~ of 3e5 x 960 (m = 128, 64 tables) 429 -> 355 us, of 4e5 x 300 (m = 64, 32)
+// 413 -> 158; keys of those 494 -> 406, ids 513 -> 455.
 //
 // Maximum inner product search (appendix): the transformed vectors are
 // P~(v) = (sqrt(kappa~^2 - ||S(v)||^2), S(v)) for data and Q~(u) = (0, S(u) / ||S(u)||) for
@@ -45,6 +48,7 @@ constexpr uint32_t kLdsBudget = 158u * 1024u;
 constexpr int kPre = 5;           // float4 prefetch registers per lane: rows * n / 4 <= kPre * lanes
 
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float4on8 __attribute__((ext_vector_type(4), aligned(8)));
 
 struct SharedArgs {
     const float *data;  // [N][n]
@@ -69,7 +73,8 @@ struct SharedArgs {
 
 // EP: 0 bucket ids, 1 raw projections, 2 one 64-bit key per table (Sec. 3.2; the fold of pack_kernel.hip),
 //     3 kappa~_l^2 (atomic max into out, float [L]), 4 maximum-inner-product data hash, 5 query hash
-// GEOM: the tile geometry of n = 128 (128-vector tiles, row stride 132) as compile-time
+// GEOM: the tile geometry of n = 128 (128-vector tiles, row stride 130; ids and projections, which are bound by their
+// stores and not by the reads, 132 with whole 16-byte writes: 613 -> 606 us at 1e6 x 512) as compile-time
 // constants: the loop over the tile's vector blocks is then unrolled and a block's LDS offset is
 // an immediate of the read instead of a vector add per read (a sixth of the kernel's
 // vector-ALU instructions, which do not overlap with its MFMAs).
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
     // coefficients in registers, and so that 16-vector tiles are possible)
     constexpr int VB = (RB >= 4 || KS >= 32) ? 1 : 2;
     extern __shared__ __align__(16) float tile[];  // 2 x [rows][stride]
-    const uint32_t n = GEOM ? 128u : a.n, n4 = n >> 2, rows = GEOM ? 128u : a.rows, stride = GEOM ? 132u : a.stride;
+    const uint32_t n = GEOM ? 128u : a.n, n4 = n >> 2, rows = GEOM ? 128u : a.rows, stride = GEOM ? (EP < 2 ? 132u : 130u) : a.stride;
     const uint32_t lane = threadIdx.x & 63, c16 = lane & 15, q = lane >> 4;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t block0 = (blockIdx.y * kWaves + wave) * RB;
@@ -136,7 +141,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
         if constexpr (KAPPA) kmax[e] = 0.f;
     }
     // the pad floats of every tile row (both buffers) stay zero for the whole launch
-    for (uint32_t i = threadIdx.x; i < 2 * rows * 4; i += kLanes) tile[(i >> 2) * stride + n + (i & 3)] = 0.f;
+    for (uint32_t i = threadIdx.x; i < 2 * rows * 2; i += kLanes) tile[(i >> 1) * stride + n + (i & 1)] = 0.f;
 
     // tile transfer: element e of the tile's float4 sequence = (vector e / n4, coordinates
     // 4 * (e % n4) ..); the slot arithmetic is redone at every use (it is cheap, and kept in
@@ -163,7 +168,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void shared_kernel(const SharedArgs 
         for (int f = 0; f < kPre; ++f) {
             const uint32_t e = tid + f * kLanes;
             const uint32_t r = __umulhi(e, a.n4_magic), c4 = e - r * n4;
-            if (r < rows) *reinterpret_cast<float4 *>(buf + r * stride + c4 * 4) = pre[f];
+            if (r < rows) *reinterpret_cast<float4on8 *>(buf + r * stride + c4 * 4) = float4on8{pre[f].x, pre[f].y, pre[f].z, pre[f].w};
         }
     };
 
@@ -443,7 +448,7 @@ SharedPlan plan_shared(uint32_t n, uint32_t k, uint32_t m, uint32_t L) {
     if (!L || k % L || (n & 3) || m > 128 || m == n) return pl;
     const uint32_t g = k / L;
     if (g & 3) return pl;
-    pl.stride = n + 4;
+    pl.stride = n + 2;
     pl.g = g;
     pl.ksteps = m <= 32 ? 8 : m <= 64 ? 16 : 32;
     pl.blocks_per_table = (g + 15) / 16;
@@ -454,7 +459,7 @@ SharedPlan plan_shared(uint32_t n, uint32_t k, uint32_t m, uint32_t L) {
     struct Shape { uint32_t waves, rows, per_cu; };
     for (const Shape sh : {Shape{16, 128, 1}, Shape{16, 64, 1}, Shape{16, 32, 1}, Shape{16, 16, 1}}) {
         if (sh.rows == 16 && pl.ksteps != 32) continue;  // only the 32-step kernel walks single 16-vector blocks
-        if (2ull * sh.rows * pl.stride * 4 * sh.per_cu > kLdsBudget) continue;
+        if (2ull * sh.rows * (n + 4) * 4 * sh.per_cu > kLdsBudget) continue;
         if ((uint64_t)sh.rows * (n / 4) > (uint64_t)kPre * sh.waves * 64) continue;
         pl.waves = sh.waves;
         pl.rows = sh.rows;
@@ -466,7 +471,7 @@ SharedPlan plan_shared(uint32_t n, uint32_t k, uint32_t m, uint32_t L) {
     pl.rb = 1;
     while (pl.rb < rb_max && pl.waves * pl.rb < pl.nblocks) pl.rb *= 2;
     pl.kblocks = (pl.nblocks + pl.waves * pl.rb - 1) / (pl.waves * pl.rb);
-    pl.lds_bytes = 2 * pl.rows * pl.stride * 4;
+    pl.lds_bytes = 2 * pl.rows * (n + 4) * 4;
     // whole-line stores when a wave's two blocks are 32 consecutive functions and every block is full
     pl.staged = pl.rb == 2 && g % 16 == 0 && pl.nblocks % 2 == 0;
     pl.supported = true;
@@ -483,10 +488,10 @@ void build_shared_tables(const lsh_params *p, std::vector<float> &coef, std::vec
     offset.assign((size_t)blocks * 16, 0.f);
     extra.assign((size_t)blocks * 64, 0.f);
     // Which sample sits in which slot (step kk, lane group kq) is free: a projection is a sum.
-    // The 64 lanes of a column-operand read address banks 4 * vector + coordinate (mod 64), so
-    // the four coordinates of a step hit distinct banks iff they differ modulo 4.  Per table,
+    // Lane groups 0 and 1, and 2 and 3, of a read hit distinct banks iff their coordinates differ in parity.  Per table,
     // deal the samples (and the pads, which read coordinate n = 0 mod 4) to the steps from the
-    // residue classes with the most left, one per class where four classes are left.
+    // residue classes modulo 4 with the most left, one per class where four classes are left, and place those of
+    // a step even, odd, even, odd.
     constexpr uint32_t kPad = 0xFFFFFFFFu;
     std::vector<uint32_t> slot_sample((size_t)(pl.nblocks / pl.blocks_per_table) * ks * 4, kPad);
     for (uint32_t table = 0; table < pl.nblocks / pl.blocks_per_table; ++table) {
@@ -494,7 +499,7 @@ void build_shared_tables(const lsh_params *p, std::vector<float> &coef, std::vec
         for (uint32_t smp = p->m; smp-- > 0;) cls[p->idx[(size_t)table * pl.g * p->m + smp] & 3].push_back(smp);
         for (uint32_t pad = p->m; pad < ks * 4; ++pad) cls[0].insert(cls[0].begin(), kPad);  // pads leave last
         for (uint32_t kk = 0; kk < ks; ++kk) {
-            uint32_t taken[4] = {0, 0, 0, 0};
+            uint32_t taken[4] = {0, 0, 0, 0}, free_slots[2][2] = {{0, 2}, {1, 3}}, used[2] = {0, 0};
             for (uint32_t kq = 0; kq < 4; ++kq) {
                 // the class with the most left among those not used in this step, else the fullest
                 int best = -1;
@@ -503,7 +508,9 @@ void build_shared_tables(const lsh_params *p, std::vector<float> &coef, std::vec
                         if (!cls[c].empty() && (pass == 1 || !taken[c]) &&
                             (best < 0 || cls[c].size() > cls[best].size()))
                             best = c;
-                slot_sample[((size_t)table * ks + kk) * 4 + kq] = cls[best].back();
+                uint32_t parity = best & 1;
+                if (used[parity] == 2) parity ^= 1;  // three of one parity
+                slot_sample[((size_t)table * ks + kk) * 4 + free_slots[parity][used[parity]++]] = cls[best].back();
                 cls[best].pop_back();
                 taken[best] = 1;
             }
@@ -594,7 +601,7 @@ int launch_shared(const lsh_params *p, int ep, const float *d_data, uint64_t N, 
     dim3 grid((uint32_t)gx, kblocks);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // the instances with the geometry of n = 128 built in are for lists of up to 64 samples; longer ones take the general one
-    const bool geom = p->n == 128 && pl.rows == 128 && pl.stride == 132 && pl.ksteps <= 16;
+    const bool geom = p->n == 128 && pl.rows == 128 && pl.stride == 130 && pl.ksteps <= 16;
     if (ep == 3 && pl.ksteps == 32 && pl.waves == 16 && !geom) {
         if (tables_per_wave == 2) return launch(&shared_kernel<32, 2, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
         if (tables_per_wave == 4) return launch(&shared_kernel<32, 4, 16, 3, false>, pl.lds_bytes, a, grid, 1024, s);
