@@ -160,7 +160,7 @@ double walk_shared_ranged(const lsh_params *p, const std::vector<double> &v) {
                                 const float c = cb[(size_t)(e / 4 * 4) * 64 + l * 4 + e % 4];
                                 const uint32_t off = (ob[(l / 16) * OW + e / 2] >> (16 * (e & 1))) & 0xFFFFu;
                                 uint32_t coord = p->n;  // beyond the row: a zero float
-                                if (off % 4 || off / 4 >= row + 4) return INFINITY;
+                                if (off % 4 || off / 4 >= row + 2) return INFINITY;
                                 if (off / 4 < row) {
                                     const uint32_t slot = off / 4 / kWindowCoords;
                                     const uint32_t r = s + (slot + kWindowSlots - s % kWindowSlots) % kWindowSlots;

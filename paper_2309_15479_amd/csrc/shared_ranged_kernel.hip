@@ -9,7 +9,7 @@
 // k * m, and the multiply-adds leave the vector ALU.
 //
 // A tile is 16 vectors.  LDS holds a ring of eight ranges of 256 coordinates of every vector,
-// row-major ([vector][8 x 256 + 4] floats: coordinate c of a vector always sits at float
+// row-major ([vector][8 x 256 + 2] floats: coordinate c of a vector always sits at float
 // c % 2048 of its row); as in ranged_kernel.hip a workgroup is 8 contracting waves plus 4
 // loading waves, and a tile passes in stages: in stage s the loading waves write range s + 7
 // while the contracting waves may read the ranges s .. s + 6.  A sample of range r can therefore
@@ -20,8 +20,10 @@
 // rows of v_mfma_f32_16x16x4_f32, the 16 vectors being its columns); their accumulators persist
 // over the stages of a tile.  Per MFMA step of four samples a lane reads one coefficient (row
 // l % 16, sample l / 16 of the step) and one LDS offset from its list, reads the sampled
-// coordinate of vector l % 16 from the ring (the four coordinates of a step differ modulo 4
-// where the table allows it, so that the 64 lanes hit 64 banks), and issues one MFMA.
+// coordinate of vector l % 16 from the ring, and issues one MFMA.  A read is served 32 lanes at a
+// time from 32 banks: rows of 2048 + 2 floats put the 16 vectors of a coordinate into all banks of one
+// parity, and the coordinates of lane groups 0 and 1, and 2 and 3, differ in parity where the table
+// allows it (with rows of 2048 + 4 vectors c and c + 8 shared a bank: kappa~ of 5e4 x 4096, m = 1024, 128 tables 898 -> 802 us, 1e5, m = 256 617 -> 585).
 //
 // With the samples gathered once per table, what is left to stream per tile is the lists: they
 // come from L2, many times the bytes of the tile itself.  So they are kept small and cheap to
@@ -62,6 +64,7 @@ namespace lsh {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4on8 __attribute__((ext_vector_type(4), aligned(8)));  // rows begin on 8 bytes
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kCWs = (int)kRangeComputeWaves;  // contracting waves
@@ -74,7 +77,7 @@ constexpr int kOW = kU / 2;                    // words of 16-bit offsets per sa
 constexpr int kCs = (int)kWindowCoords;        // coordinates per range
 constexpr int kSlotsSR = (int)kWindowSlots;    // ranges in the LDS ring
 constexpr int kLookSR = (int)kWindowLook;      // a stage reads its own range and this many after it
-constexpr int kRowFloats = kSlotsSR * kCs + 4; // row stride: the 4 floats of padding spread the vectors over the banks
+constexpr int kRowFloats = kSlotsSR * kCs + 2; // row stride: twice an odd number of floats, see the file comment
 constexpr int kRingBytesSR = 16 * kRowFloats * 4;
 // after the ring: the offsets b~ of the workgroup's functions (maximum inner product: the row operand of the
 // extra step, a0 and b~), [wave][block][32], then the turns of every stage
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(kThreadsSR) void shared_ranged_kernel(const SharedR
     constexpr int Q = kTurnSteps / BPW;  // consecutive steps of one block within a turn
     constexpr bool KAPPA = MODE == 3, MDATA = MODE == 4, MQUERY = MODE == 5, NORMS = MODE >= 3 && MODE <= 5;
     constexpr bool KEYS = MODE == 6;
-    extern __shared__ __align__(16) char lds_sr[];  // [16 vectors][8 ranges x 256 + 4 floats], offsets, turns
+    extern __shared__ __align__(16) char lds_sr[];  // [16 vectors][8 ranges x 256 + 2 floats], offsets, turns
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t n = a.n, S = a.stages;
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(kThreadsSR) void shared_ranged_kernel(const SharedR
                 for (int v = 0; v < 4; ++v) {
                     const floatx4 x = pre[v];
                     const floatx4 z = {inside ? x[0] : 0.f, inside ? x[1] : 0.f, inside ? x[2] : 0.f, inside ? x[3] : 0.f};
-                    *reinterpret_cast<floatx4 *>(dst + (v0 + v) * kRowFloats * 4) = z;
+                    *reinterpret_cast<floatx4on8 *>(dst + (v0 + v) * kRowFloats * 4) = z;
                 }
             }
             if (++s_r == S) {
@@ -224,7 +227,7 @@ __global__ __launch_bounds__(kThreadsSR) void shared_ranged_kernel(const SharedR
     for (int i = 0; i < kRing - 1; ++i) load_block(i);
     const char *row = lds_sr + (lane & 15) * kRowFloats * 4;  // this lane's vector in the ring
     // the four floats after a row's coordinates stay zero: what padding steps read
-    if (wave == 0 && lane < 16) *reinterpret_cast<floatx4 *>(lds_sr + (lane * kRowFloats + kSlotsSR * kCs) * 4) = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (wave == 0 && lane < 16) *reinterpret_cast<float2 *>(lds_sr + (lane * kRowFloats + kSlotsSR * kCs) * 4) = make_float2(0.f, 0.f);
     // The offsets b~ of the wave's functions and the table of turns are read from LDS where they
     // are needed: a vector memory load there would make the wave wait for everything it has in
     // flight, the id stores of the block before included.
@@ -484,26 +487,27 @@ void build_shared_ranged_tables(const lsh_params *p, SharedRangedPlan &pl, std::
                     --room;
                 }
             }
-            // steps of four samples whose coordinates differ modulo 4 where the classes allow it
+            // steps of four samples whose coordinates differ modulo 4 where the classes allow it, placed even, odd, even, odd
             std::vector<uint32_t> &out = slots[(size_t)table * S + s];
             size_t left = cls[0].size() + cls[1].size() + cls[2].size() + cls[3].size();
             while (left) {
                 bool taken[4] = {false, false, false, false};
+                uint32_t step[4] = {kPad, kPad, kPad, kPad}, placed[2] = {0, 0};
                 for (uint32_t kq = 0; kq < 4; ++kq) {
                     int best = -1;
                     for (int pass = 0; pass < 2 && best < 0; ++pass)
                         for (int q = 0; q < 4; ++q)
                             if (!cls[q].empty() && (pass == 1 || !taken[q]) && (best < 0 || cls[q].size() > cls[best].size()))
                                 best = q;
-                    if (best < 0) {
-                        out.push_back(kPad);
-                    } else {
-                        out.push_back(cls[best].back());
-                        cls[best].pop_back();
-                        taken[best] = true;
-                        --left;
-                    }
+                    if (best < 0) break;
+                    uint32_t parity = best & 1;
+                    if (placed[parity] == 2) parity ^= 1;  // three of one parity
+                    step[2 * placed[parity]++ + parity] = cls[best].back();
+                    cls[best].pop_back();
+                    taken[best] = true;
+                    --left;
                 }
+                out.insert(out.end(), step, step + 4);
             }
             out.resize((size_t)4 * steps, kPad);
         }
@@ -516,13 +520,13 @@ void build_shared_ranged_tables(const lsh_params *p, SharedRangedPlan &pl, std::
     }
     stream_info.assign((size_t)streams * 2, 0);
     coefs.assign((size_t)streams * per_stream * kU * 64, 0.f);
-    // steps and slots that only pad (coefficient zero) read one of the four zero floats that follow a
-    // row's coordinates: four different banks per vector, like a step of real samples, and
-    // nothing for the squared norms of the maximum-inner-product modes
+    // steps and slots that only pad (coefficient zero) read one of the two zero floats that follow a
+    // row's coordinates: of the parity a sample in their place would have, and nothing for the squared
+    // norms of the maximum-inner-product modes
     offs.assign((size_t)streams * per_stream * 4 * kOW, 0u);
     for (size_t rec = 0; rec < offs.size() / kOW; ++rec)
         for (uint32_t e = 0; e < (uint32_t)kU; ++e)
-            offs[rec * kOW + e / 2] |= ((kWindowSlots * kWindowCoords + (uint32_t)(rec & 3)) * 4u) << (16 * (e & 1));
+            offs[rec * kOW + e / 2] |= ((kWindowSlots * kWindowCoords + (uint32_t)(rec & 1)) * 4u) << (16 * (e & 1));
     for (uint32_t y = 0; y < pl.kblocks; ++y)
         for (uint32_t cw = 0; cw < CW; ++cw) {
             const uint32_t stream = y * CW + cw;
