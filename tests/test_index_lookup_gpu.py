@@ -41,6 +41,21 @@ def test_probe_finds_both_ends_of_every_bucket(lsh, N, L, distinct):
                 assert np.array_equal(count[:, l].cpu().numpy().view(np.uint32), end - first), l
 
 
+@pytest.mark.parametrize("N,L,Q", [(70001, 9, 1821), (66000, 8, 2049), (70001, 130, 128)])
+def test_probe_table_after_table(lsh, N, L, Q):
+    """Tables that are more than an L2 and many queries: a table's lookups together, the tables dealt to the XCDs."""
+    rng = np.random.default_rng(N + L)
+    keys = rng.integers(0, 3 * N, size=(N, L)).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    asked = rng.integers(0, 3 * N, size=(Q, L)).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    table = np.sort(keys, axis=0)
+    with lsh.LshIndex(torch.as_tensor(keys.view(np.int64), device="cuda")) as ix:
+        start, count = (t.cpu().numpy().view(np.uint32) for t in ix.probe(torch.as_tensor(asked.view(np.int64), device="cuda")))
+    for l in range(L):
+        first = np.searchsorted(table[:, l], asked[:, l], side="left")
+        assert np.array_equal(start[:, l], first), l
+        assert np.array_equal(count[:, l], np.searchsorted(table[:, l], asked[:, l], side="right") - first), l
+
+
 # n: fewer pieces than a group of 8 lanes, partial pieces, several turns of a wave, around and above
 # the largest query kept in LDS; Q on each side of 256, 768 and 1024 queries, soon done or not
 @pytest.mark.parametrize("n,N,L,Q,distinct,shift", [(4, 50, 1, 3, 7, 0), (24, 5000, 3, 257, 4, 0), (30, 3000, 5, 20, 2, 0),
