@@ -13,7 +13,7 @@
 // Splitters from a sample, not the keys' top bits: keys of few functions, or of one, differ in their low bits
 // only.  A key that fills a bucket of the sample is kept from its neighbours by a second splitter right
 // above it.  How well the sample was met costs time only: a bucket that LDS does not hold is sorted part by part.
-// Measured, the radix sort -> this, us: 1e6 x 32 keys of the SIFT shape 2630 -> 900 (splitters 49, tiles 219, buckets 585 at 61 % of
+// Measured, the radix sort -> this, us: 1e6 x 32 keys of the SIFT shape 2630 -> 890 (splitters 49, tiles 206, buckets 585 at 61 % of
 // the issue slots, the larger ones 31), random keys 1e6 x 2 227 -> 137, 1e5 x 64 625 -> 230, 1e4 x 32 214 -> 77, 1000 x 64
 // 169 -> 59, one key 1e6 times x 32 2160 -> 485.  Up to 2^20 pairs a table (1048576 x 8: 670 -> 291): beyond that a tile has more
 // buckets, or a bucket more pairs, than a workgroup has room for, and the radix sort stays (1.1e6 x 8: 770).
@@ -25,8 +25,9 @@ namespace lsh {
 namespace {
 
 // Tiles: 4096 rows, so that a row's number in its tile takes 16 bits.  Four tables a workgroup: pieces of 32 bytes of a
-// row, all loaded before the first is ranked.
-constexpr uint32_t kTileThreads = 1024, kTileSlots = 4, kTileRows = kTileThreads * kTileSlots, kTileColumns = 4;
+// row, all loaded before the first is ranked.  Eight rows a thread: with four, and twice the threads, some of their keys do
+// not fit the 64 registers (219 us instead of 206, and 65 MB of scratch memory written).
+constexpr uint32_t kTileThreads = 512, kTileSlots = 8, kTileRows = kTileThreads * kTileSlots, kTileColumns = 4;
 // Buckets: 2048 pairs and less on average, up to 4096 in LDS, three workgroups a CU.  A workgroup of four waves: what a pass
 // costs beside the ranking of the pairs, it costs once a wave.  (256 buckets of twice the size, two workgroups of 16 waves: 95
 // registers' worth of pairs in 64.)
@@ -400,7 +401,7 @@ size_t list_bytes(uint64_t N, uint32_t L, uint32_t buckets) { return 8 + (size_t
 // and the ranking, some 100 vector instructions a pair; the loads of all four columns are in flight before
 // the first is ranked.  The workgroups of a tile run on the same XCD: they read the same lines.
 template <bool PAIRS>
-__global__ __launch_bounds__(kTileThreads, 8) void sort_tiles(const uint64_t *__restrict__ keys, uint32_t L, uint32_t groups,
+__global__ __launch_bounds__(kTileThreads, 4) void sort_tiles(const uint64_t *__restrict__ keys, uint32_t L, uint32_t groups,
                                                               uint32_t bucket_bits, const SortedTiles out,
                                                               BucketList *__restrict__ medium,
                                                               BucketList *__restrict__ large) {
