@@ -467,9 +467,10 @@ class Bench:
         build_ms = sum(builds) / len(builds)
         base = {"workload": wl.name, "N": N, "L": L, "dtype": "u64"}
         out.append(dict(base, call="lsh_index_build", ms=build_ms, pairs_per_s=N * L / (build_ms * 1e-3),
-                        # 8 passes of 8 bits over <key, id> pairs: per pass the keys are read for the histogram (8 B)
-                        # and the pairs are read and written (12 + 12 B)
-                        roofline=hbm_roofline(N * L * 8 * 32, build_ms)))
+                        # up to 2^20 vectors by buckets: the keys are read (8 B), the pairs written and read as key and place
+                        # in the tile (10 + 10 B) and written as <key, id> (12 B); beyond, 8 passes of 8 bits, each of which
+                        # reads the keys (8 B) and reads and writes the pairs (12 + 12 B)
+                        roofline=hbm_roofline(N * L * (40 if N <= 1 << 20 else 8 * 32), build_ms)))
         out.append(dict(base, call="lsh_index_probe", queries=Q, ms=probe_ms, parity=parity))
         out.append(dict(base, call="lsh_index_nearest", queries=Q, ms=nearest_ms, candidates=candidates,
                         distinct_candidates=distinct, dtype="f32", queries_whose_source_vector_is_returned=found_source,
