@@ -57,6 +57,7 @@
 #include <vector>
 #include <type_traits>
 
+#include "ranged_few.h"
 #include "sampled_common.h"
 
 namespace lsh {
@@ -317,11 +318,7 @@ __global__ __launch_bounds__(kThreads) void sampled_ranged_kernel(const SampledA
 // what is between them at n = 4096, on as many CUs as the tile has sets of functions.  Here a workgroup brings four
 // vectors in whole, all loads in flight at once and one barrier behind them, and its waves then work through the
 // lists of a set of 64 functions each, without another one; the same lists in the same order, so the same
-// sums.  An entry names a slot of the ring: the range it means is the one among those readable in its stage, s .. s + 6, that has the slot.
-// [coordinate][4 vectors] floats of LDS, a tile's stages of 256 coordinates: up to kFewStages.
-constexpr uint32_t kFewStages = 160 * 1024 / (kC * 16), kFewAhead = 8;
-typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
-
+// sums.  [coordinate][4 vectors] floats of LDS; where an entry's coordinate is, and the order of the quads: ranged_few.h.
 template <int EP, bool VEC>
 __global__ __launch_bounds__(512) void ranged_few_kernel(const SampledArgs a, const uint32_t *__restrict__ barriers,
                                                          const uint2 *__restrict__ streams, uint32_t groups,
@@ -410,43 +407,30 @@ __global__ __launch_bounds__(512) void ranged_few_kernel(const SampledArgs a, co
             stage = __builtin_amdgcn_readlane(stages, 63);
             counts = bar[min(block + 64 + lane, blocks - 1)];
         }
-        // 1024 x (range modulo 8) + coordinate -> 256 x range + coordinate, two numbers at a time.  (Padding entries name
-        // the stage's own slot: LDS holds zeros for stages without a range.)
         const uint32_t now = __builtin_amdgcn_readlane(stages, block & 63);
         const uint32_t pair[2] = {slot[d].x, slot[d].y};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const ushortx2 since = __builtin_bit_cast(ushortx2, pair[h]) - (unsigned short)(now << 10);
-            const ushortx2 far = (since & (unsigned short)0x1C00) >> (unsigned short)2;
-            const uint32_t at = __builtin_bit_cast(uint32_t, (since & (unsigned short)0xFF) + far + (unsigned short)(now << 8));
+            const uint32_t at = few_slots(pair[h], now);
             x[d & 1][2 * h] = *reinterpret_cast<const floatx4 *>(lds + ((at & 0xFFFF) << 4));
             x[d & 1][2 * h + 1] = *reinterpret_cast<const floatx4 *>(lds + (at >> 16 << 4));
         }
     };
-    read_quad(0, 0);
-    // No test around a request: the compiler's count of those in flight is then exact (with tests it waited for the newest one,
-    // a trip to L2 a quad).  Quads beyond the last one are the last one again, times zero.
-    auto eight = [&](auto last_tag, uint32_t q0) __attribute__((always_inline)) {
-#pragma unroll
-        for (uint32_t d = 0; d < kFewAhead; ++d) {
-            const uint32_t q = q0 + d;
-            // the reads of a quad go out ahead of the multiply-adds of the quad before
-            __builtin_amdgcn_sched_barrier(0);
-            read_quad(q + 1, (d + 1) % kFewAhead);
-            __builtin_amdgcn_sched_barrier(0);
-            const bool real = !decltype(last_tag)::value || q < quads;
-            const float c[4] = {real ? __uint_as_float(coef[d].x) : 0.f, real ? __uint_as_float(coef[d].y) : 0.f,
-                                real ? __uint_as_float(coef[d].z) : 0.f, real ? __uint_as_float(coef[d].w) : 0.f};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[0][r] = fmaf(c[e], x[d & 1][e][r], acc[0][r]);
-            if constexpr (!decltype(last_tag)::value) request(q + kFewAhead, d);
-        }
+    auto read = [&](uint32_t q, int d) __attribute__((always_inline)) {
+        // the reads of a quad go out ahead of the multiply-adds of the quad before
+        __builtin_amdgcn_sched_barrier(0);
+        read_quad(q, d);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    uint32_t q0 = 0;
-    for (; q0 + kFewAhead < quads; q0 += kFewAhead) eight(std::false_type{}, q0);
-    eight(std::true_type{}, q0);
+    auto multiply = [&](uint32_t, int d) __attribute__((always_inline)) {
+        const float c[4] = {__uint_as_float(coef[d].x), __uint_as_float(coef[d].y), __uint_as_float(coef[d].z),
+                            __uint_as_float(coef[d].w)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[0][r] = fmaf(c[e], x[d & 1][e][r], acc[0][r]);
+    };
+    few_quads(quads, read, multiply, request);
     finish<4, 1, EP>(a, row0, j, acc, bias, key_pow);
 }
 

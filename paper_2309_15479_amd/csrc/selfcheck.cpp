@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "lsh_internal.h"
+#include "ranged_few.h"
 
 namespace lsh {
 namespace {
@@ -131,6 +132,62 @@ double walk_ranged(const lsh_params *p, const std::vector<double> &v) {
     return compare(p, v, walked);
 }
 
+double walk_ranged_few(const lsh_params *p, const std::vector<double> &v) {
+    // Follows every wave of the kernel for few vectors through the list of its set of functions, in the kernel's own order of
+    // quads and with its own arithmetic of slots: whole vectors in LDS, the coordinates of all stages side by side and zeros
+    // beyond the last.  Whatever the kernel reads must lie in that array, also what it would not use.
+    const SampledPlan &pl = p->plan;
+    std::vector<uint32_t> words, barriers, info;
+    build_ranged_tables(p, words, barriers, info);
+    const uint32_t CW = kRangeComputeWaves, fpt = pl.fpt, qpf = pl.qpf, U = fpt * qpf;
+    const uint32_t bar_stride = (uint32_t)(barriers.size() / pl.kblocks), in_lds = pl.stages * kWindowCoords;
+    const size_t block_words = (size_t)U * 64 * 6, off_base = (size_t)U * 64 * 4;
+    std::vector<double> walked(p->k, 0.0);
+    bool inside = true;
+    for (uint32_t set = 0; set < (p->k + 63) / 64; ++set) {
+        const uint32_t y = set / (CW * fpt), f = set / CW % fpt, stream = y * CW + set % CW;
+        const uint32_t first = info[(size_t)stream * 2], blocks = info[(size_t)stream * 2 + 1], quads = blocks * qpf;
+        if (!quads) return INFINITY;
+        const uint32_t *bar = &barriers[(size_t)y * bar_stride];
+        std::vector<uint32_t> stage_of(blocks + kFewAhead);
+        for (uint32_t b = 0, stage = 0; b < stage_of.size(); ++b) stage_of[b] = stage += bar[std::min(b, blocks - 1)];
+        uint32_t asked[kFewAhead];
+        double x[2][4][64];
+        auto quad = [&](uint32_t q, size_t &coefs, size_t &slots) {
+            const size_t block = (size_t)(first + q / qpf) * block_words, of_block = f * qpf + q % qpf;
+            coefs = block + of_block * 256;
+            slots = block + off_base + of_block * 128;
+        };
+        auto request = [&](uint32_t q, uint32_t d) { asked[d] = std::min(q, quads - 1); };
+        auto read = [&](uint32_t q, uint32_t d) {
+            size_t coefs, slots;
+            quad(asked[d], coefs, slots);
+            for (uint32_t l = 0; l < 64; ++l)
+                for (uint32_t e = 0; e < 4; ++e) {
+                    const uint32_t pair = few_slots(words[slots + l * 2 + e / 2], stage_of[q / qpf]);
+                    const uint32_t at = pair >> (16 * (e % 2)) & 0xFFFFu;
+                    if (at >= in_lds) inside = false;
+                    x[d & 1][e][l] = at < p->n ? v[at] : 0.0;
+                }
+        };
+        auto multiply = [&](uint32_t q, uint32_t d) {
+            if (asked[d] != q) inside = false;
+            size_t coefs, slots;
+            quad(asked[d], coefs, slots);
+            for (uint32_t l = 0; l < 64; ++l)
+                for (uint32_t e = 0; e < 4; ++e) {
+                    float c;
+                    std::memcpy(&c, &words[coefs + l * 4 + e], 4);
+                    const uint32_t j = set * 64 + l;
+                    if (j < p->k) walked[j] += (double)c * x[d & 1][e][l];
+                }
+        };
+        for (uint32_t d = 0; d < kFewAhead; ++d) request(d, d);
+        few_quads(quads, read, multiply, request);
+    }
+    return inside ? compare(p, v, walked) : INFINITY;
+}
+
 double walk_shared_ranged(const lsh_params *p, const std::vector<double> &v) {
     // Follows every contracting wave through one tile: stage after stage, turn after turn of the
     // list ring, step i of a turn on block i / (32 / bpw) of the wave; every offset is resolved
@@ -190,6 +247,10 @@ int lsh_params_check_lists(const lsh_params_t *p, uint64_t seed, double *worst) 
     try {
         const std::vector<double> v = lsh::test_vector(p->n, seed);
         *worst = shared ? lsh::walk_shared_ranged(p, v) : lsh::walk_ranged(p, v);
+        if (ranged && p->plan.stages <= lsh::kFewStages) {
+            const double few = lsh::walk_ranged_few(p, v);
+            if (!(few <= *worst)) *worst = few;
+        }
     } catch (const std::bad_alloc &) {
         return LSH_ERR_ALLOC;
     }

@@ -246,6 +246,19 @@ def test_list_tables_walked_on_the_host(n, k, m, w, seed, repl, L):
             assert p.check_lists(vector_seed) < 1e-14
 
 
+# What the kernel for few vectors reads of the same lists.  Its reads ahead end in a group of eight quads that the list need not
+# fill: shapes of 9, 17 and 33 to 40 ranges whose last list block opens a stage, and any others, one to four
+# functions a lane.
+@pytest.mark.parametrize("n,k,m", [(2101, 512, 48), (2196, 896, 71), (2216, 800, 105), (2390, 704, 69), (2245, 512, 48),
+                                   (4564, 560, 11), (4166, 624, 47), (2500, 4000, 70), (4096, 2048, 64), (4096, 2048, 1024)] + [
+    (low + (7919 * i) % (high - low), 512 + (389 * i) % 1600, 5 + (53 * i) % 130)
+    for low, high in ((2049, 2401), (4097, 4501), (8193, 10241)) for i in range(24)])
+def test_lists_as_few_vectors_read_them(n, k, m):
+    for seed in (5, 7):
+        with binding.LshParams(n, k, m, 8.0, seed) as p:
+            assert p.check_lists(1) < 1e-14
+
+
 @pytest.mark.parametrize("n,k,m,L,steps_max", [(4096, 2048, 64, 128, 18), (4096, 2048, 256, 128, 66),
                                                (4096, 2048, 1024, 128, 260), (16384, 4096, 512, 256, 141)])
 def test_shared_sample_schedule_needs_little_padding(n, k, m, L, steps_max):
