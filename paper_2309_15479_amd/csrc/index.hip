@@ -85,18 +85,23 @@ __global__ __launch_bounds__(256) void probe_kernel(const uint64_t *__restrict__
         probe_item<LANES>(sorted_keys + (item % L) * N, N, qkeys[item], start + item, count + item);
 }
 
-// The same table after table, every table on one XCD: what its lookups read of it first, they find in that L2.  For tables that
-// one L2 does not hold together, and enough queries; us, in turn / table after table, tables in no cache: 1000 queries in 64
+// The same table after table: what the lookups of a table read of it first, they find in an L2.  Eight tables at a time, one on
+// every XCD, while there are eight; the lookups of those that are left go to all XCDs, one table after the other (with a table on
+// each of some XCDs the others wait: 16000 queries in 11 tables of 4.8e4 13.1 us in turn, 16.8 so, 12.4 this way).
+// For tables that two L2s do not hold and enough queries; us, in turn / table after table, tables in no cache: 1000 queries in 64
 // tables of 1e5 20.3 / 19.7 (in a cache 15.1 / 10.7, between hashing and candidates 24.6 / 18), 4000 in 64 of 3e5 67 / 56,
-// 16000 in 64 of 1e5 160 / 107; 4000 in 16 of 2e4, 2.6 MB, 11.5 / 12.2: queries and results are read and written in pieces.
+// 16000 in 64 of 1e5 160 / 107.  In a cache, in turn : table after table, 500 to 64000 queries in 8 to 64 tables: of 4 MB
+// together 0.92 to 1.28, of 5.6 MB 0.94 to 1.32, of 8.8 MB 0.99 to 1.47, of 10 MB 0.98 to 1.50, of 16 MB 1.01 to 1.62: queries and results are read and written in pieces.
 constexpr uint64_t kTablesOfL2 = (4u << 20) / 8;  // keys
 template <uint32_t LANES>
 __global__ __launch_bounds__(256) void probe_tables_kernel(const uint64_t *__restrict__ sorted_keys, uint64_t N, uint32_t L,
                                                            const uint64_t *__restrict__ qkeys, uint32_t Q, uint32_t blocks,
                                                            uint32_t *__restrict__ start, uint32_t *__restrict__ count) {
-    const uint32_t l = blockIdx.x / 8 / blocks * 8 + blockIdx.x % 8;
-    const uint32_t q = (blockIdx.x / 8 % blocks * 256 + threadIdx.x) / LANES;
-    if (l >= L || q >= Q) return;
+    const uint32_t eights = L / 8 * 8, rest = blockIdx.x - eights * blocks;
+    const bool dealt = blockIdx.x < eights * blocks;
+    const uint32_t l = dealt ? blockIdx.x / 8 / blocks * 8 + blockIdx.x % 8 : eights + rest / blocks;
+    const uint32_t q = ((dealt ? blockIdx.x / 8 : rest) % blocks * 256 + threadIdx.x) / LANES;
+    if (q >= Q) return;
     const uint64_t item = (uint64_t)q * L + l;
     probe_item<LANES>(sorted_keys + l * N, N, qkeys[item], start + item, count + item);
 }
@@ -778,11 +783,11 @@ int lsh_index_probe(const lsh_index_t *ix, const uint64_t *d_qkeys, uint64_t Q, 
         hipLaunchKernelGGL(kernel, dim3((uint32_t)(wanted < (1u << 20) ? wanted : (1u << 20))), dim3(256), 0, s, ix->d_keys,
                            ix->N, ix->L, d_qkeys, items, d_start, d_count);
     };
-    const uint64_t blocks = (Q * kManyLanes + 255) / 256, tables = (ix->L + 7) / 8 * 8;
+    const uint64_t blocks = (Q * kManyLanes + 255) / 256;
     if (items <= kFewLookups) {
         launch(probe_kernel<kFewLanes>, kFewLanes);
-    } else if (ix->N * ix->L > kTablesOfL2 && Q >= 128 && ix->L >= 8 && Q < (1u << 24) && blocks * tables < (1u << 24)) {
-        hipLaunchKernelGGL(probe_tables_kernel<kManyLanes>, dim3((uint32_t)(blocks * tables)), dim3(256), 0, s, ix->d_keys, ix->N,
+    } else if (ix->N * ix->L > 2 * kTablesOfL2 && Q >= 128 && ix->L >= 8 && Q < (1u << 24) && blocks * ix->L < (1u << 24)) {
+        hipLaunchKernelGGL(probe_tables_kernel<kManyLanes>, dim3((uint32_t)(blocks * ix->L)), dim3(256), 0, s, ix->d_keys, ix->N,
                            ix->L, d_qkeys, (uint32_t)Q, (uint32_t)blocks, d_start, d_count);
     } else {
         launch(probe_kernel<kManyLanes>, kManyLanes);

@@ -41,9 +41,11 @@ def test_probe_finds_both_ends_of_every_bucket(lsh, N, L, distinct):
                 assert np.array_equal(count[:, l].cpu().numpy().view(np.uint32), end - first), l
 
 
-@pytest.mark.parametrize("N,L,Q", [(70001, 9, 1821), (66000, 8, 2049), (70001, 130, 128)])
+@pytest.mark.parametrize("N,L,Q", [(120001, 9, 1821), (132000, 8, 2049), (70001, 130, 128), (70100, 15, 1111), (48000, 23, 3000),
+                                   (70001, 9, 1821), (66000, 8, 2049)])
 def test_probe_table_after_table(lsh, N, L, Q):
-    """Tables that are more than an L2 and many queries: a table's lookups together, the tables dealt to the XCDs."""
+    """Tables that are more than two L2s and many queries: a table's lookups together, eight tables dealt to the XCDs at a
+    time and what is left over, one to seven, to all of them (the last two rows: tables too small for that)."""
     rng = np.random.default_rng(N + L)
     keys = rng.integers(0, 3 * N, size=(N, L)).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
     asked = rng.integers(0, 3 * N, size=(Q, L)).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
