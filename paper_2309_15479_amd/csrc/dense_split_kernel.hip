@@ -712,10 +712,12 @@ int launch_dense_split(const lsh_params *p, int ep, const float *d_data, uint64_
     // Blocks of 32 functions x 32 vectors, a wave each: up to one a SIMD, or two where the functions take more than one slice (their
     // waves all split the same tiles there).  us, tiles / blocks, ids of 2048 functions: 32 vectors 10.2 / 6.0, 300 11.5 / 6.3,
     // 1000 (2048 blocks) 12.0 / 9.4, 2000 13.0 / 14.9; of 512: 2000 11.2 / 6.5, 4000 11.8 / 9.3, 8000 13.0 / 14.8; of 128: 8000 8.7 / 6.6,
-    // 16000 9.0 / 9.2; of 64: 1000 7.2 / 6.3, 16000 8.3 / 7.0.
+    // 16000 9.0 / 9.2; of 64: 1000 7.2 / 6.3, 16000 8.3 / 7.0.  96 functions lie along one workgroup too, a wave of which is idle: 1000
+    // vectors 7.7 / 5.3, 9000 8.6 / 7.7 (along two, which split the same tiles twice and need a second round of waves from 8193
+    // vectors on, 6.1 and 8.9).
     const uint64_t blocks = (N + 31) / 32 * (p->k / 32);
     if (blocks <= (p->k >= 512 ? 2048 : 1024)) {
-        const int along = p->k >= 128 ? 4 : 2;
+        const int along = p->k > 64 ? 4 : 2;
         const uint32_t groups = (p->k + 32 * along - 1) / (32 * along);
         const uint64_t vector_groups = (N + 128 / along - 1) / (128 / along);
 #define LSH_FEW_CASE(E_, W_) \
