@@ -12,7 +12,19 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "liblsh.so")
 _lib = None
-_torch = None   # the module, once load_library() has run
+
+
+class _TorchAtFirstUse:
+    """In the place of torch until it is imported: by load_library, or else where a call needs it (ImportError if it is missing)."""
+
+    def __getattr__(self, name):
+        global _torch
+        import torch
+        _torch = torch
+        return getattr(torch, name)
+
+
+_torch = _TorchAtFirstUse()
 
 LSH_OK = 0
 SAMPLE_WITHOUT_REPLACEMENT = 0
@@ -233,15 +245,14 @@ class LshParams:
 def _stream(stream):
     if stream is not None:
         return ctypes.c_void_p(int(stream))
-    if _torch is None:
-        load_library()
     c = _torch._C
-    return ctypes.c_void_p(c._cuda_getCurrentRawStream(c._cuda_getDevice()))
+    try:
+        return ctypes.c_void_p(c._cuda_getCurrentRawStream(c._cuda_getDevice()))
+    except AttributeError:  # names of torch's own, not of its interface
+        return ctypes.c_void_p(_torch.cuda.current_stream().cuda_stream)
 
 
 def _dev_in(t, dtype, cols):
-    if _torch is None:
-        load_library()
     if not (isinstance(t, _torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
             and t.dim() == 2 and t.shape[1] == cols):
         raise ValueError(f"expected a contiguous CUDA tensor [N,{cols}] of {dtype}")

@@ -26,8 +26,13 @@ def lsh():
     (2100, 1024, 100, 64, 4.0),    # two, and blocks of two quads
     (2500, 4000, 70, 250, 4.0),    # two workgroups along the functions already
     (4096, 512, 64, 32, 8.0),      # one: nothing to deal out
-    (8200, 320, 100, 40, 4.0),     # forty stages: whole vectors of four just fit LDS
-    (10500, 200, 70, 25, 4.0),     # forty-eight: they do not
+    (2101, 512, 48, 32, 4.0),      # sixteen stages for nine ranges, the last list block opening one; odd n
+    (2196, 896, 71, 56, 4.0),      # the same, two functions a lane
+    (8200, 640, 100, 80, 4.0),     # forty stages: four whole vectors just fit LDS
+    (10240, 512, 33, 16, 4.0),     # forty ranges in them
+    (10500, 600, 70, 75, 4.0),     # forty-eight: they do not
+    (8200, 320, 100, 40, 4.0),     # less than 512 functions: no lists by ranges, tiles of one sub-tile
+    (10500, 200, 70, 25, 4.0),
     (960, 1024, 128, 64, 1.0),     # whole-vector tiles of eight sub-tiles
     (403, 250, 100, 125, 0.75),    # the same, nothing a multiple of anything
     (1500, 700, 100, 175, 2.0),    # tiles of four sub-tiles

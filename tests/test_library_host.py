@@ -3,6 +3,9 @@ header declares, rejects bad arguments, and draws tables bit-identical to the or
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import types
 
 import numpy as np
 import pytest
@@ -282,3 +285,37 @@ def test_list_check_needs_a_ranged_kernel():
         with pytest.raises(binding.LshError) as e:
             p.check_lists()
         assert e.value.status == -4
+
+
+_WITHOUT_TORCH = """
+import sys
+sys.modules["torch"] = None                 # any import of it fails
+from paper_2309_15479_amd import binding as b
+with b.LshParams(128, 64, 32, 4.0, 1) as p:
+    for call in (lambda: b.hash_fastlsh(p, None), lambda: b.hash_fastlsh_keys(p, None, 8), lambda: b.mips_kappa(p, None),
+                 lambda: b._stream(None)):
+        try:
+            call()
+        except ImportError:
+            continue
+        raise SystemExit("no ImportError")
+    del sys.modules["torch"]                # it is there after all
+    try:
+        b.hash_fastlsh(p, None)
+    except ValueError as e:
+        print(e)
+"""
+
+
+def test_calls_without_torch_say_so():
+    """The library loads without torch; a call on its tensors then fails as an import does, and works once torch is there."""
+    r = subprocess.run([sys.executable, "-c", _WITHOUT_TORCH], capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert r.returncode == 0 and "expected a contiguous CUDA tensor" in r.stdout, r.stdout + r.stderr
+
+
+def test_current_stream_without_the_private_names(monkeypatch):
+    torch = pytest.importorskip("torch")
+    binding.load_library()
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert binding._stream(None).value == 0x1230 and binding._stream(7).value == 7
