@@ -260,7 +260,7 @@ def _dev_in(t, dtype, cols):
 
 
 def _new(rows, cols, dtype, device):
-    return _torch.empty_strided((rows, cols), (cols, 1), dtype=dtype, device=device)
+    return _torch.empty_strided((rows, cols), (int(cols), 1), dtype=dtype, device=device)
 
 
 def _out(data, N, cols, dtype, out):

@@ -319,3 +319,12 @@ def test_current_stream_without_the_private_names(monkeypatch):
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
     assert binding._stream(None).value == 0x1230 and binding._stream(7).value == 7
+
+
+def test_numbers_of_tables_of_any_integer_type():
+    """What torch.empty takes as a size: results are allocated with strides, for which torch refuses a bool."""
+    torch = pytest.importorskip("torch")
+    binding.load_library()
+    for L in (3, np.int64(3), np.int32(3), torch.tensor(3), True):
+        out = binding._new(4, L, torch.int64, "cpu")
+        assert out.shape == (4, int(L)) and out.is_contiguous()
