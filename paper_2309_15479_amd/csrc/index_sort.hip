@@ -37,6 +37,7 @@ constexpr uint32_t kLargeThreads = 1024, kLargeSlots = 8, kLargeCap = kLargeThre
 constexpr uint32_t kMaxTiles = kMaxBuckets * kBucketMean / kTileRows;
 // The sample: 16 keys a bucket, as many as one workgroup sorts.
 constexpr uint32_t kSampleThreads = 1024, kSampleSlots = 8, kSamples = kSampleThreads * kSampleSlots / kMaxBuckets;
+static_assert(kSamples >= 2 && kSamples <= kBucketThreads, "a sample of more rows than there are");
 static_assert(kMaxTiles == 256 && kBucketThreads >= 256 && kTileRows <= 65536, "runs of a bucket: a thread each; numbers in a tile: 16 bits");
 
 struct Plan {
@@ -350,8 +351,7 @@ struct Sorter {
 __global__ __launch_bounds__(kSampleThreads) void sort_splitters(const uint64_t *__restrict__ keys, uint64_t N, uint32_t L,
                                                                  uint32_t buckets, uint64_t *__restrict__ cuts) {
     __shared__ Sorter<kSampleThreads, kSampleSlots> sh;
-    const uint32_t l = blockIdx.x, per_bucket = N < (uint64_t)buckets * kSamples ? (uint32_t)(N / buckets) : kSamples;
-    const uint32_t count = buckets * per_bucket;
+    const uint32_t l = blockIdx.x, count = buckets * kSamples;  // more rows than that: plan_of leaves 256 and more a bucket
     const Share share(count, kSampleThreads);
     uint64_t key[kSampleSlots], low = ~0ull, high = 0;
     uint32_t unused[kSampleSlots];
@@ -375,13 +375,13 @@ __global__ __launch_bounds__(kSampleThreads) void sort_splitters(const uint64_t 
     for (uint32_t i = 0; i < kSampleSlots; ++i)
         if (share.has(i)) sh.words[share.number(i)] = key[i];
     __syncthreads();
-    const uint32_t half = per_bucket / 2;
+    constexpr uint32_t half = kSamples / 2;
     for (uint32_t b = threadIdx.x + 1; b < buckets; b += kSampleThreads) {
-        const uint32_t at = b * per_bucket;
+        const uint32_t at = b * kSamples;
         const uint64_t cut = sh.words[at];
         // A key met at the splitter before too: it has a bucket of its own, which ends here.  One that lies more ahead of
         // this place than behind it goes to the bucket ahead.
-        const bool again = b > 1 && sh.words[at - per_bucket] == cut;
+        const bool again = b > 1 && sh.words[at - kSamples] == cut;
         const bool ahead = sh.words[at - half] == cut && sh.words[at + half] != cut;
         cuts[(uint64_t)l * buckets + b - 1] = (again || ahead) && cut != ~0ull ? cut + 1 : cut;
     }
