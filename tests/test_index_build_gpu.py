@@ -85,6 +85,49 @@ def test_tables_of_all_kinds_of_keys(lsh, kind, N, L):
         _check(lsh, ix, keys, f"{kind} N={N} L={L}")
 
 
+def _sampled_rows(N, L):
+    """The rows by whose keys the buckets are divided (index_sort.hip: plan_of, sort_splitters)."""
+    buckets = 1
+    while buckets * 2048 < N:
+        buckets *= 2
+    while buckets < 512 and buckets * L < 512 and buckets * 512 <= N:
+        buckets *= 2
+    j = np.arange(16 * buckets, dtype=np.uint64)
+    first, end = j * N // len(j), (j + 1) * N // len(j)
+    mixed = ((j * 0x9E3779B1 ^ 0x85EBCA6B) & 0xFFFFFFFF) * 0xC2B2AE35 & 0xFFFFFFFF
+    return torch.as_tensor((first + ((mixed ^ mixed >> np.uint64(15)) * (end - first) >> np.uint64(32))).astype(np.int64), device="cuda")
+
+
+# Keys of which the sample shows nothing: it meets key 0 only, and all others lie in the last bucket.  Some 6000 of them are
+# sorted by one workgroup of 1024 threads; more part by part: keys of all sizes, a key that alone is more than a
+# part, and a cluster a few thousand wide among some that are far off.  (300000 and 2^20 rows: 512 buckets, as many as there can be.)
+@pytest.mark.parametrize("N,L", [(20000, 3), (70001, 1), (300000, 1)])
+@pytest.mark.parametrize("kind", ["some", "all", "heavy", "cluster"])
+def test_tables_of_keys_that_the_sample_misses(lsh, kind, N, L):
+    print(f"{kind} N={N} L={L}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    keys = torch.randint(-2 ** 63, 2 ** 63 - 1, (N, L), generator=g, device="cuda")
+    below = lambda k: torch.randint(0, k, (N, L), generator=g, device="cuda")
+    if kind == "some":
+        keys[below(N) >= 6000] = 0
+    elif kind == "heavy":
+        keys[below(2) == 0] = -77
+    elif kind == "cluster":
+        keys = torch.where(below(1000) == 0, keys, 0x5EED5EED5EED5EED + below(5000))
+    keys[_sampled_rows(N, L)] = 0
+    with lsh.LshIndex(keys) as ix:
+        _check(lsh, ix, keys, f"{kind} N={N} L={L}")
+
+
+def test_largest_table_of_keys_that_the_sample_misses(lsh):
+    N = 2 ** 20
+    keys = torch.arange(N, device="cuda")[:, None] // 3 * 0x9E3779B9
+    keys[_sampled_rows(N, 1)] = 0
+    with lsh.LshIndex(keys.contiguous()) as ix:
+        _check(lsh, ix, keys, "2^20")
+
+
 def test_keys_on_no_boundary_of_16_bytes(lsh):
     keys = _random_keys(9001, 2, 4000, 3)
     moved = torch.empty(keys.numel() + 1, dtype=torch.int64, device="cuda")[1:].view(9001, 2)
