@@ -141,11 +141,12 @@ int lsh_params_get_schedule(const lsh_params_t *params, uint32_t *order, uint32_
 /*
  * Host-side check of the list tables of the kernels that work by coordinate ranges (the
  * sampled projection, Eq. 5, at large n; with one sample per table the matrix-core kernel for
- * large n): the tables are built as for the device and walked as the kernels walk them on a
+ * large n): the tables are built as for the device and walked as the kernels walk them, by the one for
+ * few vectors too where it takes the shape, on a
  * pseudo-random vector derived from seed, in double precision; *worst receives the largest
  * |walked - direct| / sum_i |a~_j[i] v[S_j[i]]| over the functions, direct being the sum of
  * Eq. 5 taken from the canonical tables (about 1e-16 when the tables are right, infinity when a
- * stream is inconsistent).  Needs no GPU.
+ * stream is inconsistent or a read would leave the tile).  Needs no GPU.
  * Errors: INVALID_ARG (null), UNSUPPORTED (the object's kernels use no such lists), ALLOC.
  */
 int lsh_params_check_lists(const lsh_params_t *params, uint64_t seed, double *worst);

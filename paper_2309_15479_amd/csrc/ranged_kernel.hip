@@ -595,10 +595,10 @@ int launch_ranged(const lsh_params *p, Epilogue ep, const float *d_data, uint64_
     const bool split = pl.fpt > 1 && ntiles * pl.kblocks * pl.fpt <= (uint64_t)p->num_cus;
     const dim3 grid((uint32_t)gx, pl.kblocks, split ? pl.fpt : 1);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // Fewer still: four vectors a workgroup, while every workgroup has a CU, with four sets of functions each, or eight.  us, one of
-    // the sets at a time / four / eight: 100 vectors of 4096 dimensions, 2048 functions, m = 64 17.8 / 11.5 / 12.0, m = 256
-    // 35 / 21 / 23, m = 1024 97 / 55 / 63; 200 of them at m = 64 18.5 / 15.7 / 12.4, 400 (beyond) 19.0 / 28 / 24; 300 vectors of 8192
-    // dimensions, 1024 functions, m = 128 30 / 34 / 18.
+    // Fewer still: four vectors a workgroup, while every workgroup has a CU, with four sets of functions each, or eight.  Keys, us, one
+    // of the sets at a time / four / eight: 100 vectors of 4096 dimensions, 2048 functions, m = 64 17.7 / 10.9 / 11.1, m = 256
+    // 35 / 20 / 22, m = 1024 98 / 55 / 63; 200 of them at m = 64 17.8 / 14.1 / 11.4, 400 (beyond) 18.7 / 26 / 22; 300 vectors of 8192
+    // dimensions, 1024 functions, m = 128 30 / 35 / 18.
     const uint64_t few_tiles = (N + 3) / 4, real_sets = (p->k + 63) / 64, cus = (uint64_t)p->num_cus;
     const uint32_t few_waves = few_tiles * ((real_sets + 3) / 4) <= cus ? 4 : 8;
     if (pl.stages <= kFewStages && few_tiles * ((real_sets + few_waves - 1) / few_waves) <= cus) {

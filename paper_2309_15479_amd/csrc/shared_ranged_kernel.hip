@@ -83,7 +83,7 @@ constexpr int kRingBytesSR = 16 * kRowFloats * 4;
 // extra step, a0 and b~), [wave][block][32], then the turns of every stage
 constexpr int kLdsLimitSR = 160 * 1024;
 constexpr int kAhead = 4;                      // register sets of a loading wave: a range is requested three stages before it is written
-static_assert(kRowFloats * 4 + 16 <= 65536, "list offsets are 16 bits");
+static_assert((kRowFloats - 1) * 4 < 65536, "list offsets are 16 bits, up to that of a row's second float of padding");
 static_assert(kSlotsSR == kLookSR + 2 && kSlotsSR % kAhead == 0, "ring geometry");
 
 // Returns v through an empty asm: values derived from it are recomputed where they are used
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kThreadsSR) void shared_ranged_kernel(const SharedR
 #pragma unroll
     for (int i = 0; i < kRing - 1; ++i) load_block(i);
     const char *row = lds_sr + (lane & 15) * kRowFloats * 4;  // this lane's vector in the ring
-    // the four floats after a row's coordinates stay zero: what padding steps read
+    // the two floats after a row's coordinates stay zero: what padding steps read (the next row begins behind them)
     if (wave == 0 && lane < 16) *reinterpret_cast<float2 *>(lds_sr + (lane * kRowFloats + kSlotsSR * kCs) * 4) = make_float2(0.f, 0.f);
     // The offsets b~ of the wave's functions and the table of turns are read from LDS where they
     // are needed: a vector memory load there would make the wave wait for everything it has in
