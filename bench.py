@@ -46,19 +46,19 @@ CSRC = os.path.join(ROOT, "paper_2309_15479_amd", "csrc")
 # source files still hash to the recorded values; otherwise `traffic` is null.  (FETCH_SIZE counts
 # 64 bytes per read request and these kernels fetch 128-byte lines: a lower bound, see the summary.)
 _KIB = 1024
-_RANGED = {"ranged_kernel.hip": "525ad148020e66df", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
+_RANGED = {"ranged_kernel.hip": "0d9a76a8d28d584e", "sampled_common.h": "9d6a9ea08ffad892", "schedule.cpp": "e034f03d037e1a15"}
 _STREAMED = {"sampled_kernel.hip": "df4f64747e76c3a2", "sampled_common.h": "9d6a9ea08ffad892"}
 _HALF = {"dense_half_kernel.hip": "2b20f5f3b2ee4dac", "dense_wide_tile.h": "4593d80dcc31c64a"}
 _SUMMARY = "profiles/hbm_traffic_all_workloads.md"
 MEASURED_TRAFFIC = {
-    "highdim/fastlsh/m64": (1770383 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/fastlsh/m256": (2222000 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
-    "highdim/fastlsh/m1024": (4061298 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m64": (1770607 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m256": (2214743 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
+    "highdim/fastlsh/m1024": (4058340 * _KIB, 1600000 * _KIB, _SUMMARY, _RANGED),
     "highdim/e2lsh": (4947326 * _KIB, 1633771 * _KIB, _SUMMARY, _HALF),
     "sift/fastlsh/m32": (250605 * _KIB, 2000000 * _KIB, _SUMMARY, _STREAMED),
     "gist/fastlsh/m128": (2375589 * _KIB, 4000000 * _KIB, _SUMMARY, _STREAMED),
     "gist/e2lsh": (3079718 * _KIB, 4080556 * _KIB, _SUMMARY, _HALF),
-    "angular/signs/m512": (57281386 * _KIB, 250027 * _KIB, _SUMMARY, _RANGED),
+    "angular/signs/m512": (60785258 * _KIB, 250018 * _KIB, _SUMMARY, _RANGED),
 }
 
 

@@ -14,9 +14,9 @@
 // only.  A key that fills a bucket of the sample is kept from its neighbours by a second splitter right
 // above it.  How well the sample was met costs time only: a bucket that LDS does not hold is sorted part by part.
 // Measured, the radix sort -> this, us: 1e6 x 32 keys of the SIFT shape 2630 -> 890 (splitters 49, tiles 206, buckets 585 at 61 % of
-// the issue slots, the larger ones 31), random keys 1e6 x 2 227 -> 137, 1e5 x 64 625 -> 230, 1e4 x 32 214 -> 77, 1000 x 64
-// 169 -> 59, one key 1e6 times x 32 2160 -> 485.  Up to 2^20 pairs a table (1048576 x 8: 670 -> 291): beyond that a tile has more
-// buckets, or a bucket more pairs, than a workgroup has room for, and the radix sort stays (1.1e6 x 8: 770).
+// the issue slots, the larger ones 31), random keys 1e6 x 2 227 -> 132, 1e5 x 64 625 -> 224, 1e4 x 32 214 -> 74, 1000 x 64
+// 169 -> 55, one key 1e6 times x 32 2160 -> 462.  Up to 2^20 pairs a table (1048576 x 8: 670 -> 285): beyond that a tile has more
+// buckets, or a bucket more pairs, than a workgroup has room for, and the radix sort stays (1.1e6 x 8: 765).
 #include "index_sort.h"
 
 #include <utility>

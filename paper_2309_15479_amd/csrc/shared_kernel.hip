@@ -23,7 +23,8 @@
 // 3, read coordinates of different parity.  (With n + 4 vectors c and c + 8 shared a bank whatever the coordinates.)
 // Tile rows begin on 8 bytes: their pieces are written as two halves by one instruction.  The 2 pad floats of a row are
 // kept zero: samples beyond m read the first.  kappa~ of 3e5 x 960 (m = 128, 64 tables) 429 -> 355 us, of 4e5 x 300 (m = 64, 32)
-// 413 -> 158; keys of those 494 -> 406, ids 513 -> 455.
+// 413 -> 158; keys of those 494 -> 406, ids 513 -> 455.  Launches of so few functions that the loads bind them gain nothing and lose
+// up to 2 %: data hashes of 2e5 x 960, 64 functions, m = 32 272 -> 278.
 //
 // Maximum inner product search (appendix): the transformed vectors are
 // P~(v) = (sqrt(kappa~^2 - ||S(v)||^2), S(v)) for data and Q~(u) = (0, S(u) / ||S(u)||) for
@@ -459,7 +460,7 @@ SharedPlan plan_shared(uint32_t n, uint32_t k, uint32_t m, uint32_t L) {
     struct Shape { uint32_t waves, rows, per_cu; };
     for (const Shape sh : {Shape{16, 128, 1}, Shape{16, 64, 1}, Shape{16, 32, 1}, Shape{16, 16, 1}}) {
         if (sh.rows == 16 && pl.ksteps != 32) continue;  // only the 32-step kernel walks single 16-vector blocks
-        if (2ull * sh.rows * (n + 4) * 4 * sh.per_cu > kLdsBudget) continue;
+        if (2ull * sh.rows * (n + 4) * 4 * sh.per_cu > kLdsBudget) continue;  // rows of n + 4 floats: ids at n = 128
         if ((uint64_t)sh.rows * (n / 4) > (uint64_t)kPre * sh.waves * 64) continue;
         pl.waves = sh.waves;
         pl.rows = sh.rows;
